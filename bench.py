@@ -19,7 +19,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
-KERNEL_SOURCES = ("paper_0908_4421_amd/csrc/kernels.hip", "paper_0908_4421_amd/csrc/imrt_internal.h")
+KERNEL_SOURCES = tuple("paper_0908_4421_amd/csrc/" + f for f in ("forward.hip", "adjoint.hip", "pass_common.h", "imrt_internal.h"))
 # counter summaries per workload (by phantom name)
 TRAFFIC_PROFILES = {
     "prostate_160x104x80_2.5mm_9field": os.path.join(ROOT, "profiles", "hbm_traffic_fwd_adj_prostate_160x104x80.txt"),

@@ -23,6 +23,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-Wall", "-Wno-unused-result", "-fvisibility=hidden"]
 SOURCES = {
     "api.hip": [],
+    "forward.hip": [],
+    "adjoint.hip": [],
     "kernels.hip": [],
     "build.hip": ["-ffp-contract=off"],
     "serve.hip": [],

@@ -319,7 +319,12 @@ int hip_error(hipError_t e, const char* what);
     if (e_ != hipSuccess) return imrt::hip_error(e_, #call); \
   } while (0)
 
-// launchers (kernels.hip)
+// launchers (forward.hip, adjoint.hip, kernels.hip)
+// check_launch: the error of the launch just made; clear_stale_error: drop an
+// error left behind by an unrelated earlier runtime call on this thread, so
+// that check_launch reports only the launch that follows
+int check_launch(const char* what);
+void clear_stale_error();
 // forward grid: wave-granular pass, fwd_grid_per_cu workgroups of 16 waves
 // (8 for several trials) per CU; workgroup-granular pass, 4x as many of 4 waves
 int forward_grid(const imrt_ctx* ctx, const imrt_dose* D, int ntrials = 1);
