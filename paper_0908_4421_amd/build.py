@@ -25,6 +25,8 @@ SOURCES = {
     "api.hip": [],
     "forward.hip": [],
     "adjoint.hip": [],
+    "onepass.hip": [],
+    "quads.hip": [],
     "kernels.hip": [],
     "build.hip": ["-ffp-contract=off"],
     "serve.hip": [],
@@ -39,7 +41,7 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def build(verbose: bool = False, jobs: int = 3) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     """Compile every HIP source for gfx950 and link libimrt.so; returns its path."""
     cc = hipcc()
     objdir = os.path.join(PKG, "_build")

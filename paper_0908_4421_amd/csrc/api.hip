@@ -1,10 +1,12 @@
 // C ABI of libimrt: argument validation, device memory, host preprocessing of
 // D (row blocks and adjoint chunks) and the stream-ordered solve driver.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <deque>
 #include <mutex>
 #include <new>
 #include <string>
@@ -60,6 +62,7 @@ int forward_grid_cap(imrt_ctx* ctx, const imrt_dose* D) {
       ctx->tune.fwd_wave = wave;
       g = std::max(g, forward_grid(ctx, D, nt));
     }
+  g = std::max(g, D->q_waves / 8);
   ctx->tune.fwd_wave = saved;
   return g;
 }
@@ -143,6 +146,14 @@ void apply_partition_targets(const imrt_ctx* ctx, imrt_dose* D) {
     partition_for_targets(D->nnz, ctx->tune.part_adj_wgs, ctx->tune.part_fwd_wgs, &D->adj_min_nnz, &D->fwd_bpw);
     D->fwd_waves = 8;
   }
+}
+
+// The dose's own partial sums, for every pass its partition may launch.
+int fit_partials(imrt_dose* D) {
+  dev_free(D->partials);
+  D->fwd_cap = forward_grid_cap(D->ctx, D);
+  D->partials_len = kMaxTrials * (D->fwd_cap + 1) + 16;
+  return dev_alloc(&D->partials, D->partials_len);
 }
 
 // Row blocks for the forward pass (at most kFwdPartNnz nonzeros and
@@ -295,6 +306,10 @@ int finish_dose(imrt_dose* D, const std::vector<int32_t>& row_ptr, const std::ve
     wg_cols[4 * v + 2] = static_cast<int32_t>(std::max<int64_t>(col_ptr[c], kw(v)));
     wg_cols[4 * v + 3] = static_cast<int32_t>(std::min<int64_t>(col_ptr[c + 1], kw(v + 1)));
   }
+  if (!D->qn.empty()) {   // a repartition: the quad form's blocks too
+    const int qrc = partition_quads(D);
+    if (qrc) return qrc;
+  }
   D->nblocks = static_cast<int32_t>(blocks.size()) - 1;
   D->nwblocks = static_cast<int32_t>(wblocks.size()) - 1;
   D->gaps.swap(gaps);
@@ -306,7 +321,6 @@ int finish_dose(imrt_dose* D, const std::vector<int32_t>& row_ptr, const std::ve
     dev_free(*p);
   dev_free(D->col_kind);
   dev_free(D->pieces);
-  dev_free(D->partials);
   int rc;
   if ((rc = dev_alloc(&D->block_row, blocks.size())) || (rc = dev_alloc(&D->block_k0, block_k0.size())) ||
       (rc = dev_alloc(&D->wblock_row, wblocks.size())) || (rc = dev_alloc(&D->wblock_k0, wblock_k0.size())) ||
@@ -331,9 +345,7 @@ int finish_dose(imrt_dose* D, const std::vector<int32_t>& row_ptr, const std::ve
   std::vector<uint8_t> kind(D->nb);
   for (int c = 0; c < D->nb; ++c) kind[c] = static_cast<uint8_t>(std::min(col_whi[c] - col_wlo[c], 2));
   IMRT_HIP(hipMemcpyAsync(D->col_kind, kind.data(), D->nb, hipMemcpyHostToDevice, s));
-  D->fwd_cap = forward_grid_cap(D->ctx, D);
-  D->partials_len = kMaxTrials * (D->fwd_cap + 1) + 16;
-  if ((rc = dev_alloc(&D->partials, D->partials_len))) return rc;
+  if ((rc = fit_partials(D))) return rc;
   IMRT_HIP(hipStreamSynchronize(s));
   return IMRT_OK;
 }
@@ -366,6 +378,10 @@ void free_dose(imrt_dose* D) {
   dev_free(D->col_wlo);
   dev_free(D->col_whi);
   dev_free(D->col_kind);
+  dev_free(D->q_col);
+  if (D->q_val) (void)hipFree(D->q_val);
+  dev_free(D->q_head);
+  dev_free(D->q_rec);
   dev_free(D->vox);
   dev_free(D->vscratch);
   dev_free(D->pieces);
@@ -388,12 +404,31 @@ void free_plan(imrt_plan* P) {
   dev_free(P->fwd_partials);
   dev_free(P->pieces);
   dev_free(P->pieces_col);
+  dev_free(P->q_acc);
+  dev_free(P->q_unit);
   dev_free(P->misc);
   dev_free(P->st);
   dev_free(P->trace);
   if (P->st_host) (void)hipHostFree(P->st_host);
   if (P->misc_host) (void)hipHostFree(P->misc_host);
   delete P;
+}
+
+// Column sums of passes of nt trials, at the matrix's present partition.
+int fit_quad(imrt_plan* P, int nt) {
+  const imrt_dose* D = P->dose;
+  if (D->q_waves == 0) return IMRT_OK;
+  int rc;
+  if (!P->q_unit && (rc = dev_alloc(&P->q_unit, kMaxTrials + (2 * kMaxTrials + 1) * static_cast<size_t>(step_grid(D->nb)))))
+    return rc;
+  const size_t need = static_cast<size_t>(quad_grid(D, nt)) * nt * D->nb;
+  if (need > P->q_acc_cap) {
+    dev_free(P->q_acc);
+    P->q_acc_cap = 0;
+    if ((rc = dev_alloc(&P->q_acc, need))) return rc;
+    P->q_acc_cap = need;
+  }
+  return IMRT_OK;
 }
 
 int plan_ready(const imrt_plan* P) {
@@ -422,7 +457,7 @@ int plan_fit(imrt_plan* P) {
     if ((rc = dev_alloc(&P->pieces, 2 * static_cast<size_t>(D->adj_grid)))) return rc;
     P->pieces_cap = D->adj_grid;
   }
-  return IMRT_OK;
+  return fit_quad(P, 1);
 }
 
 int plan_use(imrt_plan* P) {
@@ -430,21 +465,24 @@ int plan_use(imrt_plan* P) {
   return rc ? rc : plan_fit(P);
 }
 
-// Objective of the voxels the wave forward skips (the runs of rows without
-// nonzeros between its blocks): at zero dose each contributes
+// Objective of the voxels the wave forward (or the one-read pass) skips: the
+// runs of rows without nonzeros between its blocks (the rows of quads
+// without nonzeros).  At zero dose each contributes
 // F_j(0) = w_u min(-T_u, 0)^2 + w_o max(-T_o, 0)^2 (Eq. (1)), summed here in
 // float64 in row order, once per set of structures, penalties, targets and
 // partition.  The workgroup-wide forward visits every row: no constant then.
-double plan_skip_objective(imrt_plan* P) {
+double plan_skip_objective(imrt_plan* P, bool quads) {
   const imrt_dose* D = P->dose;
   if (P->ctx->tune.fwd_wave == 0) return 0.0;
-  if (P->gskip_epoch == D->part_epoch) return P->G_skip;
+  imrt_plan::Skip& K = P->skip[quads ? 1 : 0];
+  const auto& gaps = quads ? D->qgaps : D->gaps;
+  if (K.epoch == D->part_epoch) return K.G;
   // skipped rows per structure (kept until the structures or the partition change)
-  if (P->skip_hist_epoch != D->part_epoch) {
-    P->skip_hist.assign(kMaxStruct, 0);
-    for (const auto& gap : D->gaps)
-      for (int32_t j = gap.first; j < gap.second; ++j) ++P->skip_hist[P->sid_host[j]];
-    P->skip_hist_epoch = D->part_epoch;
+  if (K.hist_epoch != D->part_epoch) {
+    K.hist.assign(kMaxStruct, 0);
+    for (const auto& gap : gaps)
+      for (int32_t j = gap.first; j < gap.second; ++j) ++K.hist[P->sid_host[j]];
+    K.hist_epoch = D->part_epoch;
   }
   auto F0 = [](double Tu, double To, double wu, double wo) {
     const double under = std::fmin(0.0 - Tu, 0.0);
@@ -456,19 +494,19 @@ double plan_skip_objective(imrt_plan* P) {
   double G = 0.0;
   if (P->Tu_host.empty()) {
     for (int st = 0; st < P->nstruct; ++st)
-      if (P->skip_hist[st] > 0) {
+      if (K.hist[st] > 0) {
         const PenaltyDev& t = P->table_host[st];
-        G += static_cast<double>(P->skip_hist[st]) * F0(t.T_u, t.T_o, t.w_u, t.w_o);
+        G += static_cast<double>(K.hist[st]) * F0(t.T_u, t.T_o, t.w_u, t.w_o);
       }
   } else {
-    for (const auto& gap : D->gaps)
+    for (const auto& gap : gaps)
       for (int32_t j = gap.first; j < gap.second; ++j) {
         const PenaltyDev& t = P->table_host[P->sid_host[j]];
         G += F0(static_cast<double>(P->Tu_host[j]), static_cast<double>(P->To_host[j]), t.w_u, t.w_o);
       }
   }
-  P->G_skip = G;
-  P->gskip_epoch = D->part_epoch;
+  K.G = G;
+  K.epoch = D->part_epoch;
   return G;
 }
 
@@ -519,11 +557,54 @@ FwdArgs base_fwd(const imrt_dose* D) {
   return a;
 }
 
-// Residual (nv) and iterate (nb) buffers 0..count-1.
-int ensure_buffers(imrt_plan* P, int count) {
+// Arguments of the one-read pass over D, without a vector or outputs.
+FwdArgs base_quad(const imrt_dose* D, int mode) {
+  FwdArgs a{};
+  a.stream_cp = stream_policy(D->ctx, quad_bytes(D));
+  a.mode = mode;
+  a.storage = D->storage;
+  a.col_scale = D->col_scale;
+  a.nv = D->nv;
+  a.nb = D->nb;
+  a.q_head = D->q_head;
+  a.q_rec = D->q_rec;
+  a.q_col = D->q_col;
+  a.q_val = D->q_val;
+  a.q_nblocks = D->q_nblocks;
+  a.q_kmax = D->q_kmax;
+  a.q_rowsum = D->q_rowsum;
+  a.q_colsum = D->q_colsum;
+  return a;
+}
+
+// The plan's penalties and the bound |r| <= pen_w (|z| + pen_T) on the
+// residual they give: both sides of a voxel may be active.
+void set_quad_penalties(FwdArgs& a, const imrt_plan* P) {
+  set_plan_penalties(a, P);
+  double w = 0.0, T = 0.0;
+  for (const PenaltyDev& t : P->table_host) {
+    w = std::max(w, std::max(t.w_u, t.w_o));
+    T = std::max(T, std::max(std::fabs(t.T_u), std::fabs(t.T_o)));
+  }
+  a.pen_w = 2.0 * w;
+  a.pen_T = std::max(T, P->T_vox);
+}
+
+// Step (or reduction) over the column sums of a pass of nt trials.
+AdjArgs base_step(const imrt_dose* D, int nt) {
+  AdjArgs a{};
+  a.col_scale = D->col_scale;
+  a.nb = D->nb;
+  a.q_parts = quad_grid(D, nt);
+  return a;
+}
+
+// Residual (nv; unless the one-read pass needs none) and iterate (nb)
+// buffers 0..count-1.
+int ensure_buffers(imrt_plan* P, int count, bool residuals = true) {
   for (int i = 0; i < count; ++i) {
     int rc;
-    if (P->rbuf[i] == nullptr && (rc = dev_alloc(&P->rbuf[i], P->dose->nv))) return rc;
+    if (residuals && P->rbuf[i] == nullptr && (rc = dev_alloc(&P->rbuf[i], P->dose->nv))) return rc;
     if (P->xbuf[i] == nullptr && (rc = dev_alloc(&P->xbuf[i], P->dose->nb))) return rc;
   }
   return IMRT_OK;
@@ -533,6 +614,16 @@ int ensure_buffers(imrt_plan* P, int count) {
 // float64 total lands in P->misc[slot].
 int eval_forward(imrt_plan* P, const float* x, float* dose_out, float* r_out, int slot) {
   const imrt_dose* D = P->dose;
+  if (one_read(P->ctx, D, 1, P->nstruct)) {
+    FwdArgs a = base_quad(D, QM_EVAL);
+    set_quad_penalties(a, P);
+    a.x = x;
+    a.d_out = dose_out;
+    a.partials = P->fwd_partials;
+    const int grid = quad_grid(D, 1);
+    const int rc = launch_quad(P->ctx, a, 1, forward_waves(1, D->fwd_waves), grid);
+    return rc ? rc : launch_wave_sum(P->ctx, P->fwd_partials, quad_parts(D), P->misc + slot, plan_skip_objective(P, true));
+  }
   FwdArgs a = base_fwd(D);
   a.mode = FWD_EVAL;
   set_plan_penalties(a, P);
@@ -543,7 +634,7 @@ int eval_forward(imrt_plan* P, const float* x, float* dose_out, float* r_out, in
   const int grid = std::min(forward_grid(P->ctx, D), P->fwd_cap);
   int rc = launch_forward(P->ctx, D, a, 1, grid);
   if (rc) return rc;
-  return launch_sum(P->ctx, P->fwd_partials, grid, P->misc + slot, plan_skip_objective(P));
+  return launch_sum(P->ctx, P->fwd_partials, grid, P->misc + slot, plan_skip_objective(P, false));
 }
 
 AdjArgs base_adj(const imrt_dose* D) {
@@ -576,6 +667,30 @@ int adjoint_into(const imrt_ctx* ctx, const imrt_dose* D, const float* r, double
   a.out = out;
   a.scale = scale;
   return launch_adjoint(ctx, D, a, 1);
+}
+
+// Objective partials and gradient of x by the one-read pass, through the
+// given buffers; total receives G.
+int quad_gradient(imrt_plan* P, const float* x, float* g, double* parts, unsigned long long* acc, double* unit,
+                  double* total) {
+  const imrt_dose* D = P->dose;
+  FwdArgs a = base_quad(D, QM_GRAD);
+  set_quad_penalties(a, P);
+  a.x = x;
+  a.partials = parts;
+  a.q_acc = acc;
+  a.q_unit = unit;
+  const int grid = quad_grid(D, 1);
+  AdjArgs r = base_step(D, 1);
+  r.q_acc = acc;
+  r.q_unit = unit;
+  r.out = g;
+  r.scale = 2.0;
+  int rc;
+  if ((rc = launch_quad(P->ctx, a, 1, forward_waves(1, D->fwd_waves), grid)) ||
+      (rc = launch_wave_sum(P->ctx, parts, quad_parts(D), total, plan_skip_objective(P, true))))
+    return rc;
+  return launch_reduce(P->ctx, r, nullptr);
 }
 
 int fetch_misc(imrt_plan* P, int n) {
@@ -672,6 +787,10 @@ int* option_slot(imrt_ctx* ctx, const char* name, int64_t* lo) {
     *lo = 0;
     return &ctx->tune.voxel_tiles;
   }
+  if (n == "one_read") {
+    *lo = 0;
+    return &ctx->tune.one_read;
+  }
   if (n == "stream_nt") {
     *lo = 0;
     return &ctx->tune.stream_nt;
@@ -693,7 +812,7 @@ int imrt_ctx_set_option(imrt_ctx* ctx, const char* name, int64_t value) {
                      : (nm == "fwd_blocks_per_wave")                                         ? 1024
                      : (nm == "serve_adjoint_workgroups" || nm == "serve_forward_workgroups") ? 65536
                      : (nm == "serve_groups_per_poll")                                      ? 4096
-                     : (nm == "stream_nt")                                                  ? 2
+                     : (nm == "stream_nt" || nm == "one_read")                                                  ? 2
                                                                                  : (int64_t(1) << 30);
   if (value < lo || value > hi) return set_error(IMRT_EINVAL, std::string("value out of range for ") + name);
   *slot = static_cast<int>(value);
@@ -727,6 +846,8 @@ int imrt_build_dose_matrix(imrt_ctx* ctx, const imrt_geometry* geom, imrt_dtype 
   try {
     rc = build_phantom(ctx, geom, D);
     if (rc == IMRT_OK) rc = store16(D, storage);
+    if (rc == IMRT_OK) rc = build_quads(D);
+    if (rc == IMRT_OK) rc = fit_partials(D);
   } catch (const std::bad_alloc&) {
     rc = set_error(IMRT_ENOMEM, "host allocation failed");
   }
@@ -816,6 +937,8 @@ int imrt_dose_from_csr(imrt_ctx* ctx, int32_t nv, int32_t nb, int64_t nnz, const
     apply_partition_targets(ctx, D);
     rc = finish_dose(D, rp, cp);
     if (rc == IMRT_OK) rc = store16(D, storage);
+    if (rc == IMRT_OK) rc = build_quads(D);
+    if (rc == IMRT_OK) rc = fit_partials(D);
   } catch (const std::bad_alloc&) {
     rc = set_error(IMRT_ENOMEM, "host allocation failed");
   }
@@ -993,14 +1116,18 @@ int imrt_dose_apply(const imrt_dose* D, const float* x_dev, float* d_dev) {
   if (!D || !x_dev || !d_dev) return set_error(IMRT_EINVAL, "dose, x or d is NULL");
   int rc = use_device(D->ctx);
   if (rc) return rc;
-  FwdArgs a = base_fwd(D);
-  a.mode = FWD_PLAIN;
+  const bool quads = one_read(D->ctx, D, 1, 0);
+  FwdArgs a = quads ? base_quad(D, QM_PLAIN) : base_fwd(D);
+  if (!quads) a.mode = FWD_PLAIN;
   a.x = x_dev;
   a.d_out = D->vox ? D->vscratch : d_dev;
   a.partials = D->partials;
   // rows the wave blocks skip have no nonzeros: their dose is 0
-  if (!D->gaps.empty() && D->ctx->tune.fwd_wave && (rc = launch_zero(D->ctx, a.d_out, D->nv))) return rc;
-  if ((rc = launch_forward(D->ctx, D, a, 1, std::min(forward_grid(D->ctx, D), D->fwd_cap)))) return rc;
+  if (!(quads ? D->qgaps : D->gaps).empty() && D->ctx->tune.fwd_wave && (rc = launch_zero(D->ctx, a.d_out, D->nv)))
+    return rc;
+  rc = quads ? launch_quad(D->ctx, a, 1, forward_waves(1, D->fwd_waves), quad_grid(D, 1))
+             : launch_forward(D->ctx, D, a, 1, std::min(forward_grid(D->ctx, D), D->fwd_cap));
+  if (rc) return rc;
   return D->vox ? launch_permute(D->ctx, D->vscratch, D->vox, D->nv, d_dev, true) : IMRT_OK;
 }
 
@@ -1035,7 +1162,7 @@ int imrt_plan_create(imrt_ctx* ctx, const imrt_dose* dose, imrt_plan** out) {
   P->fwd_cap = grid;
   P->pieces_cap = dose->adj_grid;
   if ((rc = dev_alloc(&P->sid, dose->nv)) || (rc = dev_alloc(&P->table, kMaxStruct)) ||
-      (rc = ensure_buffers(P, 2)) || (rc = dev_alloc(&P->gk, dose->nb)) || (rc = dev_alloc(&P->vtmp, dose->nv)) ||
+      (rc = ensure_buffers(P, 2, dose->q_waves == 0)) || (rc = fit_quad(P, 1)) || (rc = dev_alloc(&P->gk, dose->nb)) || (rc = dev_alloc(&P->vtmp, dose->nv)) ||
       (rc = dev_alloc(&P->fwd_partials, static_cast<size_t>(kMaxTrials) * (grid + 1))) ||
       (rc = dev_alloc(&P->pieces, 2 * static_cast<size_t>(dose->adj_grid))) ||
       (rc = dev_alloc(&P->pieces_col, 2 * static_cast<size_t>(dose->nb))) || (rc = dev_alloc(&P->misc, 16)) ||
@@ -1079,8 +1206,7 @@ int imrt_set_structures(imrt_plan* P, const uint8_t* voxel_struct, int32_t nstru
   }
   IMRT_HIP(hipMemcpy(P->sid, ids.data(), D->nv, hipMemcpyHostToDevice));
   P->sid_host.swap(ids);
-  P->gskip_epoch = -1;
-  P->skip_hist_epoch = -1;
+  for (auto& K : P->skip) K.epoch = K.hist_epoch = -1;
   P->nstruct = nstruct;
   P->have_struct = true;
   P->have_pen = false;  // the table must match the new structure count
@@ -1111,7 +1237,7 @@ int imrt_set_penalties(imrt_plan* P, const imrt_penalty* table) {
     if (present[s]) wmax = std::max(wmax, std::max(t[s].w_u, t[s].w_o));
   IMRT_HIP(hipMemcpy(P->table, t.data(), sizeof(PenaltyDev) * P->nstruct, hipMemcpyHostToDevice));
   P->table_host.swap(t);
-  P->gskip_epoch = -1;
+  for (auto& K : P->skip) K.epoch = -1;
   P->w_max = wmax;
   P->have_pen = true;
   return IMRT_OK;
@@ -1126,7 +1252,8 @@ int imrt_set_voxel_targets(imrt_plan* P, const float* T_under, const float* T_ov
     dev_free(P->To_vox);
     P->Tu_host.clear();
     P->To_host.clear();
-    P->gskip_epoch = -1;
+    P->T_vox = 0.0;
+    for (auto& K : P->skip) K.epoch = -1;
     return IMRT_OK;
   }
   if (!T_under || !T_over) return set_error(IMRT_EINVAL, "give both T_under and T_over, or neither");
@@ -1152,7 +1279,10 @@ int imrt_set_voxel_targets(imrt_plan* P, const float* T_under, const float* T_ov
   IMRT_HIP(hipMemcpy(P->To_vox, T_over, sizeof(float) * nv, hipMemcpyHostToDevice));
   P->Tu_host.assign(T_under, T_under + nv);
   P->To_host.assign(T_over, T_over + nv);
-  P->gskip_epoch = -1;
+  P->T_vox = 0.0;
+  for (int j = 0; j < nv; ++j)
+    P->T_vox = std::max(P->T_vox, static_cast<double>(std::max(std::fabs(T_under[j]), std::fabs(T_over[j]))));
+  for (auto& K : P->skip) K.epoch = -1;
   return IMRT_OK;
 }
 
@@ -1164,7 +1294,7 @@ int imrt_evaluate_objective(imrt_plan* P, const float* x_dev, double* G_out, flo
   float* d_int = (dose_dev && D->vox) ? P->vtmp : dose_dev;
   if ((rc = use_device(P->ctx))) return rc;
   // rows the wave blocks skip have no nonzeros: their dose is 0
-  if (d_int && !D->gaps.empty() && P->ctx->tune.fwd_wave && (rc = launch_zero(P->ctx, d_int, D->nv))) return rc;
+  if (d_int && !(one_read(P->ctx, D, 1, P->nstruct) ? D->qgaps : D->gaps).empty() && P->ctx->tune.fwd_wave && (rc = launch_zero(P->ctx, d_int, D->nv))) return rc;
   if ((rc = eval_forward(P, x_dev, d_int, nullptr, 0))) return rc;
   if (dose_dev && D->vox && (rc = launch_permute(P->ctx, P->vtmp, D->vox, D->nv, dose_dev, true))) return rc;
   if ((rc = fetch_misc(P, 1))) return rc;
@@ -1176,9 +1306,13 @@ int imrt_gradient(imrt_plan* P, const float* x_dev, float* g_dev, double* G_out)
   int rc = plan_use(P);
   if (rc) return rc;
   if (!x_dev || !g_dev) return set_error(IMRT_EINVAL, "x or g is NULL");
-  if ((rc = use_device(P->ctx)) || (rc = eval_forward(P, x_dev, nullptr, P->rbuf[0], 0)) ||
-      (rc = adjoint_into(P->ctx, P->dose, P->rbuf[0], 2.0, g_dev)))
+  if ((rc = use_device(P->ctx))) return rc;
+  if (one_read(P->ctx, P->dose, 1, P->nstruct)) {
+    if ((rc = quad_gradient(P, x_dev, g_dev, P->fwd_partials, P->q_acc, P->q_unit, P->misc))) return rc;
+  } else if ((rc = ensure_buffers(P, 1)) || (rc = eval_forward(P, x_dev, nullptr, P->rbuf[0], 0)) ||
+             (rc = adjoint_into(P->ctx, P->dose, P->rbuf[0], 2.0, g_dev))) {
     return rc;
+  }
   if (G_out) {
     if ((rc = fetch_misc(P, 1))) return rc;
     *G_out = P->misc_host[0];
@@ -1213,6 +1347,25 @@ int imrt_gradient_noalloc(imrt_plan* P, const float* x_dev, float* g_dev, double
   double* parts = reinterpret_cast<double*>(base + off_part);
   double* pieces = reinterpret_cast<double*>(base + off_pieces);
   double* total = reinterpret_cast<double*>(base + off_total);
+  if (one_read(P->ctx, D, 1, P->nstruct)) {
+    // (no residual: objective partials, unit, total, then the column sums,
+    // whose size the partition bounds)
+    const size_t qgrid = static_cast<size_t>(quad_grid(D, 1));
+    double* head = reinterpret_cast<double*>(base);
+    const size_t off_acc = up(sizeof(double) * (static_cast<size_t>(quad_parts(D)) + 2));
+    const size_t qneed = off_acc + 8 * qgrid * static_cast<size_t>(D->nb);
+    if (qneed > IMRT_NOALLOC_SCRATCH_BYTES)
+      return set_error(IMRT_EINVAL, "imrt_gradient_noalloc: the column sums exceed the scratch");
+    if ((rc = quad_gradient(P, x_dev, g_dev, head + 2, reinterpret_cast<unsigned long long*>(base + off_acc), head + 1,
+                            head)))
+      return rc;
+    if (G_out) {
+      IMRT_HIP(hipMemcpyAsync(P->misc_host, head, sizeof(double), hipMemcpyDeviceToHost, P->ctx->stream));
+      IMRT_HIP(hipStreamSynchronize(P->ctx->stream));
+      *G_out = P->misc_host[0];
+    }
+    return IMRT_OK;
+  }
   // forward pass: residual and objective partials (every workgroup writes its
   // own partial and every row its residual, so nothing starts at zero)
   FwdArgs fa = base_fwd(D);
@@ -1222,7 +1375,7 @@ int imrt_gradient_noalloc(imrt_plan* P, const float* x_dev, float* g_dev, double
   fa.r_out = r;
   fa.partials = parts;
   if ((rc = launch_forward(P->ctx, D, fa, 1, grid)) ||
-      (rc = launch_sum(P->ctx, parts, grid, total, plan_skip_objective(P))))
+      (rc = launch_sum(P->ctx, parts, grid, total, plan_skip_objective(P, false))))
     return rc;
   // adjoint pass: g = 2 D^T r (pieces written by the workgroups that share a column)
   AdjArgs aa = base_adj(D);
@@ -1266,7 +1419,33 @@ int imrt_estimate_lambda0(imrt_plan* P, const float* v0_dev, int32_t iters, doub
   float* v = P->xbuf[0];
   float* w = P->gk;
   if ((rc = launch_normalize(C, v0_dev, D->nb, v, P->misc + 1))) return rc;
-  for (int it = 0; it <= iters; ++it) {
+  const bool quads = one_read(C, D, 1, P->nstruct);
+  if (quads) {
+    // D^T D v and its squared norm's partial sums in two launches; the next
+    // pass divides by the norm while it stages the vector
+    const int grid = quad_grid(D, 1), wv = forward_waves(1, D->fwd_waves), sg = step_grid(D->nb);
+    double* norm = P->q_unit + kMaxTrials;
+    FwdArgs a = base_quad(D, QM_POWER);
+    a.x = v;
+    a.partials = P->fwd_partials;
+    a.q_acc = P->q_acc;
+    a.q_unit = P->q_unit;
+    AdjArgs r = base_step(D, 1);
+    r.q_acc = P->q_acc;
+    r.q_unit = P->q_unit;
+    r.out = w;
+    r.scale = 1.0;
+    for (int it = 0; it < iters; ++it) {
+      if ((rc = launch_quad(C, a, 1, wv, grid)) || (rc = launch_reduce(C, r, norm))) return rc;
+      a.x = w;
+      a.norm = norm;
+      a.norm_parts = sg;
+    }
+    if ((rc = launch_quad(C, a, 1, wv, grid)) || (rc = launch_sum(C, P->fwd_partials, quad_parts(D), P->misc)) ||
+        (iters > 0 && (rc = launch_sum(C, norm, sg, P->misc + 1))))
+      return rc;
+  }
+  for (int it = 0; it <= iters && !quads; ++it) {
     FwdArgs a = base_fwd(D);
     a.mode = FWD_PLAIN;
     a.x = v;
@@ -1328,7 +1507,8 @@ int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev
   const imrt_dose* D = P->dose;
   imrt_ctx* C = P->ctx;
   hipStream_t s = C->stream;
-  if (forward_lds_bytes(D->nb, nt, P->nstruct, C->tune.fwd_wave != 0, D->fwd_st, D->fwd_waves) > C->max_lds)
+  const bool quads = one_read(C, D, nt, P->nstruct);
+  if (!quads && forward_lds_bytes(D->nb, nt, P->nstruct, C->tune.fwd_wave != 0, D->fwd_st, D->fwd_waves) > C->max_lds)
     return set_error(IMRT_EUNSUPPORTED, "nb * trials_per_pass exceeds the LDS budget of the forward pass");
 
   // x_1 >= 0 and finite (initialisation of the method)
@@ -1337,7 +1517,7 @@ int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev
   IMRT_HIP(hipStreamSynchronize(s));
   for (float v : xh)
     if (!(v >= 0.0f) || !std::isfinite(v)) return set_error(IMRT_EINVAL, "x_1 must be finite and >= 0");
-  if ((rc = ensure_buffers(P, nt + 1))) return rc;
+  if ((rc = ensure_buffers(P, nt + 1, !quads)) || (quads && (rc = fit_quad(P, nt)))) return rc;
   // the iterate buffers other than x_1's start zeroed (the forward pass
   // blends all candidates with 0/1 weights, so none may be non-finite)
   for (int j = 1; j <= nt; ++j) IMRT_HIP(hipMemsetAsync(P->xbuf[j], 0, sizeof(float) * D->nb, s));
@@ -1379,6 +1559,26 @@ int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev
 // state pointers, which depend on the pass).
 void solve_args(imrt_plan* P, int nt, int grid, int cap, FwdArgs& fa, AdjArgs& aa) {
   const imrt_dose* D = P->dose;
+  if (one_read(P->ctx, D, nt, P->nstruct)) {
+    fa = base_quad(D, QM_SOLVE);
+    fa.grid = grid;
+    set_quad_penalties(fa, P);
+    aa = base_step(D, nt);
+    for (int i = 0; i <= kMaxTrials; ++i) fa.xbuf[i] = aa.xbuf[i] = P->xbuf[i];
+    fa.partials = P->fwd_partials;
+    fa.q_acc = P->q_acc;
+    fa.q_unit = P->q_unit;
+    aa.q_acc = P->q_acc;
+    aa.q_unit = P->q_unit;
+    fa.q_steps = aa.q_steps = P->q_unit + kMaxTrials;
+    aa.out = P->gk;
+    aa.scale = 2.0;
+    aa.fwd_partials = P->fwd_partials;
+    aa.fwd_parts = quad_parts(D);
+    aa.trace = cap > 0 ? P->trace : nullptr;
+    aa.G_skip = plan_skip_objective(P, true);
+    return;
+  }
   fa = base_fwd(D);
   fa.mode = FWD_SOLVE;
   fa.grid = grid;
@@ -1407,7 +1607,23 @@ void solve_args(imrt_plan* P, int nt, int grid, int cap, FwdArgs& fa, AdjArgs& a
   aa.step_partials = P->fwd_partials + static_cast<size_t>(nt) * grid;
   aa.step_parts = 1;
   aa.trace = cap > 0 ? P->trace : nullptr;
-  aa.G_skip = plan_skip_objective(P);
+  aa.G_skip = plan_skip_objective(P, false);
+}
+
+// Workgroups of a solve's forward (or one-read) pass.
+int solve_grid(const imrt_plan* P, int nt) {
+  return one_read(P->ctx, P->dose, nt, P->nstruct) ? quad_grid(P->dose, nt)
+                                                    : std::min(forward_grid(P->ctx, P->dose, nt), P->fwd_cap);
+}
+
+// x_1 into the buffers a solve starts from: iterate 0, which in the one-read
+// pass is also the trial that the initial evaluation takes (x_k: buffer nt).
+hipError_t solve_start(imrt_plan* P, int nt, const float* x) {
+  const size_t bytes = sizeof(float) * P->dose->nb;
+  hipError_t e = hipMemcpyAsync(P->xbuf[0], x, bytes, hipMemcpyDeviceToDevice, P->ctx->stream);
+  if (e == hipSuccess && one_read(P->ctx, P->dose, nt, P->nstruct))
+    e = hipMemcpyAsync(P->xbuf[nt], x, bytes, hipMemcpyDeviceToDevice, P->ctx->stream);
+  return e;
 }
 
 int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_solve_result* res) {
@@ -1462,13 +1678,14 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
   if (e == hipSuccess) e = hipEventRecord(ev_start, s);
   if (e == hipSuccess) e = hipMemcpyAsync(P->st, &P->st_host[0], sizeof(SolverState), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(P->st + 1, &P->st_host[0], sizeof(SolverState), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(P->xbuf[0], x_dev, sizeof(float) * D->nb, hipMemcpyDeviceToDevice, s);
+  if (e == hipSuccess) e = solve_start(P, nt, x_dev);
   if (e != hipSuccess) {
     cleanup();
     return hip_error(e, "solve setup");
   }
 
-  const int grid = std::min(forward_grid(C, D, nt), P->fwd_cap);
+  const bool quads = one_read(C, D, nt, P->nstruct);
+  const int grid = solve_grid(P, nt);
   FwdArgs fa;
   AdjArgs aa;
   solve_args(P, nt, grid, cap, fa, aa);
@@ -1483,7 +1700,8 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
     if (r != hipSuccess) return hip_error(r, "hipEventCreate");
     fa.st_in = state_in();
     fa.st_out = state_out();
-    const int rr = launch_forward(C, D, fa, nt, grid, f0, f1);
+    const int rr = quads ? launch_quad(C, fa, nt, forward_waves(nt, D->fwd_waves), grid, f0, f1)
+                         : launch_forward(C, D, fa, nt, grid, f0, f1);
     ++pass;
     return rr;
   };
@@ -1493,7 +1711,7 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
     if (r != hipSuccess) return hip_error(r, "hipEventCreate");
     aa.st_in = state_in();
     aa.st_out = state_out();
-    const int rr = launch_adjoint(C, D, aa, nt, a0, a1);
+    const int rr = quads ? launch_step(C, aa, nt, a0, a1) : launch_adjoint(C, D, aa, nt, a0, a1);
     ++pass;
     return rr;
   };
@@ -1658,6 +1876,8 @@ struct BatchBuffers {
   AdjArgs* aargs = nullptr;
   int32_t* fslots = nullptr;
   int32_t* aslots = nullptr;
+  int32_t* qslots = nullptr;      // one-read passes and their steps
+  int32_t* sslots = nullptr;
   SolverState* poll = nullptr;    // pinned host, 2 slots of 2n states
   hipEvent_t ev_start = nullptr, ev_end = nullptr, ev_poll[2] = {nullptr, nullptr};
   hipGraph_t graph = nullptr;
@@ -1676,7 +1896,8 @@ struct BatchBuffers {
       if (e) (void)hipEventDestroy(e);
     if (poll) (void)hipHostFree(poll);
     for (void* p : {static_cast<void*>(st), static_cast<void*>(fargs), static_cast<void*>(aargs),
-                    static_cast<void*>(fslots), static_cast<void*>(aslots)})
+                    static_cast<void*>(fslots), static_cast<void*>(aslots), static_cast<void*>(qslots),
+                    static_cast<void*>(sslots)})
       if (p) (void)hipFree(p);
   }
 };
@@ -1704,6 +1925,7 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
   }
   if (C->tune.fwd_wave == 0) return set_error(IMRT_EUNSUPPORTED, "the batched solve needs fwd_wave = 1");
   std::vector<int> nt(n), cap(n), fgrid(n), agrid(n);
+  std::vector<char> quads(n);   // plans whose passes are one-read passes
   std::vector<SolverState> init(n);
   int rc;
   for (int i = 0; i < n; ++i) {
@@ -1739,13 +1961,16 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
   hipStream_t s = C->stream;
   std::vector<FwdArgs> fa(n);
   std::vector<AdjArgs> aa(n);
-  size_t lds = 0;
+  size_t lds = 0, qlds = 0;
   for (int i = 0; i < n; ++i) {
     imrt_plan* P = plans[i];
-    fgrid[i] = std::min(forward_grid(C, P->dose, nt[i]), P->fwd_cap);
-    agrid[i] = P->dose->adj_grid;
-    lds = std::max(lds, forward_lds_bytes(P->dose->nb, nt[i], P->nstruct, true, fst, fwv));
+    quads[i] = one_read(C, P->dose, nt[i], P->nstruct);
+    fgrid[i] = solve_grid(P, nt[i]);
+    agrid[i] = quads[i] ? step_grid(P->dose->nb) : P->dose->adj_grid;
+    if (quads[i]) qlds = std::max(qlds, quad_lds_bytes(P->dose->nb, nt[i], P->nstruct, QM_SOLVE));
+    else lds = std::max(lds, forward_lds_bytes(P->dose->nb, nt[i], P->nstruct, true, fst, fwv));
   }
+  const int qwv = forward_waves(nt[0], fwv);
   // the live plans' matrix streams share the last-level cache: their policy
   // follows the bytes of the distinct matrices of the unfinished plans
   // together, taken again whenever plans drop out
@@ -1755,7 +1980,7 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
     for (int i : live)
       if (std::find(seen.begin(), seen.end(), plans[i]->dose) == seen.end()) {
         seen.push_back(plans[i]->dose);
-        bytes += stream_bytes(plans[i]->dose);
+        bytes += quads[i] ? quad_bytes(plans[i]->dose) : stream_bytes(plans[i]->dose);
       }
     return stream_policy(C, bytes);
   };
@@ -1772,10 +1997,41 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
   std::vector<int> active(n);
   for (int i = 0; i < n; ++i) active[i] = i;
   batch_cp = live_policy(active);
-  std::vector<int32_t> fs, as;
-  batch_slots(active, fgrid, fs);
-  batch_slots(active, agrid, as);
-  if (dev_alloc(&B.fslots, fs.size()) || dev_alloc(&B.aslots, as.size())) return IMRT_ENOMEM;
+  // slot tables: {forward, adjoint, one-read pass, step}
+  using Tables = std::array<std::vector<int32_t>, 4>;
+  auto tables = [&](const std::vector<int>& live, Tables& t) {
+    std::vector<int> two, one;
+    for (int i : live) (quads[i] ? one : two).push_back(i);
+    batch_slots(two, fgrid, t[0]);
+    batch_slots(two, agrid, t[1]);
+    batch_slots(one, fgrid, t[2]);
+    batch_slots(one, agrid, t[3]);
+  };
+  Tables sl;
+  tables(active, sl);
+  int32_t** const dst[4] = {&B.fslots, &B.aslots, &B.qslots, &B.sslots};
+  for (int k = 0; k < 4; ++k)
+    if (dev_alloc(dst[k], std::max<size_t>(sl[k].size(), 1))) return IMRT_ENOMEM;
+  auto upload = [&](const Tables& t) {
+    hipError_t r = hipSuccess;
+    for (int k = 0; k < 4 && r == hipSuccess; ++k)
+      if (!t[k].empty()) r = hipMemcpyAsync(*dst[k], t[k].data(), sizeof(int32_t) * t[k].size(), hipMemcpyHostToDevice, s);
+    return r;
+  };
+  int count[4];
+  auto counts = [&](const Tables& t) {
+    for (int k = 0; k < 4; ++k) count[k] = static_cast<int>(t[k].size());
+  };
+  counts(sl);
+  auto passes = [&](bool second) -> int {   // the steps and adjoint passes, or the (one-read) forward passes
+    int r;
+    if (second) {
+      r = launch_adjoint_batch(C, B.aargs, B.aslots, count[1], nt[0], storage, batch_cp);
+      return r ? r : launch_step_batch(C, B.aargs, B.sslots, count[3], nt[0]);
+    }
+    r = launch_forward_batch(C, B.fargs, B.fslots, count[0], nt[0], fst, fwv, lds, batch_cp);
+    return r ? r : launch_quad_batch(C, B.fargs, B.qslots, count[2], nt[0], storage, qwv, qlds, batch_cp);
+  };
   std::vector<SolverState> st_host(2 * static_cast<size_t>(n));
   for (int i = 0; i < n; ++i) st_host[2 * i] = st_host[2 * i + 1] = init[i];
   hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&B.poll), sizeof(SolverState) * 4 * n, hipHostMallocDefault);
@@ -1787,16 +2043,14 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
   if (e == hipSuccess) e = hipMemcpyAsync(B.st, st_host.data(), sizeof(SolverState) * 2 * n, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(B.fargs, fa.data(), sizeof(FwdArgs) * n, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(B.aargs, aa.data(), sizeof(AdjArgs) * n, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(B.fslots, fs.data(), sizeof(int32_t) * fs.size(), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(B.aslots, as.data(), sizeof(int32_t) * as.size(), hipMemcpyHostToDevice, s);
-  for (int i = 0; i < n && e == hipSuccess; ++i)
-    e = hipMemcpyAsync(plans[i]->xbuf[0], x_dev[i], sizeof(float) * plans[i]->dose->nb, hipMemcpyDeviceToDevice, s);
+  if (e == hipSuccess) e = upload(sl);
+  for (int i = 0; i < n && e == hipSuccess; ++i) e = solve_start(plans[i], nt[i], x_dev[i]);
   // the host vectors above must outlive the copies
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_error(e, "batch setup");
 
   // initial evaluation G(x_1) of every plan
-  if ((rc = launch_forward_batch(C, B.fargs, B.fslots, static_cast<int>(fs.size()), nt[0], fst, fwv, lds, batch_cp))) {
+  if ((rc = passes(false))) {
     (void)hipStreamSynchronize(s);
     return rc;
   }
@@ -1816,9 +2070,8 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
     if (r != hipSuccess) return hip_error(r, "hipStreamBeginCapture");
     int lrc = IMRT_OK;
     for (long long k = 0; k < K && lrc == IMRT_OK; ++k) {
-      lrc = launch_adjoint_batch(C, B.aargs, B.aslots, static_cast<int>(as.size()), nt[0], storage, batch_cp);
-      if (lrc == IMRT_OK)
-        lrc = launch_forward_batch(C, B.fargs, B.fslots, static_cast<int>(fs.size()), nt[0], fst, fwv, lds, batch_cp);
+      lrc = passes(true);
+      if (lrc == IMRT_OK) lrc = passes(false);
     }
     r = hipStreamEndCapture(s, &B.graph);
     if (lrc) return lrc;
@@ -1836,8 +2089,7 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
     max_groups = std::max(max_groups, (static_cast<long long>(params[i].max_iter) + 1) *
                                           (params[i].max_backtracks / nt[i] + 2) + 4);
   // slot tables whose stream-ordered uploads may still be pending
-  std::vector<std::vector<int32_t>> keep;
-  keep.reserve(4 * static_cast<size_t>(n) + 4);
+  std::deque<Tables> keep;
   int q[2];
   int nq = 0, next_slot = 0;
   long long enq = 0;
@@ -1873,16 +2125,9 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
         if (!active.empty()) {
           // (each table stays in `keep` until the end: its upload is asynchronous)
           keep.emplace_back();
-          batch_slots(active, fgrid, keep.back());
-          const std::vector<int32_t>& nf = keep.back();
-          e = hipMemcpyAsync(B.fslots, nf.data(), sizeof(int32_t) * nf.size(), hipMemcpyHostToDevice, s);
-          fs.assign(nf.begin(), nf.end());
-          keep.emplace_back();
-          batch_slots(active, agrid, keep.back());
-          const std::vector<int32_t>& na = keep.back();
-          if (e == hipSuccess)
-            e = hipMemcpyAsync(B.aslots, na.data(), sizeof(int32_t) * na.size(), hipMemcpyHostToDevice, s);
-          as.assign(na.begin(), na.end());
+          tables(active, keep.back());
+          counts(keep.back());
+          e = upload(keep.back());
           if (e != hipSuccess) {
             (void)hipStreamSynchronize(s);
             return hip_error(e, "batch slot upload");

@@ -676,9 +676,11 @@ int build_phantom(imrt_ctx* ctx, const imrt_geometry* G, imrt_dose* D) {
   }
   g.nv = nv;
 
-  // Internal voxel order: tiles of 4 x 4 x 2 grid voxels (x fastest inside a
-  // tile, tiles in x, y, z order; a tile's coarse voxels after its grid
-  // voxels), so that the voxels a beamlet crosses sit close together in
+  // Internal voxel order: tiles of 4 x 4 x 2 grid voxels (tiles in x, y, z
+  // order; a tile's coarse voxels after its grid voxels; inside a tile
+  // squares of 2 x 2 voxels, the quads of the one-read pass: of all groups of
+  // four they share the most columns, 0.83 of a quad's entries at the paper's
+  // scale against 0.79 for four voxels along x), so that the voxels a beamlet crosses sit close together in
   // memory whatever the beam direction.  Row p of D is the voxel with API
   // index vox[p] and point code codes[p].
   std::vector<int32_t> codes;
@@ -690,17 +692,17 @@ int build_phantom(imrt_ctx* ctx, const imrt_geometry* G, imrt_dose* D) {
     for (int z0 = 0; z0 < G->nz; z0 += tz)
       for (int y0 = 0; y0 < G->ny; y0 += ty)
         for (int x0 = 0; x0 < G->nx; x0 += tx) {
-          for (int z = z0; z < std::min(z0 + tz, G->nz); ++z)
-            for (int y = y0; y < std::min(y0 + ty, G->ny); ++y)
-              for (int x = x0; x < std::min(x0 + tx, G->nx); ++x) {
-                const int j = x + G->nx * (y + G->ny * z);
-                const int a = api_code.empty() ? j : fine_api[j];
-                if (a < 0) continue;
-                if (p >= nv) return set_error(IMRT_EINVAL, "internal: voxel tiles overrun the layout");
-                D->vox_host[p] = a;
-                codes[p] = j;
-                ++p;
-              }
+          for (int i = 0; i < tx * ty * tz; ++i) {
+            const int x = x0 + (i & 1) + ((i >> 1) & 2), y = y0 + ((i >> 1) & 1) + ((i >> 2) & 2), z = z0 + (i >> 4);
+            if (x >= G->nx || y >= G->ny || z >= G->nz) continue;
+            const int j = x + G->nx * (y + G->ny * z);
+            const int a = api_code.empty() ? j : fine_api[j];
+            if (a < 0) continue;
+            if (p >= nv) return set_error(IMRT_EINVAL, "internal: voxel tiles overrun the layout");
+            D->vox_host[p] = a;
+            codes[p] = j;
+            ++p;
+          }
           if (api_code.empty()) continue;
           const int bz = z0 / 2;
           if (bz >= G->nz / 2) continue;

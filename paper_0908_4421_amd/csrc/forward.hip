@@ -38,10 +38,6 @@ __device__ __forceinline__ int lanes_per_row(int nr) {
   return L;
 }
 
-struct RowPenalty {
-  double Tu, To, wu, wo;
-};
-
 // Penalty of a row: the structure's entry of the LDS copy of the table, or
 // per-voxel thresholds when given.
 __device__ __forceinline__ RowPenalty row_penalty(const Penalties& p, int row, const PenaltyDev* tab,
@@ -53,16 +49,6 @@ __device__ __forceinline__ RowPenalty row_penalty(const Penalties& p, int row, c
     r.To = static_cast<double>(p.To_vox[row]);
   }
   return r;
-}
-
-// One-sided quadratic penalty of a voxel (Eq. (1)) and its half-derivative.
-__device__ __forceinline__ void penalty(const RowPenalty& p, float z, double& F, float& r) {
-#pragma clang fp contract(off)
-  const double zd = static_cast<double>(z);
-  const double under = fmin(zd - p.Tu, 0.0);
-  const double over = fmax(zd - p.To, 0.0);
-  F = p.wu * under * under + p.wo * over * over;
-  r = static_cast<float>(p.wu * under + p.wo * over);
 }
 
 template <int NT>

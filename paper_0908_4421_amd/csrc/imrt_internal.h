@@ -97,6 +97,37 @@ enum Storage : int32_t { ST_F32 = 0, ST_BF16 = 1, ST_F16 = 2 };
 constexpr int32_t ST_F32C16 = 3;
 constexpr bool coded(int st) { return st == ST_BF16 || st == ST_F16; }
 
+// ---- quad form of D (one-read pass) --------------------------------------------
+// Four consecutive rows form a quad; an entry of a quad is a column (stored as
+// column + 1 in 16 bits, 0 for none) and its four values, -0 where the row
+// has no nonzero there.  A wave's work is a list of blocks: a block is up to
+// 64 / L quads of L lanes each (L = 4 .. 64), lane `sub` of a quad taking
+// entries sub, sub + L, ... in at most quad_steps() steps.  A quad of more
+// entries than that spans several blocks: dose of all of them, the penalty
+// with the last, whose entries are still in registers, and then the adjoint
+// product of the others, read again.
+//   head of a block: {first entry, flags below}; a wave's list ends at flags 0
+//   record of each 4 lanes of a block: {offset of their quad's first entry |
+//   entries << 16, quad's first row / 4}
+constexpr int quad_steps(int storage) { return storage == ST_F32 ? 4 : 6; }
+constexpr int kQuadPad = 512;          // entries past the last one that loads may name
+constexpr int kQuadFirst = 1 << 12, kQuadDose = 1 << 13, kQuadFinish = 1 << 14, kQuadAdjoint = 1 << 15;
+__host__ __device__ inline int quad_count(int flags) { return flags & 0xFF; }
+__host__ __device__ inline int quad_log2(int flags) { return (flags >> 8) & 0xF; }
+// LDS stride of a staged vector or of a trial's column sums (slot 0: no column)
+__host__ __device__ inline int quad_stride(int nb) { return (nb + 1 + 3) & ~3; }
+constexpr int kStepCols = 16;          // columns of one step workgroup
+constexpr int kStepThreads = 512;
+__host__ __device__ inline int step_grid(int nb) { return (nb + kStepCols - 1) / kStepCols; }
+enum QuadMode : int32_t {
+  QM_SOLVE = 0,   // trials of a solve, with their gradients
+  QM_EVAL = 1,    // objective of x, dose optional
+  QM_GRAD = 2,    // objective and gradient of x
+  QM_PLAIN = 3,   // dose of x, partials of sum d^2
+  QM_POWER = 4    // D^T D of w / ||w||, partials of sum d^2
+};
+constexpr bool quad_grad(int mode) { return mode == QM_SOLVE || mode == QM_GRAD || mode == QM_POWER; }
+
 struct FwdArgs {
   const int32_t* row_ptr;
   const int32_t* col_idx;
@@ -132,6 +163,19 @@ struct FwdArgs {
   float* d_out;              // eval/plain: dose (nullable in eval)
   float* r_out;              // eval: residual (nullable)
   double* partials;          // [trial][gridDim.x] objective partials, then (solve) [trial] step norms
+  // one-read pass (mode: a QuadMode; in a solve xbuf[q] is trial q, xbuf[NT] x_k)
+  const uint2* q_head;
+  const uint2* q_rec;
+  const uint16_t* q_col;
+  const void* q_val;
+  int32_t q_nblocks, q_kmax; // blocks, and of each wave (absent ones at its end)
+  double q_rowsum, q_colsum; // largest row and column sum of D (16-bit storage: of the codes)
+  double pen_w, pen_T;       // |r| <= pen_w (|z| + pen_T)
+  double* q_unit;            // per trial: unit of the column sums (0: they are float64)
+  unsigned long long* q_acc; // [workgroup][trial][nb] column sums
+  double* q_steps;           // [trial][step_grid] step norms of the trials, then the last step's, copied there
+  const double* norm;        // QM_POWER: norm_parts partial sums of ||w||^2 (none: x is v itself)
+  int32_t norm_parts;
   const SolverState* st_in;  // solve: state before this pass
   SolverState* st_out;       // solve: state after it (copied through by workgroup 0)
 };
@@ -175,6 +219,12 @@ struct AdjArgs {
   TraceDev* trace;
   double G_skip;             // objective of the voxels the wave forward skips (rows without
                              // nonzeros between its blocks), added to every trial's G
+  // step of the one-read pass
+  const unsigned long long* q_acc;
+  const double* q_unit;
+  double* q_steps;           // [trial][step_grid] step norms read, then as many written
+  int32_t q_parts;           // workgroups of the pass
+  float* xbuf[kMaxTrials + 1];
 };
 
 // ---- host-side objects ------------------------------------------------------------
@@ -194,6 +244,8 @@ struct Tuning {
   int serve_fwd_wgs = 32;          // share their dispatches with the other live plans
   int serve_groups = 16;           // (adjoint, forward) groups a server runs between polls
   int serve_shared_adj = 0;        // live solves on one resident matrix share its adjoint pass
+  int one_read = 1;                // new matrices get the quad form, which solves and gradients read once
+                                   // per iteration (0: never; 2: also where it holds more bytes)
   int stream_nt = 2;               // solve passes read the matrix streams non-temporally: 0 never,
                                    // 1 always, 2 when they exceed the last-level cache
 };
@@ -256,6 +308,18 @@ struct imrt_dose {
   int32_t* col_whi = nullptr;
   uint8_t* col_kind = nullptr; // per column: 0 one adjoint workgroup, 1 two, 2 more
   double* pieces = nullptr;
+  // quad form (q_waves 0: not kept): entries, and the blocks of its q_waves
+  // waves.  qn and qrow (host): entries and first row / 4 of every quad in
+  // entry order; qgaps: runs of rows in quads without nonzeros.
+  int64_t nent = 0;
+  uint16_t* q_col = nullptr;
+  void* q_val = nullptr;
+  uint2* q_head = nullptr;
+  uint2* q_rec = nullptr;
+  int32_t q_nblocks = 0, q_kmax = 0, q_waves = 0;
+  double q_rowsum = 0.0, q_colsum = 0.0;
+  std::vector<int32_t> qn, qrow;
+  std::vector<std::pair<int32_t, int32_t>> qgaps;
   // internal voxel order (nullable: the caller's order): row p of D is voxel
   // vox[p]; every voxel-indexed array crossing the API is permuted
   int32_t* vox = nullptr;
@@ -290,6 +354,10 @@ struct imrt_plan {
   double* pieces = nullptr;       // 2 * adjoint grid
   int32_t pieces_cap = 0;         // adjoint grid the pieces were sized for
   double* pieces_col = nullptr;   // 2 * nb
+  // one-read pass: column sums of its workgroups, their units, step norms
+  unsigned long long* q_acc = nullptr;
+  size_t q_acc_cap = 0;
+  double* q_unit = nullptr;       // kMaxTrials units, 2 kMaxTrials step_grid(nb) step norms, step_grid(nb) squares
   double* misc = nullptr;         // small reduction scratch
   imrt::SolverState* st = nullptr;  // 2 states, alternately read and written by consecutive passes
   imrt::TraceDev* trace = nullptr;
@@ -301,10 +369,13 @@ struct imrt_plan {
   std::vector<uint8_t> sid_host;
   std::vector<imrt::PenaltyDev> table_host;
   std::vector<float> Tu_host, To_host;
-  double G_skip = 0.0;
-  int64_t gskip_epoch = -1;               // dose partition the constant was computed for (-1: stale)
-  std::vector<int64_t> skip_hist;         // skipped rows per structure id
-  int64_t skip_hist_epoch = -1;
+  double T_vox = 0.0;                     // largest |target| of them
+  struct Skip {
+    double G = 0.0;
+    int64_t epoch = -1;                   // dose partition the constant was computed for (-1: stale)
+    std::vector<int64_t> hist;            // skipped rows per structure id
+    int64_t hist_epoch = -1;
+  } skip[2];                              // of the wave forward, of the one-read pass
 };
 
 namespace imrt {
@@ -376,6 +447,31 @@ int launch_normalize(const imrt_ctx* ctx, const float* w, int nb, float* v_out, 
 int launch_permute(const imrt_ctx* ctx, const float* in, const int32_t* vox, int n, float* out, bool scatter);
 // Replace D's float32 values by 16-bit codes with per-beamlet scales (build.hip).
 int store16(imrt_dose* D, int storage);
+
+// one-read pass (onepass.hip)
+size_t quad_lds_bytes(int nb, int ntrials, int nstruct, int mode);
+int launch_quad(const imrt_ctx* ctx, const FwdArgs& a, int ntrials, int waves, int grid, hipEvent_t before = nullptr,
+                hipEvent_t after = nullptr);
+int launch_step(const imrt_ctx* ctx, const AdjArgs& a, int ntrials, hipEvent_t before = nullptr,
+                hipEvent_t after = nullptr);
+int launch_quad_batch(const imrt_ctx* ctx, const FwdArgs* args, const int32_t* slots, int nslots, int ntrials,
+                      int storage, int waves, size_t lds, int stream_cp);
+int launch_step_batch(const imrt_ctx* ctx, const AdjArgs* args, const int32_t* slots, int nslots, int ntrials);
+// Groups of solves sharing a matrix of 8-wave workgroups (groups as for
+// launch_adjoint_multi_batch; nstruct: the largest of the plans').
+int launch_quad_shared(const imrt_ctx* ctx, const FwdArgs* args, const int32_t* groups, int group_k,
+                       const int32_t* slots, int nslots, int storage, int nb, int nstruct);
+int launch_reduce(const imrt_ctx* ctx, const AdjArgs& a, double* norm);
+// out = (sum of parts[0..n) in the step's order) + add
+int launch_wave_sum(const imrt_ctx* ctx, const double* parts, int n, double* out, double add);
+// The quad form of a finished matrix (quads.hip), where it pays; its blocks
+// for the matrix's partition.
+int build_quads(imrt_dose* D);
+int partition_quads(imrt_dose* D);
+bool one_read(const imrt_ctx* C, const imrt_dose* D, int nt, int nstruct);
+int quad_grid(const imrt_dose* D, int nt);
+inline int quad_parts(const imrt_dose* D) { return D->q_waves / 8; }   // objective partials of a one-read pass
+int64_t quad_bytes(const imrt_dose* D);
 
 // phantom builder (build.hip)
 int build_phantom(imrt_ctx* ctx, const imrt_geometry* g, imrt_dose* D);

@@ -179,6 +179,24 @@ __device__ __forceinline__ double state_f64(int32_t sw, size_t byte_off) {
                                         static_cast<uint32_t>(lo));
 }
 
+// ---- penalty ------------------------------------------------------------------------
+struct RowPenalty {
+  double Tu, To, wu, wo;
+};
+
+// One-sided quadratic penalty of a voxel (Eq. (1)) and its half-derivative.
+__device__ __forceinline__ void penalty(const RowPenalty& p, float z, double& F, float& r) {
+#pragma clang fp contract(off)
+  const double zd = static_cast<double>(z);
+  const double under = fmin(zd - p.Tu, 0.0);
+  const double over = fmax(zd - p.To, 0.0);
+  F = p.wu * under * under + p.wo * over * over;
+  r = static_cast<float>(p.wu * under + p.wo * over);
+}
+
+// An s_waitcnt that waits for all loads.
+constexpr int kWaitVmcnt0 = 0x0F70;   // vmcnt 0, expcnt and lgkmcnt unchecked
+
 // ---- stored values --------------------------------------------------------------
 // A lane holds its entries in groups of four: float32 storage as int4 column
 // indices and float4 values, 16-bit storage as two 32-bit words of packed

@@ -23,6 +23,8 @@ extern "C" {
 int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev, int* nt_out, int* cap_out,
                   imrt::SolverState* init_out);
 void solve_args(imrt_plan* P, int nt, int grid, int cap, imrt::FwdArgs& fa, imrt::AdjArgs& aa);
+int solve_grid(const imrt_plan* P, int nt);
+hipError_t solve_start(imrt_plan* P, int nt, const float* x);
 }
 
 using namespace imrt;
@@ -61,6 +63,7 @@ struct Live {
   float* x = nullptr;          // start point, then scratch
   int64_t bytes = 0;           // plan buffers charged to the budget
   int nt = 1, grid = 1;
+  bool quads = false;          // its passes are one-read passes
   Clock::time_point arrival, admitted;
   double lambda0 = 0.0;
   void* trace_dst = nullptr;   // the request's trace buffer (filled by its wait)
@@ -83,13 +86,15 @@ struct Finished {
 int64_t dose_bytes(const imrt_dose* D) {
   const int64_t nnz = D->nnz, nv = D->nv, nb = D->nb;
   const int64_t per_nz = (D->storage == ST_F32) ? (D->col16 ? 18 : 16) : 10;
-  return per_nz * nnz + 4 * (nv + 1) + 4 * (nb + 1) + 2 * nv /* ids, order */ + 4 * nv /* permutation scratch */ +
+  const int64_t quads = (D->q_waves > 0) ? quad_bytes(D) + 136 * static_cast<int64_t>(D->q_nblocks) : 0;
+  return quads + per_nz * nnz + 4 * (nv + 1) + 4 * (nb + 1) + 2 * nv /* ids, order */ + 4 * nv /* permutation scratch */ +
          4 * static_cast<int64_t>(D->nwblocks + D->nblocks) * 2 + 16 * D->adj_grid + 9 * nb;
 }
 
 int64_t plan_bytes(const imrt_dose* D, int nt) {
   const int64_t nv = D->nv, nb = D->nb;
-  return (4 * (nt + 1) + 4 + 1) * nv + (4 * (nt + 1) + 4 + 16) * nb + 16 * D->adj_grid + 8 * 4096;
+  const int64_t quads = (D->q_waves > 0) ? 8 * (static_cast<int64_t>(quad_grid(D, nt)) * nt * nb + nb) : 0;
+  return quads + (4 * (nt + 1) + 4 + 1) * nv + (4 * (nt + 1) + 4 + 16) * nb + 16 * D->adj_grid + 8 * 4096;
 }
 
 }  // namespace
@@ -113,12 +118,12 @@ struct imrt_server {
   SolverState* st = nullptr;
   FwdArgs* fargs = nullptr;
   AdjArgs* aargs = nullptr;
-  int32_t* fslots = nullptr;
-  int32_t* aslots = nullptr;
-  int32_t* gtab = nullptr;      // shared-matrix adjoint groups
-  size_t fslot_cap = 0, aslot_cap = 0, gtab_cap = 0;
+  // slot tables of the forward passes, adjoint passes, one-read passes and
+  // steps, and the shared-matrix groups of the adjoint and one-read passes
+  int32_t* tab[6] = {};
+  size_t tab_cap[6] = {};
   int64_t shared_groups = 0;    // adjoint dispatch groups that served two or more solves at once
-  int64_t adj_groups = 0;       // adjoint dispatch groups in all
+  int64_t adj_groups = 0;       // adjoint dispatch groups in all (a one-read pass is one)
   std::vector<Live> live;       // index = batch slot of the plan
   std::vector<char> occupied;
   int64_t served = 0;
@@ -251,7 +256,8 @@ bool admit(imrt_server* S, Pending& p, int slot) {
   p.params.profile = 0;
   if ((rc = solve_prepare(L.plan, &p.params, L.x, &L.nt, &cap, &init))) return fail(rc);
   if (S->ctx.tune.fwd_wave == 0) return fail(set_error(IMRT_EUNSUPPORTED, "serving needs fwd_wave = 1"));
-  L.grid = std::min(forward_grid(C, D, L.nt), L.plan->fwd_cap);
+  L.quads = one_read(C, D, L.nt, L.plan->nstruct);
+  L.grid = solve_grid(L.plan, L.nt);
   FwdArgs fa;
   AdjArgs aa;
   solve_args(L.plan, L.nt, L.grid, cap, fa, aa);
@@ -268,12 +274,13 @@ bool admit(imrt_server* S, Pending& p, int slot) {
   e = hipMemcpyAsync(S->st + 2 * slot, two, sizeof(two), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(S->fargs + slot, &fa, sizeof(fa), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(S->aargs + slot, &aa, sizeof(aa), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(L.plan->xbuf[0], L.x, sizeof(float) * D->nb, hipMemcpyDeviceToDevice, s);
+  if (e == hipSuccess) e = solve_start(L.plan, L.nt, L.x);
   if (e != hipSuccess) return fail(hip_error(e, "admission upload"));
   // the initial evaluation G(x_1), alone (the batch then continues with
   // (adjoint, forward) groups)
-  if ((rc = launch_forward(C, D, fa, L.nt, L.grid))) return fail(rc);
+  rc = L.quads ? launch_quad(C, fa, L.nt, forward_waves(L.nt, D->fwd_waves), L.grid)
+               : launch_forward(C, D, fa, L.nt, L.grid);
+  if (rc) return fail(rc);
   e = hipStreamSynchronize(s);   // the small host arrays above must outlive the copies
   if (e != hipSuccess) return fail(hip_error(e, "admission"));
   L.admitted = Clock::now();
@@ -303,7 +310,7 @@ void worker_main(imrt_server* S) {
   hipStream_t s = C->stream;
   const int K = std::max(1, S->ctx.tune.serve_groups);   // groups between polls: bounds a new request's wait
   std::vector<SolverState> seen(2 * static_cast<size_t>(S->max_live));
-  std::vector<int32_t> fs, as, gt;
+  std::vector<int32_t> tab[6];   // (as S->tab)
   for (;;) {
     // admission, in arrival order, while a slot and memory are free
     std::vector<Pending> take;
@@ -358,12 +365,14 @@ void worker_main(imrt_server* S) {
       continue;
     }
     // slot tables of the live plans (each at a multiple of the die count)
-    fs.clear();
-    as.clear();
-    gt.clear();
-    int storage = -1, fst = -1, fwv = 16, nt = 1;
-    size_t lds = 0;
+    for (auto& t : tab) t.clear();
+    int storage = -1, fst = -1, fwv = 16, nt = 1, qnb = 0, qns = 0;
+    size_t lds = 0, qlds = 0;
     bool mixed = false;
+    auto slots = [](std::vector<int32_t>& t, int id, int count) {
+      while (t.size() % kXcds) t.push_back(-1);
+      for (int w = 0; w < count; ++w) t.push_back((id << 16) | w);
+    };
     for (int i : active) {
       const Live& L = S->live[i];
       const imrt_dose* D = L.plan->dose;
@@ -374,21 +383,36 @@ void worker_main(imrt_server* S) {
         nt = L.nt;
       }
       mixed = mixed || D->storage != storage || D->fwd_st != fst || D->fwd_waves != fwv || L.nt != nt;
-      while (fs.size() % kXcds) fs.push_back(-1);
-      for (int w = 0; w < L.grid; ++w) fs.push_back((i << 16) | w);
-      lds = std::max(lds, forward_lds_bytes(D->nb, L.nt, L.plan->nstruct, true, D->fwd_st, D->fwd_waves));
+      if (L.quads) {
+        slots(tab[3], i, step_grid(D->nb));
+        qlds = std::max(qlds, quad_lds_bytes(D->nb, L.nt, L.plan->nstruct, QM_SOLVE));
+        qnb = std::max(qnb, D->nb);
+        qns = std::max(qns, L.plan->nstruct);
+      } else {
+        slots(tab[0], i, L.grid);
+        lds = std::max(lds, forward_lds_bytes(D->nb, L.nt, L.plan->nstruct, true, D->fwd_st, D->fwd_waves));
+      }
     }
     // Adjoint slots: the live solves on one resident matrix (re-plans of a
     // patient) form groups of up to kShareMax that read the matrix once per
     // pass (shared-matrix adjoint); without sharing every solve is its own
-    // group.  Each group takes the matrix's adjoint grid of slots.
-    std::vector<std::vector<int>> groups;
-    {
+    // group.  Each group takes the matrix's adjoint grid of slots.  One-read
+    // passes likewise, where the group's vectors and column sums fit LDS.
+    size_t most = kShareMax;
+    while (most > 1 && quad_lds_bytes(qnb, static_cast<int>(most), static_cast<int>(most) * qns, QM_SOLVE) > C->max_lds)
+      most /= 2;
+    int gk[2];
+    size_t ngroups = 0, nshared = 0;
+    for (int one = 0; one < 2; ++one) {
+      std::vector<std::vector<int>> groups;
+      const bool share = S->ctx.tune.serve_shared_adj && (one == 0 || (nt == 1 && fwv == 8));
+      const size_t cap = one ? most : kShareMax;
       std::vector<const imrt_dose*> order;
       std::map<const imrt_dose*, std::vector<int>> by_dose;
       for (int i : active) {
+        if (S->live[i].quads != (one == 1)) continue;
         const imrt_dose* D = S->live[i].plan->dose;
-        if (!S->ctx.tune.serve_shared_adj) {
+        if (!share) {
           groups.push_back({i});
           continue;
         }
@@ -397,46 +421,51 @@ void worker_main(imrt_server* S) {
       }
       for (const imrt_dose* D : order) {
         const std::vector<int>& v = by_dose[D];
-        for (size_t j = 0; j < v.size(); j += kShareMax)
-          groups.emplace_back(v.begin() + j, v.begin() + std::min(v.size(), j + kShareMax));
+        for (size_t j = 0; j < v.size(); j += cap)
+          groups.emplace_back(v.begin() + j, v.begin() + std::min(v.size(), j + cap));
       }
-    }
-    size_t gmax = 1;
-    for (const auto& g : groups) gmax = std::max(gmax, g.size());
-    const int gk = gmax <= 1 ? 1 : (gmax <= 2 ? 2 : 4);
-    for (size_t g = 0; g < groups.size(); ++g) {
-      const imrt_dose* D = S->live[groups[g][0]].plan->dose;
-      const int id = (gk == 1) ? groups[g][0] : static_cast<int>(g);
-      while (as.size() % kXcds) as.push_back(-1);
-      for (int w = 0; w < D->adj_grid; ++w) as.push_back((id << 16) | w);
-      if (gk > 1) {
-        gt.push_back(static_cast<int32_t>(groups[g].size()));
-        for (int q = 0; q < gk; ++q) gt.push_back(groups[g][std::min<size_t>(q, groups[g].size() - 1)]);
+      size_t gmax = 1;
+      for (const auto& g : groups) {
+        gmax = std::max(gmax, g.size());
+        nshared += g.size() > 1;
+      }
+      ngroups += groups.size();
+      gk[one] = gmax <= 1 ? 1 : (gmax <= 2 ? 2 : 4);
+      for (size_t g = 0; g < groups.size(); ++g) {
+        const Live& L = S->live[groups[g][0]];
+        slots(tab[1 + one], gk[one] == 1 ? groups[g][0] : static_cast<int>(g), one ? L.grid : L.plan->dose->adj_grid);
+        if (gk[one] > 1) {
+          tab[4 + one].push_back(static_cast<int32_t>(groups[g].size()));
+          for (int q = 0; q < gk[one]; ++q)
+            tab[4 + one].push_back(groups[g][std::min<size_t>(q, groups[g].size() - 1)]);
+        }
       }
     }
     int rc = IMRT_OK;
     if (mixed) rc = set_error(IMRT_EINVAL, "live solves of one server must share storage, layout and trials_per_pass");
-    if (!rc) rc = grow_slots(S, &S->fslots, &S->fslot_cap, fs.size());
-    if (!rc) rc = grow_slots(S, &S->aslots, &S->aslot_cap, as.size());
-    if (!rc && gk > 1) rc = grow_slots(S, &S->gtab, &S->gtab_cap, gt.size());
     hipError_t e = hipSuccess;
-    if (!rc) e = hipMemcpyAsync(S->fslots, fs.data(), sizeof(int32_t) * fs.size(), hipMemcpyHostToDevice, s);
-    if (!rc && e == hipSuccess)
-      e = hipMemcpyAsync(S->aslots, as.data(), sizeof(int32_t) * as.size(), hipMemcpyHostToDevice, s);
-    if (!rc && e == hipSuccess && gk > 1)
-      e = hipMemcpyAsync(S->gtab, gt.data(), sizeof(int32_t) * gt.size(), hipMemcpyHostToDevice, s);
-    if (!rc && e != hipSuccess) rc = hip_error(e, "server slot upload");
+    int count[6];
+    for (int k = 0; k < 6 && !rc; ++k) {
+      count[k] = static_cast<int>(tab[k].size());
+      if (count[k] == 0) continue;
+      rc = grow_slots(S, &S->tab[k], &S->tab_cap[k], tab[k].size());
+      if (!rc) e = hipMemcpyAsync(S->tab[k], tab[k].data(), sizeof(int32_t) * tab[k].size(), hipMemcpyHostToDevice, s);
+      if (!rc && e != hipSuccess) rc = hip_error(e, "server slot upload");
+    }
+    const int qwv = forward_waves(nt, fwv);
     for (int k = 0; k < K && !rc; ++k) {
-      if (gk == 1) rc = launch_adjoint_batch(C, S->aargs, S->aslots, static_cast<int>(as.size()), nt, storage, 0);
-      else
-        rc = launch_adjoint_multi_batch(C, S->aargs, S->gtab, gk, S->aslots, static_cast<int>(as.size()), nt,
-                                        storage);
-      if (!rc) rc = launch_forward_batch(C, S->fargs, S->fslots, static_cast<int>(fs.size()), nt, fst, fwv, lds, 0);
+      if (gk[0] == 1) rc = launch_adjoint_batch(C, S->aargs, S->tab[1], count[1], nt, storage, 0);
+      else rc = launch_adjoint_multi_batch(C, S->aargs, S->tab[4], gk[0], S->tab[1], count[1], nt, storage);
+      if (!rc) rc = launch_step_batch(C, S->aargs, S->tab[3], count[3], nt);
+      if (!rc) rc = launch_forward_batch(C, S->fargs, S->tab[0], count[0], nt, fst, fwv, lds, 0);
+      if (!rc && gk[1] == 1) rc = launch_quad_batch(C, S->fargs, S->tab[2], count[2], nt, storage, qwv, qlds, 0);
+      if (!rc && gk[1] > 1)
+        rc = launch_quad_shared(C, S->fargs, S->tab[5], gk[1], S->tab[2], count[2], storage, qnb, qns);
     }
     if (!rc) {
       std::lock_guard<std::mutex> g(S->mu);
-      S->adj_groups += static_cast<int64_t>(K) * static_cast<int64_t>(groups.size());
-      for (const auto& grp : groups) S->shared_groups += (grp.size() > 1) ? K : 0;
+      S->adj_groups += static_cast<int64_t>(K) * static_cast<int64_t>(ngroups);
+      S->shared_groups += static_cast<int64_t>(K) * static_cast<int64_t>(nshared);
     }
     if (!rc) {
       e = hipMemcpyAsync(seen.data(), S->st, sizeof(SolverState) * 2 * S->max_live, hipMemcpyDeviceToHost, s);
@@ -637,7 +666,8 @@ int imrt_server_destroy(imrt_server* S) {
     if (S->occupied[i]) release(S, i);
   for (auto& kv : S->residents) (void)imrt_dose_destroy(kv.second.dose);
   for (void* p : {static_cast<void*>(S->st), static_cast<void*>(S->fargs), static_cast<void*>(S->aargs),
-                  static_cast<void*>(S->fslots), static_cast<void*>(S->aslots), static_cast<void*>(S->gtab)})
+                  static_cast<void*>(S->tab[0]), static_cast<void*>(S->tab[1]), static_cast<void*>(S->tab[2]),
+                  static_cast<void*>(S->tab[3]), static_cast<void*>(S->tab[4]), static_cast<void*>(S->tab[5])})
     if (p) (void)hipFree(p);
   if (S->ctx.stream) (void)hipStreamDestroy(S->ctx.stream);
   delete S;
