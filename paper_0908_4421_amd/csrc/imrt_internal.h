@@ -99,20 +99,38 @@ constexpr bool coded(int st) { return st == ST_BF16 || st == ST_F16; }
 
 // ---- quad form of D (one-read pass) --------------------------------------------
 // Four consecutive rows form a quad; an entry of a quad is a column (stored as
-// column + 1 in 16 bits, 0 for none) and its four values, -0 where the row
-// has no nonzero there.  A wave's work is a list of blocks: a block is up to
-// 64 / L quads of L lanes each (L = 4 .. 64), lane `sub` of a quad taking
-// entries sub, sub + L, ... in at most quad_steps() steps.  A quad of more
-// entries than that spans several blocks: dose of all of them, the penalty
-// with the last, whose entries are still in registers, and then the adjoint
-// product of the others, read again.
+// 4 (column + 1) in 16 bits, 0 for none) and its four values, -0 where the
+// row has no nonzero there.  A wave's work is a list of blocks: a block is up
+// to 64 / L quads of L lanes each (L = 4 .. 64), lane `sub` of a quad taking
+// entries sub, sub + L, ... in at most quad_steps() steps.  With 16-bit
+// storage a step takes a pair of entries, 4 bytes of columns and 16 bytes of
+// codes: quads then hold an even number of entries, the last one possibly
+// without a column, and a pair is entries r and r + n / 2 in column order of
+// a part of n entries (a quad, or a quad's share of one block), so that the
+// columns that one instruction gathers from LDS run on over the lanes.
+// (float32 values, 16 bytes an entry, are not paired: two loads at two places
+// cost more cache lines than the halved column loads save, 19.2 against
+// 19.4 ms for the paper-scale plan; with 16-bit storage 11.3 against 11.5 ms
+// for the two-trial re-plan, 20.7 against 23.9 us for the dose alone.)  A quad
+// of more entries than a block holds spans several blocks: dose of all of
+// them, the penalty with the last, whose entries are still in registers, and
+// then the adjoint product of the others, read again.
 //   head of a block: {first entry, flags below}; a wave's list ends at flags 0
 //   record of each 4 lanes of a block: {offset of their quad's first entry |
 //   entries << 16, quad's first row / 4}
-constexpr int quad_steps(int storage) { return storage == ST_F32 ? 4 : 6; }
+constexpr int quad_run(int storage) { return coded(storage) ? 2 : 1; }      // entries a lane takes a step
+constexpr int quad_steps(int storage) { return coded(storage) ? 3 : 4; }
+constexpr int quad_full(int storage) { return 64 * quad_run(storage) * quad_steps(storage); }   // entries of a block
+// Parts of a quad of n entries, of which a block holds `full` at most: the
+// last one full, the others before it about equal, their bounds rounded up to
+// even places (so none exceeds `full`) but for the last one's start.
+__host__ __device__ inline int quad_parts_before(int n, int full) { return n > full ? (n - 1) / full : 0; }
+__host__ __device__ inline int quad_part(int n, int full, int before, int k) {
+  if (k >= before) return k > before ? n : n - full;
+  return 2 * static_cast<int>((static_cast<int64_t>(n - full) * k + 2 * before - 1) / (2 * before));
+}
 constexpr int kQuadPad = 512;          // entries past the last one that loads may name
 constexpr int kQuadFirst = 1 << 12, kQuadDose = 1 << 13, kQuadFinish = 1 << 14, kQuadAdjoint = 1 << 15;
-__host__ __device__ inline int quad_count(int flags) { return flags & 0xFF; }
 __host__ __device__ inline int quad_log2(int flags) { return (flags >> 8) & 0xF; }
 // LDS stride of a staged vector or of a trial's column sums (slot 0: no column)
 __host__ __device__ inline int quad_stride(int nb) { return (nb + 1 + 3) & ~3; }

@@ -91,8 +91,8 @@ __device__ __forceinline__ bool quad_hole(const QuadVal<ST>& v, int u) {
 // (NP: plans with penalties of their own)
 template <int ST, int NP>
 struct QuadStage {
-  QuadVal<ST> v[quad_steps(ST)];
-  uint32_t c[quad_steps(ST)];
+  QuadVal<ST> v[quad_run(ST) * quad_steps(ST)];
+  uint32_t c[quad_steps(ST)];   // one column or two each
   uint32_t sid[NP];
   float tu[NP], to[NP];
 };
@@ -114,26 +114,46 @@ struct ManyPlans {
   __device__ __forceinline__ bool has(int q) const { return q < n; }
 };
 
-// Loads of one block: slot `step` of a lane is entry sub + step * L of its
-// quad; slots past the quad read zeros out of bounds (column code 0: none).
+// Column of entry m of a lane, as the byte offset into a staged vector.
+template <int ST, int NP>
+__device__ __forceinline__ uint32_t quad_col(const QuadStage<ST, NP>& S, int m) {
+  if constexpr (quad_run(ST) == 1) return S.c[m];
+  else return (m & 1) ? S.c[m / 2] >> 16 : S.c[m / 2] & 0xFFFFu;
+}
+__device__ __forceinline__ float staged(const float* xs, uint32_t c) {
+  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(xs) + c);
+}
+// The column sum of the same column.
+template <typename T>
+__device__ __forceinline__ T* sum_at(T* acc, uint32_t c) {
+  return reinterpret_cast<T*>(reinterpret_cast<char*>(acc) + 2 * c);
+}
+
+// Loads of one block; steps past a lane's entries read zeros out of bounds
+// (column code 0: none).
 template <int ST, int CP, int NP, typename Plans>
 __device__ __forceinline__ void quad_issue(const Plans& P, const uint2 rec, int e0, int flags, int lane,
                                            QuadStage<ST, NP>& S) {
   const FwdArgs& a = P(0);
-  constexpr int VB = coded(ST) ? 8 : 16;
+  constexpr int VB = coded(ST) ? 8 : 16, R = quad_run(ST);   // bytes of an entry's values
   const int e = quad_log2(flags), L = 1 << e;
-  const int sub = lane & (L - 1), n = static_cast<int>(rec.x >> 16);
-  const int rel = static_cast<int>(rec.x & 0xFFFFu) + sub;
-  // (64 M entries at most from e0; the arrays are padded by as many)
+  const int sub = lane & (L - 1), n = static_cast<int>(rec.x >> 16) / R;
+  const uint32_t at0 = (rec.x & 0xFFFFu) / R + sub;
+  // (a block ends at most kQuadPad entries after e0; the arrays are padded by as many)
   const rsrc_t rc = make_rsrc(a.q_col + e0, 2u * kQuadPad);
   const rsrc_t rv = make_rsrc(static_cast<const char*>(a.q_val) + static_cast<size_t>(e0) * VB, VB * kQuadPad);
 #pragma unroll
   for (int m = 0; m < quad_steps(ST); ++m) {
-    const bool in = sub + m * L < n;
-    const uint32_t at = in ? static_cast<uint32_t>(rel + m * L) : 0x00FFFFFFu;
-    S.c[m] = __builtin_amdgcn_raw_buffer_load_b16(rc, 2u * at, 0, CP);
-    if constexpr (coded(ST)) S.v[m] = load_u2s<CP>(rv, VB * at);
-    else S.v[m] = load_f4s<CP>(rv, VB * at);
+    const uint32_t at = sub + m * L < n ? at0 + m * L : 0x00800000u;
+    if constexpr (R == 2) {
+      S.c[m] = __builtin_amdgcn_raw_buffer_load_b32(rc, 4u * at, 0, CP);
+      const int4 w = load_i4s<CP>(rv, 16u * at);
+      S.v[2 * m] = make_uint2(w.x, w.y);
+      S.v[2 * m + 1] = make_uint2(w.z, w.w);
+    } else {
+      S.c[m] = __builtin_amdgcn_raw_buffer_load_b16(rc, 2u * at, 0, CP);
+      S.v[m] = load_f4s<CP>(rv, 16u * at);
+    }
   }
   const uint32_t row = 4u * rec.y + (lane & 3);
   const uint32_t nv = static_cast<uint32_t>(a.nv);
@@ -172,7 +192,7 @@ template <int NT, int MODE, int WAVES, int ST, int CP, typename Plans>
 __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst) {
   constexpr int NP = Plans::kMany ? NT : 1;
   const FwdArgs& a = P(0);
-  constexpr int THREADS = WAVES * 64, M = quad_steps(ST), U = WAVES == 16 ? 4 : 8;
+  constexpr int THREADS = WAVES * 64, M = quad_run(ST) * quad_steps(ST), U = WAVES == 16 ? 4 : 8;
   constexpr bool GRAD = quad_grad(MODE);
   constexpr bool PEN = MODE != QM_PLAIN && MODE != QM_POWER;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -390,12 +410,12 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
         for (int u = 0; u < 4; ++u) z[q][u] = 0.0f;
     }
     if (flags & kQuadDose) {
-      // (steps past the block's last are idle lanes: zeros)
+      // (idle lanes multiply zeros)
 #pragma unroll
       for (int q = 0; q < NT; ++q) {
         float x[M];
 #pragma unroll
-        for (int m = 0; m < M; ++m) x[m] = xs[q * nbs + S.c[m]];
+        for (int m = 0; m < M; ++m) x[m] = staged(xs + q * nbs, quad_col(S, m));
 #pragma unroll
         for (int m = 0; m < M; ++m)
 #pragma unroll
@@ -423,14 +443,15 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
         const double r4[4] = {quad_bcast<0>(rd[q]), quad_bcast<1>(rd[q]), quad_bcast<2>(rd[q]), quad_bcast<3>(rd[q])};
 #pragma unroll
         for (int m = 0; m < M; ++m) {
-          if (S.c[m] != 0) {
+          const uint32_t c = quad_col(S, m);
+          if (c != 0) {
             QuadVal<ST> v = S.v[m];
             // (codes are decoded again: keeping the dose's floats costs registers)
             if constexpr (coded(ST)) asm("" : "+v"(v.x), "+v"(v.y));
             double t = static_cast<double>(val_of<ST>(v, 0)) * r4[0];
 #pragma unroll
             for (int u = 1; u < 4; ++u) t = __builtin_fma(static_cast<double>(val_of<ST>(v, u)), r4[u], t);
-            __hip_atomic_fetch_add(acc + q * nbs + S.c[m], to_fixed(t), __ATOMIC_RELAXED,
+            __hip_atomic_fetch_add(sum_at(acc + q * nbs, c), to_fixed(t), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
           }
         }
@@ -443,8 +464,8 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
   auto slow = [&](int q) {
     float zq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     double r4[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int k = 0; k < kmax; ++k) {
-      const uint2 hd = load_head(blk0 + k), rec = load_rec(k);
+    for (int b = 0; b < kmax; ++b) {
+      const uint2 hd = load_head(blk0 + b), rec = load_rec(b);
       const int flags = uniform(static_cast<int>(hd.y)), e = quad_log2(flags);
       if (flags == 0) break;
       const int sub = lane & ((1 << e) - 1), n = static_cast<int>(rec.x >> 16);
@@ -452,14 +473,16 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
       const auto* ev = static_cast<const QuadVal<ST>*>(a.q_val) + at;
       const uint16_t* ec = a.q_col + at;
       if (flags & kQuadFirst) zq[0] = zq[1] = zq[2] = zq[3] = 0.0f;
+      constexpr int R = quad_run(ST);   // (the lanes' entries in their steps' order)
       if (flags & kQuadDose)
-        for (int j = sub; j < n; j += 1 << e) {
-          const QuadVal<ST> v = ev[j];
-          const float x = xs[q * nbs + ec[j]];
+        for (int j = sub; j < n / R; j += 1 << e)
+          for (int k = R * j; k < R * j + R; ++k) {
+            const QuadVal<ST> v = ev[k];
+            const float x = staged(xs + q * nbs, ec[k]);
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (!quad_hole<ST>(v, u)) zq[u] = fmaf(val_of<ST>(v, u), x, zq[u]);
-        }
+            for (int u = 0; u < 4; ++u)
+              if (!quad_hole<ST>(v, u)) zq[u] = fmaf(val_of<ST>(v, u), x, zq[u]);
+          }
       if (flags & kQuadFinish) {
         const int p = Plans::kMany ? q : 0;
         RowPenalty pen{0.0, 0.0, 0.0, 0.0};
@@ -475,25 +498,25 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
         r4[3] = quad_bcast<3>(r);
       }
       if (GRAD && (flags & kQuadAdjoint))
-        for (int j = sub; j < n; j += 1 << e) {
-          const QuadVal<ST> v = ev[j];
-          double t = 0.0;
+        for (int j = sub; j < n / R; j += 1 << e)
+          for (int k = R * j; k < R * j + R; ++k) {
+            const QuadVal<ST> v = ev[k];
+            double t = 0.0;
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (!quad_hole<ST>(v, u)) t = __builtin_fma(static_cast<double>(val_of<ST>(v, u)), r4[u], t);
-          unsigned long long* to = acc + q * nbs + ec[j];
-          if (wild[q])
-            __hip_atomic_fetch_add(reinterpret_cast<double*>(to), t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          else
-            __hip_atomic_fetch_add(to, to_fixed(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+            for (int u = 0; u < 4; ++u)
+              if (!quad_hole<ST>(v, u)) t = __builtin_fma(static_cast<double>(val_of<ST>(v, u)), r4[u], t);
+            unsigned long long* to = sum_at(acc + q * nbs, ec[k]);
+            if (wild[q])
+              __hip_atomic_fetch_add(reinterpret_cast<double*>(to), t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            else
+              __hip_atomic_fetch_add(to, to_fixed(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
     }
   };
 
   if (!any_wild) {
     // Block i is in A; block i + 1's loads are issued into B before block i's
-    // arithmetic (an absent block reads zeros out of bounds), and the record
-    // of block i + 2 with them.
+    // arithmetic, and the record of block i + 2 with them.
     int i = 0;
     auto turn = [&](const QuadStage<ST, NP>& cur, QuadStage<ST, NP>& nxt) {
       const uint2 rc = rec0;
@@ -512,9 +535,9 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
       compute(cur, rc, f);
       return fl != 0;
     };
-    while (fl != 0) {
+    for (bool more = fl != 0; more;) {
       if (!turn(A, B)) break;
-      if (!turn(B, A)) break;
+      more = turn(B, A);
     }
   } else {
 #pragma unroll

@@ -57,7 +57,8 @@ __device__ __forceinline__ double stored(const float* val, const uint16_t* val16
   else return static_cast<double>(val[k]);
 }
 
-// Entries of the quads in their final order: quad rows qrow[i], first entry ptr[i].
+// Entries of the quads in their final order: quad rows qrow[i], first entry
+// ptr[i] (ptr[nq]: their number).
 template <int ST, typename Col>
 __global__ __launch_bounds__(kThreads) void quad_fill_kernel(const int32_t* row_ptr, const Col* col, const float* val,
                                                              const uint16_t* val16, int nv, int nq,
@@ -66,9 +67,23 @@ __global__ __launch_bounds__(kThreads) void quad_fill_kernel(const int32_t* row_
   const int i = blockIdx.x * kThreads + threadIdx.x;
   double rs[4] = {0.0, 0.0, 0.0, 0.0};
   if (i < nq) {
-    int e = ptr[i];
+    const int e0 = ptr[i], n = ptr[i + 1] - e0, full = quad_full(ST);
+    const int before = quad_parts_before(n, full);
+    int r = 0, part = 0, p0 = 0, p1 = quad_part(n, full, before, 1);
+    // place of entry r of the part [p0, p1): in column order, or in pairs
+    auto place = [&]() {
+      if (quad_run(ST) == 1) return e0 + r;
+      if (r == p1) {
+        ++part;
+        p0 = p1;
+        p1 = quad_part(n, full, before, part + 1);
+      }
+      const int h = (p1 - p0) / 2, j = r - p0;
+      return e0 + p0 + (j < h ? 2 * j : 2 * (j - h) + 1);
+    };
     merge_rows(row_ptr, col, nv, qrow[i], [&](int c, const int (&k)[4]) {
-      q_col[e] = static_cast<uint16_t>(c + 1);
+      const int e = place();
+      q_col[e] = static_cast<uint16_t>(4 * (c + 1));
       if constexpr (coded(ST)) {
         uint32_t h[4];
 #pragma unroll
@@ -86,8 +101,13 @@ __global__ __launch_bounds__(kThreads) void quad_fill_kernel(const int32_t* row_
         }
         static_cast<float4*>(q_val)[e] = make_float4(v[0], v[1], v[2], v[3]);
       }
-      ++e;
+      ++r;
     });
+    if (coded(ST) && r < n) {
+      const int e = place();
+      q_col[e] = 0;
+      static_cast<uint2*>(q_val)[e] = make_uint2(0x80008000u, 0x80008000u);
+    }
   }
   double m = fmax(fmax(rs[0], rs[1]), fmax(rs[2], rs[3]));
   for (int d = 1; d < 64; d <<= 1) m = fmax(m, __shfl_xor(m, d));
@@ -124,9 +144,9 @@ int alloc(void** p, size_t bytes) {
 // quads of a block are of one size and its lanes take equally many steps.
 constexpr int kWindow = 512;
 
-int lanes_for(int n, int steps) {
+int lanes_for(int n, int storage) {
   int L = 4;
-  while (L < 64 && L * steps < n) L *= 2;
+  while (L < 64 && L * quad_full(storage) < 64 * n) L *= 2;
   return L;
 }
 
@@ -164,7 +184,10 @@ int build_quads(imrt_dose* D) {
   IMRT_HIP(hipMemsetAsync(d_sums, 0, 2 * sizeof(unsigned long long), s));
   IMRT_HIP(hipStreamSynchronize(s));
   int64_t nent = 0;
-  for (int32_t v : n) nent += v;
+  for (int32_t& v : n) {
+    v += v % quad_run(D->storage);
+    nent += v;
+  }
   // The rule: the quad form where its one read is fewer bytes than the two
   // passes' reads together.
   const int64_t per = c16 ? 10 : 18, two = c16 ? 10 : 14;
@@ -184,7 +207,7 @@ int build_quads(imrt_dose* D) {
   }
   const int nq = static_cast<int>(qrow.size());
   {
-    std::vector<int32_t> first(static_cast<size_t>(D->nb) + 2), tmp(kWindow);
+    std::vector<int32_t> first(static_cast<size_t>(D->nb) + 3), tmp(kWindow);
     for (int w0 = 0; w0 < nq; w0 += kWindow) {
       const int w1 = std::min(nq, w0 + kWindow);
       int top = 0;
@@ -196,7 +219,7 @@ int build_quads(imrt_dose* D) {
       std::copy(tmp.begin(), tmp.begin() + (w1 - w0), qrow.begin() + w0);
     }
   }
-  std::vector<int32_t> order(2 * static_cast<size_t>(nq));   // rows, first entries
+  std::vector<int32_t> order(2 * static_cast<size_t>(nq) + 1);   // rows, first entries
   int64_t at = 0;
   for (int i = 0; i < nq; ++i) {
     qn.push_back(n[qrow[i]]);
@@ -204,6 +227,7 @@ int build_quads(imrt_dose* D) {
     order[static_cast<size_t>(nq) + i] = static_cast<int32_t>(at);
     at += qn[i];
   }
+  order.back() = static_cast<int32_t>(at);
   const size_t ents = static_cast<size_t>(nent) + kQuadPad, vb = c16 ? 8 : 16;
   if ((rc = alloc(&ord.p, sizeof(int32_t) * order.size())) ||
       (rc = alloc(reinterpret_cast<void**>(&D->q_col), 2 * ents)) || (rc = alloc(&D->q_val, vb * ents)))
@@ -240,14 +264,14 @@ int build_quads(imrt_dose* D) {
 // blocks.  As in the wave forward, a matrix solved alone spreads over up to
 // 16 waves of every compute unit, one with per-plan targets over fewer.
 int partition_quads(imrt_dose* D) {
-  const int steps = quad_steps(D->storage), full = 64 * steps, nq = static_cast<int>(D->qn.size());
+  const int full = quad_full(D->storage), run = quad_run(D->storage), nq = static_cast<int>(D->qn.size());
   const std::vector<int32_t>& qn = D->qn;
   constexpr int kQuadCost = 8;   // of a quad beside its entries, in entries
   int64_t total = 0, slots = 0;
   for (int32_t n : qn) {
     total += n + kQuadCost;
-    const int L = lanes_for(n, steps);
-    slots += static_cast<int64_t>(L) * ((n + L - 1) / L);
+    const int step = run * lanes_for(n, D->storage);
+    slots += static_cast<int64_t>(step) * ((n + step - 1) / step);
   }
   // two steps a wave at least when alone, fwd_bpw blocks in shared dispatches
   const int64_t per = D->fwd_waves == 16 ? 128 : static_cast<int64_t>(full) * D->fwd_bpw;
@@ -264,12 +288,11 @@ int partition_quads(imrt_dose* D) {
   int32_t e0 = 0;
   auto block = [&](int flags, int q, int nqb, int L, int start, int count) {
     // nqb quads from q on (or entries [start, start + count) of one)
-    int most = 0, rel = 0;
+    int rel = 0;
     uint2 r[16];
     for (int g = 0; g < 16; ++g) r[g] = make_uint2(0, 0);
     for (int j = 0; j < nqb; ++j) {
       const int n = count > 0 ? count : qn[q + j];
-      most = std::max(most, n);
       for (int g = j * L / 4; g < (j + 1) * L / 4; ++g)
         r[g] = make_uint2(static_cast<uint32_t>(rel) | (static_cast<uint32_t>(n) << 16),
                           static_cast<uint32_t>(D->qrow[q + j]));
@@ -277,7 +300,7 @@ int partition_quads(imrt_dose* D) {
     }
     int e = 2;
     while ((1 << e) < L) ++e;
-    head.push_back(make_int2(e0 + start, flags | (e << 8) | ((most + L - 1) / L)));
+    head.push_back(make_int2(e0 + start, flags | (e << 8)));
     rec.insert(rec.end(), r, r + 16);
   };
   constexpr int kAll = kQuadFirst | kQuadDose | kQuadFinish | kQuadAdjoint;
@@ -291,8 +314,8 @@ int partition_quads(imrt_dose* D) {
     if (w == waves - 1) qe = nq;
     while (q < qe) {
       if (qn[q] > full) {
-        const int n = qn[q], parts = (n - 1) / full;   // before the last one, which is full
-        auto part = [&](int k) { return static_cast<int>(static_cast<int64_t>(n - full) * k / parts); };
+        const int n = qn[q], parts = quad_parts_before(n, full);   // before the last one, which is full
+        auto part = [&](int k) { return quad_part(n, full, parts, k); };
         for (int k = 0; k < parts; ++k)
           block(kQuadDose | (k == 0 ? kQuadFirst : 0), q, 1, 64, part(k), part(k + 1) - part(k));
         block(kQuadDose | kQuadFinish | kQuadAdjoint, q, 1, 64, n - full, full);
@@ -301,9 +324,9 @@ int partition_quads(imrt_dose* D) {
         ++q;
         continue;
       }
-      int c = 1, L = lanes_for(qn[q], steps);
+      int c = 1, L = lanes_for(qn[q], D->storage);
       while (q + c < qe && qn[q + c] <= full) {
-        const int Ln = std::max(L, lanes_for(qn[q + c], steps));
+        const int Ln = std::max(L, lanes_for(qn[q + c], D->storage));
         if ((c + 1) * Ln > 64) break;
         L = Ln;
         ++c;

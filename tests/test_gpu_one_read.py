@@ -87,6 +87,30 @@ def test_products_against_float64_and_two_passes(nv, nb, longest, storage):
     assert got[2][3] == got[0][3] and abs(got[2][4] - got[0][4]) <= 1e-5 * got[0][4]
 
 
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_quads_of_exact_sizes(storage):
+    """Quads one entry around the sizes that fill one, two, three and four
+    blocks (256 entries in float32, 384 in 16 bits), every row full."""
+    sizes = [n for full in (256, 384) for k in (1, 2, 3, 4) for n in (k * full - 1, k * full, k * full + 1)]
+    nb = max(sizes)
+    rng = np.random.default_rng(11)
+    rows = [r for q, n in enumerate(sizes) for r in 4 * q + np.repeat(np.arange(4), n)]
+    cols = np.concatenate([np.tile(np.sort(rng.choice(nb, n, replace=False)), 4) for n in sizes])
+    vals = (rng.integers(64, 128, len(cols)) / 128.0).astype(np.float32)
+    D = sp.csr_matrix((vals, (rows, cols)), shape=(4 * len(sizes), nb))
+    for c in range(nb):   # a largest value of 1 in every column: exact in 16 bits
+        D[int(D[:, c].argmax()), c] = 1.0
+    D.sort_indices()
+    sid = rng.integers(0, 2, D.shape[0]).astype(np.uint8)
+    x = rng.uniform(0.0, 0.02, nb).astype(np.float32)
+    z, G, g = _reference(D, sid, x)
+    ctx, lib, plan = _plan(D, sid, storage, 2)
+    eps = (nb + 4) * 2.0 ** -24
+    assert np.max(np.abs(to_host(lib.apply(to_dev(x))) - z)) <= eps * np.max(np.abs(z))
+    got, Gm = plan.gradient(to_dev(x))
+    assert abs(Gm - G) <= 4 * eps * G and rel_normwise(to_host(got), g) <= 8 * eps
+
+
 @pytest.mark.parametrize("nt", [1, 2, 4])
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
 def test_solve_equals_two_pass_steps(storage, nt):
