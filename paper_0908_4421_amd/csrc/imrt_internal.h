@@ -192,6 +192,9 @@ struct FwdArgs {
   double* q_unit;            // per trial: unit of the column sums (0: they are float64)
   unsigned long long* q_acc; // [workgroup][trial][nb] column sums
   double* q_steps;           // [trial][step_grid] step norms of the trials, then the last step's, copied there
+  const int32_t* vox;        // dose output: row j goes to d_out[vox[j]] (null: d_out[j]),
+  const int32_t* zero;       // and d_out[zero[i]] = 0 for nzero places (rows of empty quads)
+  int32_t nzero;
   const double* norm;        // QM_POWER: norm_parts partial sums of ||w||^2 (none: x is v itself)
   int32_t norm_parts;
   const SolverState* st_in;  // solve: state before this pass
@@ -338,6 +341,8 @@ struct imrt_dose {
   double q_rowsum = 0.0, q_colsum = 0.0;
   std::vector<int32_t> qn, qrow;
   std::vector<std::pair<int32_t, int32_t>> qgaps;
+  int32_t* q_zero = nullptr;   // the voxels of those rows, in the caller's order
+  int32_t nzero = 0;
   // internal voxel order (nullable: the caller's order): row p of D is voxel
   // vox[p]; every voxel-indexed array crossing the API is permuted
   int32_t* vox = nullptr;
@@ -479,7 +484,9 @@ int launch_step_batch(const imrt_ctx* ctx, const AdjArgs* args, const int32_t* s
 // launch_adjoint_multi_batch; nstruct: the largest of the plans').
 int launch_quad_shared(const imrt_ctx* ctx, const FwdArgs* args, const int32_t* groups, int group_k,
                        const int32_t* slots, int nslots, int storage, int nb, int nstruct);
-int launch_reduce(const imrt_ctx* ctx, const AdjArgs& a, double* norm);
+// sum (nullable): *sum = (sum of parts[0..n) in the step's order) + add, taken along
+int launch_reduce(const imrt_ctx* ctx, const AdjArgs& a, double* norm, double* sum = nullptr,
+                  const double* parts = nullptr, int n = 0, double add = 0.0);
 // out = (sum of parts[0..n) in the step's order) + add
 int launch_wave_sum(const imrt_ctx* ctx, const double* parts, int n, double* out, double add);
 // The quad form of a finished matrix (quads.hip), where it pays; its blocks

@@ -95,6 +95,7 @@ struct QuadStage {
   uint32_t c[quad_steps(ST)];   // one column or two each
   uint32_t sid[NP];
   float tu[NP], to[NP];
+  uint32_t vox;   // passes that write the dose: the voxel of the lane's row
 };
 
 // The plans of a pass: one, or up to K that share the matrix (the first
@@ -131,7 +132,7 @@ __device__ __forceinline__ T* sum_at(T* acc, uint32_t c) {
 
 // Loads of one block; steps past a lane's entries read zeros out of bounds
 // (column code 0: none).
-template <int ST, int CP, int NP, typename Plans>
+template <int MODE, int ST, int CP, int NP, typename Plans>
 __device__ __forceinline__ void quad_issue(const Plans& P, const uint2 rec, int e0, int flags, int lane,
                                            QuadStage<ST, NP>& S) {
   const FwdArgs& a = P(0);
@@ -157,6 +158,9 @@ __device__ __forceinline__ void quad_issue(const Plans& P, const uint2 rec, int 
   }
   const uint32_t row = 4u * rec.y + (lane & 3);
   const uint32_t nv = static_cast<uint32_t>(a.nv);
+  if (MODE == QM_EVAL || MODE == QM_PLAIN)
+    S.vox = static_cast<uint32_t>(load_i32(make_rsrc(a.vox, a.vox ? 4u * nv : 0u), 4u * row));
+  if (MODE == QM_PLAIN || MODE == QM_POWER) return;
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const Penalties& pen = P(p).pen;
@@ -251,7 +255,10 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
   auto head_fl = [&](int i) { return __builtin_amdgcn_readlane(static_cast<int>(heads.y), i & 63); };
   QuadStage<ST, NP> A, B;
   int e0 = head_e0(0), fl = head_fl(0);
-  quad_issue<ST, CP>(P, rec0, e0, fl, lane, A);
+  quad_issue<MODE, ST, CP>(P, rec0, e0, fl, lane, A);
+
+  if (MODE == QM_EVAL || MODE == QM_PLAIN)
+    for (int i = sl.w * THREADS + tid; i < a.nzero; i += sl.G * THREADS) a.d_out[a.zero[i]] = 0.0f;
 
   bool on[NP];   // plans that are not done
 #pragma unroll
@@ -366,7 +373,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
 
   // The doses of a block's quads (summed over each quad's lanes; a lane keeps
   // its own voxel, row lane & 3), their objective and residuals.
-  auto finish = [&](int q, const float (&zq)[4], int e, const uint2 rec, const RowPenalty& pen) {
+  auto finish = [&](int q, const float (&zq)[4], int e, const uint2 rec, const RowPenalty& pen, uint32_t vox) {
     const uint32_t row = 4u * rec.y + (lane & 3);
     const bool own = rec.x != 0 && row < static_cast<uint32_t>(a.nv);
     const bool count = own && (lane & ((1 << e) - 1)) < 4;
@@ -388,7 +395,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
     }
     pacc[q] += count ? F : 0.0;
     if (MODE == QM_EVAL || MODE == QM_PLAIN) {
-      if (q == 0 && count) store_f32(dout, 4u * row, d);
+      if (q == 0 && count) store_f32(dout, 4u * (a.vox ? vox : row), d);
     }
     return own ? r : 0.0f;
   };
@@ -428,7 +435,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
 #pragma unroll
       for (int q = 0; q < NT; ++q) {
         if (PEN && q < NP) pen = penalty_of(q, S.sid[q], S.tu[q], S.to[q]);
-        const float r = finish(q, z[q], quad_log2(flags), rec, pen);
+        const float r = finish(q, z[q], quad_log2(flags), rec, pen, S.vox);
         if (GRAD) {
           live[q] = active(q) && __ballot(r != 0.0f) != 0;
           rd[q] = static_cast<double>(r) * up[q];
@@ -487,11 +494,12 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
         const int p = Plans::kMany ? q : 0;
         RowPenalty pen{0.0, 0.0, 0.0, 0.0};
         const uint32_t row = 4u * rec.y + (lane & 3);
+        const uint32_t vox = a.vox && row < static_cast<uint32_t>(a.nv) ? a.vox[row] : row;
         if (PEN && row < static_cast<uint32_t>(a.nv)) {
           const Penalties& pp = P(p).pen;
           pen = penalty_of(p, pp.sid[row], pp.Tu_vox ? pp.Tu_vox[row] : 0.0f, pp.To_vox ? pp.To_vox[row] : 0.0f);
         }
-        const double r = static_cast<double>(finish(q, zq, e, rec, pen)) * up[q];
+        const double r = static_cast<double>(finish(q, zq, e, rec, pen, vox)) * up[q];
         r4[0] = quad_bcast<0>(r);
         r4[1] = quad_bcast<1>(r);
         r4[2] = quad_bcast<2>(r);
@@ -529,7 +537,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
       e0 = head_e0(i);
       fl = head_fl(i);
       rec0 = rec1;
-      quad_issue<ST, CP>(P, rec0, e0, fl, lane, nxt);
+      quad_issue<MODE, ST, CP>(P, rec0, e0, fl, lane, nxt);
       rec1 = load_rec(i + 1);
       __builtin_amdgcn_sched_barrier(0);
       compute(cur, rc, f);
@@ -835,8 +843,18 @@ __global__ __launch_bounds__(kStepThreads) void step_batch_kernel(const AdjArgs*
 
 // out = scale * D^T r from a pass's column sums; norm (nullable): each
 // workgroup's sum of squares of its entries.
-__global__ __launch_bounds__(kStepThreads) void reduce_kernel(AdjArgs a, double* norm) {
+// With `sum` one more workgroup adds parts[0..n) as wave_sum_kernel does.
+__global__ __launch_bounds__(kStepThreads) void reduce_kernel(AdjArgs a, double* norm, double* sum,
+                                                              const double* parts, int n, double add) {
   __shared__ unsigned long long sh[kStepThreads];
+  if (static_cast<int>(blockIdx.x) == step_grid(a.nb)) {
+    if (threadIdx.x >= 64) return;
+    SumLoads<8> L;
+    sum_start(parts, n, L);
+    const double s = sum_finish(parts, n, L);
+    if (threadIdx.x == 0) *sum = s + add;
+    return;
+  }
   const int tid = threadIdx.x, c = blockIdx.x * kStepCols + (tid & (kStepCols - 1)), p0 = tid / kStepCols;
   const rsrc_t ra = acc_rsrc(a, 1);
   ColParts CP;
@@ -1018,9 +1036,11 @@ int launch_wave_sum(const imrt_ctx* ctx, const double* parts, int n, double* out
   return check_launch("wave_sum_kernel");
 }
 
-int launch_reduce(const imrt_ctx* ctx, const AdjArgs& a, double* norm) {
+int launch_reduce(const imrt_ctx* ctx, const AdjArgs& a, double* norm, double* sum, const double* parts, int n,
+                  double add) {
   clear_stale_error();
-  hipLaunchKernelGGL(reduce_kernel, dim3(step_grid(a.nb)), dim3(kStepThreads), 0, ctx->stream, a, norm);
+  hipLaunchKernelGGL(reduce_kernel, dim3(step_grid(a.nb) + (sum ? 1 : 0)), dim3(kStepThreads), 0, ctx->stream, a, norm,
+                     sum, parts, n, add);
   return check_launch("reduce_kernel");
 }
 
