@@ -64,6 +64,7 @@ int forward_grid_cap(imrt_ctx* ctx, const imrt_dose* D) {
     }
   g = std::max(g, D->q_waves / 8);
   ctx->tune.fwd_wave = saved;
+  if (D->nwblocks == 0) g = std::max(g, kWaves * ctx->tune.fwd_grid_per_cu * ctx->num_cu);   // (blocks yet to come)
   return g;
 }
 
@@ -150,18 +151,20 @@ void apply_partition_targets(const imrt_ctx* ctx, imrt_dose* D) {
 
 // The dose's own partial sums, for every pass its partition may launch.
 int fit_partials(imrt_dose* D) {
+  const int cap = forward_grid_cap(D->ctx, D), len = kMaxTrials * (cap + 1) + 16;
+  if (D->partials && len <= D->partials_len) return IMRT_OK;
   dev_free(D->partials);
-  D->fwd_cap = forward_grid_cap(D->ctx, D);
-  D->partials_len = kMaxTrials * (D->fwd_cap + 1) + 16;
-  return dev_alloc(&D->partials, D->partials_len);
+  D->partials_len = 0;
+  const int rc = dev_alloc(&D->partials, len);
+  if (rc) return rc;
+  D->fwd_cap = cap;
+  D->partials_len = len;
+  return IMRT_OK;
 }
 
-// Row blocks for the forward pass (at most kFwdPartNnz nonzeros and
-// kFwdRowsMax rows each, or one longer row alone), and the adjoint partition:
-// workgroup w of G owns nonzeros [w*nnz/G, (w+1)*nnz/G) of the CSC arrays.
-int finish_dose(imrt_dose* D, const std::vector<int32_t>& row_ptr, const std::vector<int32_t>& col_ptr) {
-  if (D->fwd_st < 0)   // the forward layout, fixed with the first partition
-    D->fwd_st = (D->storage == ST_F32 && D->nb <= 65536 && D->ctx->tune.fwd_col16) ? ST_F32C16 : D->storage;
+// Row blocks for the forward pass: at most kFwdPartNnz nonzeros and
+// kFwdRowsMax rows each, or one longer row alone.
+int finish_rows(imrt_dose* D, const std::vector<int32_t>& row_ptr) {
   std::vector<int32_t> blocks, block_k0;
   blocks.push_back(0);
   int r = 0;
@@ -268,6 +271,72 @@ int finish_dose(imrt_dose* D, const std::vector<int32_t>& row_ptr, const std::ve
   wblocks.push_back(nv);
   wblock_k0.push_back(row_ptr[nv]);
 
+  D->nblocks = static_cast<int32_t>(blocks.size()) - 1;
+  D->gaps.swap(gaps);
+  D->part_epoch += 1;
+  // (a repartition replaces the previous tables)
+  for (int32_t** p : {&D->block_row, &D->block_k0, &D->wblock_row, &D->wblock_k0, &D->wblock_end}) dev_free(*p);
+  int rc;
+  if ((rc = dev_alloc(&D->block_row, blocks.size())) || (rc = dev_alloc(&D->block_k0, block_k0.size())) ||
+      (rc = dev_alloc(&D->wblock_row, wblocks.size())) || (rc = dev_alloc(&D->wblock_k0, wblock_k0.size())) ||
+      (rc = dev_alloc(&D->wblock_end, std::max<size_t>(wblock_end.size(), 1))))
+    return rc;
+  hipStream_t s = D->ctx->stream;
+  auto upload = [&](int32_t* to, const std::vector<int32_t>& v) {
+    return hipMemcpyAsync(to, v.data(), sizeof(int32_t) * v.size(), hipMemcpyHostToDevice, s);
+  };
+  IMRT_HIP(upload(D->block_row, blocks));
+  IMRT_HIP(upload(D->block_k0, block_k0));
+  IMRT_HIP(upload(D->wblock_row, wblocks));
+  IMRT_HIP(upload(D->wblock_k0, wblock_k0));
+  IMRT_HIP(upload(D->wblock_end, wblock_end));
+  IMRT_HIP(hipStreamSynchronize(s));
+  D->nwblocks = static_cast<int32_t>(wblocks.size()) - 1;   // (the blocks are there)
+  return fit_partials(D);
+}
+
+// The row blocks of a matrix that keeps the quad form are made when a pass
+// first needs them (a solve whose trials do not fit the one-read pass, or the
+// workgroup-wide forward): its one-read passes never do.
+int ensure_rows(const imrt_dose* dose) {
+  auto* D = const_cast<imrt_dose*>(dose);
+  std::lock_guard<std::mutex> lock(D->late);
+  if (D->nwblocks > 0) return IMRT_OK;
+  const int rc = use_device(D->ctx);
+  if (rc) return rc;
+  try {
+    std::vector<int32_t> rp(static_cast<size_t>(D->nv) + 1);
+    IMRT_HIP(hipMemcpy(rp.data(), D->row_ptr, sizeof(int32_t) * rp.size(), hipMemcpyDeviceToHost));
+    return finish_rows(D, rp);
+  } catch (const std::bad_alloc&) {
+    return set_error(IMRT_ENOMEM, "host allocation failed");
+  }
+}
+
+// The internal voxel order on the host (D has one).
+int host_order(const imrt_dose* dose, const int32_t** vox) {
+  auto* D = const_cast<imrt_dose*>(dose);
+  std::lock_guard<std::mutex> lock(D->late);
+  if (D->vox_host.empty()) {
+    const int rc = use_device(D->ctx);
+    if (rc) return rc;
+    try {
+      std::vector<int32_t> v(static_cast<size_t>(D->nv));
+      IMRT_HIP(hipMemcpy(v.data(), D->vox, sizeof(int32_t) * v.size(), hipMemcpyDeviceToHost));
+      D->vox_host.swap(v);
+    } catch (const std::bad_alloc&) {
+      return set_error(IMRT_ENOMEM, "host allocation failed");
+    }
+  }
+  *vox = D->vox_host.data();
+  return IMRT_OK;
+}
+
+// The adjoint partition: workgroup w of G owns nonzeros [w*nnz/G,
+// (w+1)*nnz/G) of the CSC arrays.
+int finish_columns(imrt_dose* D, const std::vector<int32_t>& col_ptr) {
+  if (D->fwd_st < 0)   // the forward layout, fixed with the first partition
+    D->fwd_st = (D->storage == ST_F32 && D->nb <= 65536 && D->ctx->tune.fwd_col16) ? ST_F32C16 : D->storage;
   const int G = adjoint_grid_for(D->ctx, D->nnz, D->adj_min_nnz);
   const int64_t nnz = D->nnz;
   auto kw = [&](int64_t w) { return w * nnz / G; };
@@ -310,42 +379,26 @@ int finish_dose(imrt_dose* D, const std::vector<int32_t>& row_ptr, const std::ve
     const int qrc = partition_quads(D);
     if (qrc) return qrc;
   }
-  D->nblocks = static_cast<int32_t>(blocks.size()) - 1;
-  D->nwblocks = static_cast<int32_t>(wblocks.size()) - 1;
-  D->gaps.swap(gaps);
   D->part_epoch += 1;
   D->adj_grid = G;
   // (a repartition replaces the previous tables)
-  for (int32_t** p : {&D->block_row, &D->block_k0, &D->wblock_row, &D->wblock_k0, &D->wblock_end, &D->wg_cols,
-                      &D->col_wlo, &D->col_whi})
-    dev_free(*p);
+  for (int32_t** p : {&D->wg_cols, &D->col_wlo, &D->col_whi}) dev_free(*p);
   dev_free(D->col_kind);
   dev_free(D->pieces);
   int rc;
-  if ((rc = dev_alloc(&D->block_row, blocks.size())) || (rc = dev_alloc(&D->block_k0, block_k0.size())) ||
-      (rc = dev_alloc(&D->wblock_row, wblocks.size())) || (rc = dev_alloc(&D->wblock_k0, wblock_k0.size())) ||
-      (rc = dev_alloc(&D->wblock_end, std::max<size_t>(wblock_end.size(), 1))) ||
-      (rc = dev_alloc(&D->wg_cols, 4 * static_cast<size_t>(G))) ||
+  if ((rc = dev_alloc(&D->wg_cols, 4 * static_cast<size_t>(G))) ||
       (rc = dev_alloc(&D->col_wlo, static_cast<size_t>(D->nb))) ||
       (rc = dev_alloc(&D->col_whi, static_cast<size_t>(D->nb))) ||
       (rc = dev_alloc(&D->col_kind, static_cast<size_t>(D->nb))) ||
       (rc = dev_alloc(&D->pieces, 2 * static_cast<size_t>(G))))
     return rc;
   hipStream_t s = D->ctx->stream;
-  IMRT_HIP(hipMemcpyAsync(D->block_row, blocks.data(), sizeof(int32_t) * blocks.size(), hipMemcpyHostToDevice, s));
-  IMRT_HIP(hipMemcpyAsync(D->block_k0, block_k0.data(), sizeof(int32_t) * block_k0.size(), hipMemcpyHostToDevice, s));
-  IMRT_HIP(hipMemcpyAsync(D->wblock_row, wblocks.data(), sizeof(int32_t) * wblocks.size(), hipMemcpyHostToDevice, s));
-  IMRT_HIP(hipMemcpyAsync(D->wblock_k0, wblock_k0.data(), sizeof(int32_t) * wblock_k0.size(),
-                          hipMemcpyHostToDevice, s));
-  IMRT_HIP(hipMemcpyAsync(D->wblock_end, wblock_end.data(), sizeof(int32_t) * wblock_end.size(),
-                          hipMemcpyHostToDevice, s));
   IMRT_HIP(hipMemcpyAsync(D->wg_cols, wg_cols.data(), sizeof(int32_t) * wg_cols.size(), hipMemcpyHostToDevice, s));
   IMRT_HIP(hipMemcpyAsync(D->col_wlo, col_wlo.data(), sizeof(int32_t) * D->nb, hipMemcpyHostToDevice, s));
   IMRT_HIP(hipMemcpyAsync(D->col_whi, col_whi.data(), sizeof(int32_t) * D->nb, hipMemcpyHostToDevice, s));
   std::vector<uint8_t> kind(D->nb);
   for (int c = 0; c < D->nb; ++c) kind[c] = static_cast<uint8_t>(std::min(col_whi[c] - col_wlo[c], 2));
   IMRT_HIP(hipMemcpyAsync(D->col_kind, kind.data(), D->nb, hipMemcpyHostToDevice, s));
-  if ((rc = fit_partials(D))) return rc;
   IMRT_HIP(hipStreamSynchronize(s));
   return IMRT_OK;
 }
@@ -461,9 +514,11 @@ int plan_fit(imrt_plan* P) {
   return fit_quad(P, 1);
 }
 
-int plan_use(imrt_plan* P) {
-  const int rc = plan_ready(P);
-  return rc ? rc : plan_fit(P);
+int plan_use(imrt_plan* P, int nt = 1) {
+  int rc = plan_ready(P);
+  if (rc) return rc;
+  if (!one_read(P->ctx, P->dose, nt, P->nstruct) && (rc = ensure_rows(P->dose))) return rc;
+  return plan_fit(P);
 }
 
 // Objective of the voxels the wave forward (or the one-read pass) skips: the
@@ -861,6 +916,7 @@ int imrt_build_dose_matrix(imrt_ctx* ctx, const imrt_geometry* geom, imrt_dtype 
     rc = build_phantom(ctx, geom, D);
     if (rc == IMRT_OK) rc = store16(D, storage);
     if (rc == IMRT_OK) rc = build_quads(D);
+    if (rc == IMRT_OK && !one_read(ctx, D, 1, 0)) rc = ensure_rows(D);
     if (rc == IMRT_OK) rc = fit_partials(D);
   } catch (const std::bad_alloc&) {
     rc = set_error(IMRT_ENOMEM, "host allocation failed");
@@ -869,11 +925,13 @@ int imrt_build_dose_matrix(imrt_ctx* ctx, const imrt_geometry* geom, imrt_dtype 
     const hipError_t e = hipMalloc(reinterpret_cast<void**>(&D->vscratch), sizeof(float) * D->nv);
     if (e != hipSuccess) rc = hip_error(e, "hipMalloc(permutation scratch)");
   }
+  const int32_t* order = nullptr;
+  if (rc == IMRT_OK && voxel_struct_out && D->vox) rc = host_order(D, &order);
   if (rc == IMRT_OK && voxel_struct_out) {
     std::vector<uint8_t> ids(D->nv);
     const hipError_t e = hipMemcpy(ids.data(), D->sid, D->nv, hipMemcpyDeviceToHost);
     if (e != hipSuccess) rc = hip_error(e, "hipMemcpy(voxel_struct)");
-    for (int32_t p = 0; rc == IMRT_OK && p < D->nv; ++p) voxel_struct_out[D->vox ? D->vox_host[p] : p] = ids[p];
+    for (int32_t p = 0; rc == IMRT_OK && p < D->nv; ++p) voxel_struct_out[order ? order[p] : p] = ids[p];
   }
   if (rc) {
     free_dose(D);
@@ -918,7 +976,7 @@ int imrt_dose_from_csr(imrt_ctx* ctx, int32_t nv, int32_t nb, int64_t nnz, const
   D->fwd_bpw = ctx->tune.fwd_bpw;
   try {
     // CSC by a stable counting sort over columns: rows stay ascending.
-    std::vector<int32_t> rp(row_ptr, row_ptr + nv + 1), cp(nb + 1, 0);
+    std::vector<int32_t> cp(nb + 1, 0);
     for (int64_t k = 0; k < nnz; ++k) cp[col_idx[k] + 1]++;
     for (int i = 0; i < nb; ++i) cp[i + 1] += cp[i];
     // (stored in the tiled slot order of the CSC arrays; unused slots zero)
@@ -949,9 +1007,10 @@ int imrt_dose_from_csr(imrt_ctx* ctx, int32_t nv, int32_t nb, int64_t nnz, const
       return hip_error(e, "upload of D");
     }
     apply_partition_targets(ctx, D);
-    rc = finish_dose(D, rp, cp);
+    rc = finish_columns(D, cp);
     if (rc == IMRT_OK) rc = store16(D, storage);
     if (rc == IMRT_OK) rc = build_quads(D);
+    if (rc == IMRT_OK && !one_read(ctx, D, 1, 0)) rc = ensure_rows(D);
     if (rc == IMRT_OK) rc = fit_partials(D);
   } catch (const std::bad_alloc&) {
     rc = set_error(IMRT_ENOMEM, "host allocation failed");
@@ -1069,7 +1128,9 @@ int export_dose(const imrt_dose* D, int32_t* row_ptr, int32_t* col_idx, float* v
       if (voxel_struct) std::memcpy(voxel_struct, sid.data(), nv);
       return IMRT_OK;
     }
-    const std::vector<int32_t>& vox = D->vox_host;
+    const int32_t* vox = nullptr;
+    const int orc = host_order(D, &vox);
+    if (orc) return orc;
     std::vector<int32_t> ipos(nv);
     for (int32_t p = 0; p < nv; ++p) ipos[vox[p]] = p;
     if (want_csr) {
@@ -1138,6 +1199,7 @@ int imrt_dose_apply(const imrt_dose* D, const float* x_dev, float* d_dev) {
     set_quad_dose(a, D, d_dev);
     return launch_quad(D->ctx, a, 1, forward_waves(1, D->fwd_waves), quad_grid(D, 1));
   }
+  if ((rc = ensure_rows(D))) return rc;
   FwdArgs a = base_fwd(D);
   a.mode = FWD_PLAIN;
   a.x = x_dev;
@@ -1212,7 +1274,9 @@ int imrt_set_structures(imrt_plan* P, const uint8_t* voxel_struct, int32_t nstru
   }
   if (voxel_struct) {
     // caller's voxel order to the internal one
-    for (int32_t p = 0; p < D->nv; ++p) ids[p] = voxel_struct[D->vox ? D->vox_host[p] : p];
+    const int32_t* order = nullptr;
+    if (D->vox && (rc = host_order(D, &order))) return rc;
+    for (int32_t p = 0; p < D->nv; ++p) ids[p] = voxel_struct[order ? order[p] : p];
   } else {
     if (!D->sid) return set_error(IMRT_EINVAL, "NULL structure ids need a dose matrix from imrt_build_dose_matrix");
     IMRT_HIP(hipMemcpy(ids.data(), D->sid, D->nv, hipMemcpyDeviceToHost));
@@ -1284,11 +1348,13 @@ int imrt_set_voxel_targets(imrt_plan* P, const float* T_under, const float* T_ov
   const imrt_dose* D = P->dose;
   std::vector<float> tu, to;
   if (D->vox) {
+    const int32_t* order = nullptr;
+    if ((rc = host_order(D, &order))) return rc;
     tu.resize(nv);
     to.resize(nv);
     for (int32_t p = 0; p < nv; ++p) {
-      tu[p] = T_under[D->vox_host[p]];
-      to[p] = T_over[D->vox_host[p]];
+      tu[p] = T_under[order[p]];
+      to[p] = T_over[order[p]];
     }
     T_under = tu.data();
     T_over = to.data();
@@ -1360,6 +1426,7 @@ int imrt_gradient_noalloc(imrt_plan* P, const float* x_dev, float* g_dev, double
   unsigned char* base = noalloc_scratch(P->ctx->device);
   if (!base) return set_error(IMRT_EINVAL, "no scratch for this device (create the context first)");
   const imrt_dose* D = P->dose;
+  if (!one_read(P->ctx, D, 1, P->nstruct) && (rc = ensure_rows(D))) return rc;   // (there, but after an option's change)
   const int grid = forward_grid(P->ctx, D, 1);
   // scratch layout, every part 256-byte aligned: residual (nv floats),
   // forward objective partials (grid doubles), adjoint pieces (2 per
@@ -1540,6 +1607,7 @@ int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev
   imrt_ctx* C = P->ctx;
   hipStream_t s = C->stream;
   const bool quads = one_read(C, D, nt, P->nstruct);
+  if (!quads && (rc = plan_use(P, nt))) return rc;
   if (!quads && forward_lds_bytes(D->nb, nt, P->nstruct, C->tune.fwd_wave != 0, D->fwd_st, D->fwd_waves) > C->max_lds)
     return set_error(IMRT_EUNSUPPORTED, "nb * trials_per_pass exceeds the LDS budget of the forward pass");
 
@@ -2223,13 +2291,18 @@ int repartition(imrt_dose* D, int32_t adj_min_nnz, int32_t fwd_blocks_per_wave, 
   IMRT_HIP(hipStreamSynchronize(s));
   if (adj_min_nnz == D->adj_min_nnz && fwd_blocks_per_wave == D->fwd_bpw && fwd_waves == D->fwd_waves) return IMRT_OK;
   try {
-    std::vector<int32_t> rp(static_cast<size_t>(D->nv) + 1), cp(static_cast<size_t>(D->nb) + 1);
-    IMRT_HIP(hipMemcpy(rp.data(), D->row_ptr, sizeof(int32_t) * rp.size(), hipMemcpyDeviceToHost));
+    std::vector<int32_t> rp, cp(static_cast<size_t>(D->nb) + 1);
+    if (D->nwblocks > 0) {
+      rp.resize(static_cast<size_t>(D->nv) + 1);
+      IMRT_HIP(hipMemcpy(rp.data(), D->row_ptr, sizeof(int32_t) * rp.size(), hipMemcpyDeviceToHost));
+    }
     IMRT_HIP(hipMemcpy(cp.data(), D->col_ptr, sizeof(int32_t) * cp.size(), hipMemcpyDeviceToHost));
     D->adj_min_nnz = adj_min_nnz;
     D->fwd_bpw = fwd_blocks_per_wave;
     D->fwd_waves = fwd_waves;
-    return finish_dose(D, rp, cp);
+    int r = finish_columns(D, cp);
+    if (!r && D->nwblocks > 0) r = finish_rows(D, rp);
+    return r ? r : fit_partials(D);
   } catch (const std::bad_alloc&) {
     return set_error(IMRT_ENOMEM, "host allocation failed");
   }

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -346,7 +347,10 @@ struct imrt_dose {
   // internal voxel order (nullable: the caller's order): row p of D is voxel
   // vox[p]; every voxel-indexed array crossing the API is permuted
   int32_t* vox = nullptr;
-  std::vector<int32_t> vox_host;
+  std::vector<int32_t> vox_host;   // downloaded when first needed (host_order)
+  // guards what a matrix gets on first use: vox_host, and the row blocks of
+  // a matrix that keeps the quad form (ensure_rows)
+  std::mutex late;
   float* vscratch = nullptr;   // nv floats for permuted products
   // structure ids from the phantom builder (nullable; internal order)
   uint8_t* sid = nullptr;
@@ -509,6 +513,9 @@ void apply_partition_targets(const imrt_ctx* ctx, imrt_dose* D);
 
 // host preprocessing (api.hip)
 int alloc_nonzeros(imrt_dose* D);
-int finish_dose(imrt_dose* D, const std::vector<int32_t>& row_ptr, const std::vector<int32_t>& col_ptr);
+int finish_columns(imrt_dose* D, const std::vector<int32_t>& col_ptr);
+int finish_rows(imrt_dose* D, const std::vector<int32_t>& row_ptr);
+int ensure_rows(const imrt_dose* D);
+int fit_partials(imrt_dose* D);
 
 }  // namespace imrt

@@ -215,18 +215,19 @@ int build_quads(imrt_dose* D) {
   const int64_t per = c16 ? 10 : 18, two = c16 ? 10 : 14;
   if (nent >= (int64_t(1) << 31) - kQuadPad) return IMRT_OK;
   if (D->ctx->tune.one_read < 2 && nent * per > D->nnz * two) return IMRT_OK;
-  std::vector<int32_t> qn, qrow;
+  std::vector<int32_t> qrow(nqa);
   std::vector<std::pair<int32_t, int32_t>> gaps;
-  qn.reserve(nqa);
-  qrow.reserve(nqa);
-  for (int q = 0; q < nqa; ++q) {
+  size_t some = 0;
+  for (int q = 0; q < nqa;) {
     if (n[q] > 0) {
-      qrow.push_back(q);
+      qrow[some++] = q++;
       continue;
     }
-    if (!gaps.empty() && gaps.back().second == 4 * q) gaps.back().second = std::min(4 * q + 4, D->nv);
-    else gaps.emplace_back(4 * q, std::min(4 * q + 4, D->nv));
+    const int q0 = q;
+    while (q < nqa && n[q] == 0) ++q;
+    gaps.emplace_back(4 * q0, std::min(4 * q, D->nv));
   }
+  qrow.resize(some);
   const int nq = static_cast<int>(qrow.size());
   for (const auto& gap : gaps) D->nzero += gap.second - gap.first;
   if (D->nzero > 0) {
@@ -251,9 +252,10 @@ int build_quads(imrt_dose* D) {
     }
   }
   std::vector<int32_t> order(2 * static_cast<size_t>(nq) + 1);   // rows, first entries
+  std::vector<int32_t> qn(nq);
   int64_t at = 0;
   for (int i = 0; i < nq; ++i) {
-    qn.push_back(n[qrow[i]]);
+    qn[i] = n[qrow[i]];
     order[i] = qrow[i];
     order[static_cast<size_t>(nq) + i] = static_cast<int32_t>(at);
     at += qn[i];
