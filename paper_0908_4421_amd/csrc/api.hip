@@ -1608,7 +1608,7 @@ int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev
   hipStream_t s = C->stream;
   const bool quads = one_read(C, D, nt, P->nstruct);
   if (!quads && (rc = plan_use(P, nt))) return rc;
-  if (!quads && forward_lds_bytes(D->nb, nt, P->nstruct, C->tune.fwd_wave != 0, D->fwd_st, D->fwd_waves) > C->max_lds)
+  if (forward_lds_bytes(D->nb, nt, P->nstruct, C->tune.fwd_wave != 0, D->fwd_st, D->fwd_waves) > C->max_lds)
     return set_error(IMRT_EUNSUPPORTED, "nb * trials_per_pass exceeds the LDS budget of the forward pass");
 
   // x_1 >= 0 and finite (initialisation of the method)
