@@ -460,6 +460,7 @@ void free_plan(imrt_plan* P) {
   dev_free(P->pieces_col);
   dev_free(P->q_acc);
   dev_free(P->q_unit);
+  dev_free(P->whole);
   dev_free(P->misc);
   dev_free(P->st);
   dev_free(P->trace);
@@ -1726,6 +1727,51 @@ hipError_t solve_start(imrt_plan* P, int nt, const float* x) {
   return e;
 }
 
+// A plan solved alone takes its steps and passes in one launch where the step
+// is small enough for every workgroup to repeat: a column per thread, and at
+// most kWholeSums column sums to add.  Launches set the time of such plans.
+constexpr int64_t kWholeSums = 1 << 14;
+
+bool whole_passes(const imrt_plan* P, const imrt_solve_params* prm, int nt) {
+  const imrt_dose* D = P->dose;
+  return nt == 1 && prm->profile == 0 && one_read(P->ctx, D, 1, P->nstruct) && D->fwd_waves == 16 && D->nb <= 16 * 64 &&
+         static_cast<int64_t>(quad_grid(D, 1)) * D->nb <= kWholeSums;
+}
+
+// The two copies of its iteration state.
+int fit_whole(imrt_plan* P, WholeSet (&set)[2]) {
+  const imrt_dose* D = P->dose;
+  auto up = [](size_t n) { return (n + 255) & ~static_cast<size_t>(255); };
+  const size_t nb = static_cast<size_t>(D->nb), vec = up(4 * nb), steps = up(8 * static_cast<size_t>(step_grid(D->nb)));
+  const size_t parts = up(8 * static_cast<size_t>(quad_parts(D))), acc = up(8 * nb * quad_grid(D, 1));
+  const size_t one = 3 * vec + steps + parts + acc + 2 * 256;
+  if (2 * one > P->whole_cap) {
+    dev_free(P->whole);
+    P->whole_cap = 0;
+    const int rc = dev_alloc(&P->whole, 2 * one);
+    if (rc) return rc;
+    P->whole_cap = 2 * one;
+  }
+  static_assert(sizeof(SolverState) <= 256, "a state takes one place");
+  for (int k = 0; k < 2; ++k) {
+    char* p = P->whole + k * one;
+    auto take = [&](size_t n) {
+      char* at = p;
+      p += n;
+      return at;
+    };
+    set[k].xk = reinterpret_cast<float*>(take(vec));
+    set[k].g = reinterpret_cast<float*>(take(vec));
+    set[k].xt = reinterpret_cast<float*>(take(vec));
+    set[k].steps = reinterpret_cast<double*>(take(steps));
+    set[k].parts = reinterpret_cast<double*>(take(parts));
+    set[k].acc = reinterpret_cast<unsigned long long*>(take(acc));
+    set[k].unit = reinterpret_cast<double*>(take(256));
+    set[k].st = reinterpret_cast<SolverState*>(take(256));
+  }
+  return IMRT_OK;
+}
+
 int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_solve_result* res) {
   if (!res) return set_error(IMRT_EINVAL, "result is NULL");
   int nt = 1, cap = 0, rc;
@@ -1735,6 +1781,9 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
   imrt_ctx* C = P->ctx;
   hipStream_t s = C->stream;
   P->st_host[0] = init;
+  const bool whole = whole_passes(P, prm, nt);
+  WholeSet set[2];
+  if (whole && (rc = fit_whole(P, set))) return rc;
 
   hipEvent_t ev_start = nullptr, ev_end = nullptr, ev_poll[2] = {nullptr, nullptr};
   // profile mode: HIP events around every profile-th forward and adjoint launch
@@ -1779,6 +1828,13 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
   if (e == hipSuccess) e = hipMemcpyAsync(P->st, &P->st_host[0], sizeof(SolverState), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(P->st + 1, &P->st_host[0], sizeof(SolverState), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = solve_start(P, nt, x_dev);
+  if (whole) {
+    // the first copy: x_1 as iterate and as the trial of the initial evaluation
+    const size_t nb4 = sizeof(float) * D->nb;
+    if (e == hipSuccess) e = hipMemcpyAsync(set[0].st, &P->st_host[0], sizeof(SolverState), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(set[0].xk, x_dev, nb4, hipMemcpyDeviceToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(set[0].xt, x_dev, nb4, hipMemcpyDeviceToDevice, s);
+  }
   if (e != hipSuccess) {
     cleanup();
     return hip_error(e, "solve setup");
@@ -1816,8 +1872,25 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
     return rr;
   };
 
+  WholeArgs wa{};
+  wa.trace = aa.trace;
+  wa.G_skip = aa.G_skip;
+  auto whole_pass = [&]() -> int {
+    wa.in = set[pass & 1];
+    wa.out = set[(pass + 1) & 1];
+    wa.first = pass == 0;
+    ++pass;
+    return launch_whole(C, fa, wa, grid);
+  };
+  auto group = [&]() -> int {
+    if (whole) return whole_pass();
+    const int r = adjoint_pass();
+    return r ? r : forward_pass();
+  };
+  auto state_now = [&]() { return whole ? set[pass & 1].st : state_in(); };
+
   // initial evaluation G(x_1)
-  if ((rc = forward_pass())) {
+  if ((rc = whole ? whole_pass() : forward_pass())) {
     (void)hipStreamSynchronize(s);
     cleanup();
     return rc;
@@ -1847,7 +1920,7 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
     }
     if (batch > 0 && nq < 2) {
       for (long long i = 0; i < batch; ++i) {
-        if ((rc = adjoint_pass()) || (rc = forward_pass())) {
+        if ((rc = group())) {
           (void)hipStreamSynchronize(s);
           cleanup();
           return rc;
@@ -1856,7 +1929,7 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
       enq += batch;
       const int slot = next_slot;
       next_slot ^= 1;
-      e = hipMemcpyAsync(&P->st_host[slot], state_in(), sizeof(SolverState), hipMemcpyDeviceToHost, s);
+      e = hipMemcpyAsync(&P->st_host[slot], state_now(), sizeof(SolverState), hipMemcpyDeviceToHost, s);
       if (e == hipSuccess) e = hipEventRecord(ev_poll[slot], s);
       if (e != hipSuccess) {
         (void)hipStreamSynchronize(s);
@@ -1889,13 +1962,14 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
   }
   // final state and iterate
   e = hipStreamSynchronize(s);
-  if (e == hipSuccess) e = hipMemcpy(&P->st_host[0], state_in(), sizeof(SolverState), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = hipMemcpy(&P->st_host[0], state_now(), sizeof(SolverState), hipMemcpyDeviceToHost);
   const int xi = P->st_host[0].xi;
   if (e == hipSuccess && (xi < 0 || xi > nt)) {
     cleanup();
     return set_error(IMRT_EINVAL, "internal: iterate buffer index out of range");
   }
-  if (e == hipSuccess) e = hipMemcpyAsync(x_dev, P->xbuf[xi], sizeof(float) * D->nb, hipMemcpyDeviceToDevice, s);
+  const float* x_end = whole ? set[pass & 1].xk : P->xbuf[xi];
+  if (e == hipSuccess) e = hipMemcpyAsync(x_dev, x_end, sizeof(float) * D->nb, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess) e = hipEventRecord(ev_end, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   float ms = 0.f;

@@ -143,9 +143,26 @@ enum QuadMode : int32_t {
   QM_EVAL = 1,    // objective of x, dose optional
   QM_GRAD = 2,    // objective and gradient of x
   QM_PLAIN = 3,   // dose of x, partials of sum d^2
-  QM_POWER = 4    // D^T D of w / ||w||, partials of sum d^2
+  QM_POWER = 4,   // D^T D of w / ||w||, partials of sum d^2
+  QM_WHOLE = 5    // a small plan's step and pass in one
 };
-constexpr bool quad_grad(int mode) { return mode == QM_SOLVE || mode == QM_GRAD || mode == QM_POWER; }
+constexpr bool quad_grad(int mode) { return mode != QM_EVAL && mode != QM_PLAIN; }
+
+// A small plan's iteration state, of which a launch reads one copy and writes
+// the other: iterate, gradient and trial, step norms (per 16 columns), unit,
+// objective partials and column sums of its pass, solver state.
+struct WholeSet {
+  float *xk, *g, *xt;
+  double *steps, *unit, *parts;
+  unsigned long long* acc;
+  SolverState* st;
+};
+struct WholeArgs {
+  WholeSet in, out;
+  TraceDev* trace;
+  double G_skip;
+  int32_t first;   // the initial evaluation: no decision yet
+};
 
 struct FwdArgs {
   const int32_t* row_ptr;
@@ -384,6 +401,8 @@ struct imrt_plan {
   // one-read pass: column sums of its workgroups, their units, step norms
   unsigned long long* q_acc = nullptr;
   size_t q_acc_cap = 0;
+  char* whole = nullptr;          // both copies of a small plan's iteration state
+  size_t whole_cap = 0;
   double* q_unit = nullptr;       // kMaxTrials units, 2 kMaxTrials step_grid(nb) step norms, step_grid(nb) squares
   double* misc = nullptr;         // small reduction scratch
   imrt::SolverState* st = nullptr;  // 2 states, alternately read and written by consecutive passes
@@ -479,6 +498,7 @@ int store16(imrt_dose* D, int storage);
 size_t quad_lds_bytes(int nb, int ntrials, int nstruct, int mode);
 int launch_quad(const imrt_ctx* ctx, const FwdArgs& a, int ntrials, int waves, int grid, hipEvent_t before = nullptr,
                 hipEvent_t after = nullptr);
+int launch_whole(const imrt_ctx* ctx, const FwdArgs& a, const WholeArgs& w, int grid);
 int launch_step(const imrt_ctx* ctx, const AdjArgs& a, int ntrials, hipEvent_t before = nullptr,
                 hipEvent_t after = nullptr);
 int launch_quad_batch(const imrt_ctx* ctx, const FwdArgs* args, const int32_t* slots, int nslots, int ntrials,

@@ -195,3 +195,24 @@ def test_row_blocks_made_when_first_needed():
         assert np.max(np.abs(to_host(lib.apply(to_dev(x1))) - z)) <= eps * np.max(np.abs(z))
     for (k, m, s, _, Ga), (k2, m2, s2, _, Gb) in zip(*tr):
         assert (k, m, s) == (k2, m2, s2) and abs(Ga - Gb) <= 1e-5 * Gb
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("nv,nb,longest", [(9, 2, 2), (403, 17, 9), (1501, 211, 40), (2003, 1024, 25)])
+def test_one_launch_per_iteration_equals_two(nv, nb, longest, storage):
+    """A small plan's launch that decides, steps and passes in one gives the
+    bits of the two launches that a profiled solve keeps; with the stopping
+    rule, backtracks and resumption too.  (1,024 beamlets: one per thread.)"""
+    D, sid = _matrix(nv, nb, longest, seed=nv)
+    ctx, lib, plan = _plan(D, sid, storage, 2)
+    x1 = np.ones(nb, np.float32)
+    lam, _ = plan.lambda0(to_dev(x1), 20)
+    for kw in (dict(max_iter=30, fixed_iters=True), dict(max_iter=400, delta=1e-4, warm_start=True),
+               dict(max_iter=5, fixed_iters=True, warm_start=True), dict(max_iter=0)):
+        out = []
+        for profile in (0, 3):
+            x = to_dev(x1)
+            res, t = plan.solve(x, eps=1e-4, alpha=2.0, lambda0=4 * lam, trace=True, profile=profile, **kw)
+            out.append((t, to_host(x).tobytes(), res.G_initial, res.G_final, res.iterations, res.status,
+                        res.forward_passes, res.adjoint_passes))
+        assert out[0] == out[1], kw
