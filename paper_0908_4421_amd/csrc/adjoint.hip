@@ -34,6 +34,17 @@ __device__ __forceinline__ int logical_wg(const Slot sl, bool xcd_map) {
   return (xcd_map && G % kXcds == 0) ? (w % kXcds) * (G / kXcds) + w / kXcds : w;
 }
 
+// The nonzeros of workgroup lw.
+__device__ __forceinline__ void wg_range(const AdjArgs& a, int lw, int& k0, int& k1) {
+  if (a.wg_k != nullptr) {
+    k0 = uniform(a.wg_k[lw]);
+    k1 = uniform(a.wg_k[lw + 1]);
+  } else {
+    k0 = split_point(lw, static_cast<int>(a.nnz), a.grid);
+    k1 = split_point(lw + 1, static_cast<int>(a.nnz), a.grid);
+  }
+}
+
 // rv covers the value array from the same entry as ri: float32 values in
 // the index slots' order, or 16-bit codes in that order at half the width.
 template <int ST, int CP = 0>
@@ -176,8 +187,8 @@ __device__ __forceinline__ void adj_pass(const AdjArgs& a, const Slot sl) {
   __shared__ Decision dec;
   const int tid = threadIdx.x;
   const int lw = logical_wg(sl, a.xcd_map != 0);
-  const int k0w = split_point(lw, static_cast<int>(a.nnz), a.grid);
-  const int k1w = split_point(lw + 1, static_cast<int>(a.nnz), a.grid);
+  int k0w, k1w;
+  wg_range(a, lw, k0w, k1w);
   const int kb = k0w & ~(kTile - 1);
   const int nrounds = (k1w > kb) ? (k1w - kb + kAdjStep - 1) / kAdjStep : 0;
   // whole tiles: entries of a partial tile sit anywhere in it
@@ -325,8 +336,8 @@ __device__ __forceinline__ void adj_multi_pass(const AdjArgs* __restrict__ args,
   const AdjArgs& a = args[uniform(plans[0])];   // the shared matrix and partition
   const int tid = threadIdx.x;
   const int lw = logical_wg(sl, a.xcd_map != 0);
-  const int k0w = split_point(lw, static_cast<int>(a.nnz), a.grid);
-  const int k1w = split_point(lw + 1, static_cast<int>(a.nnz), a.grid);
+  int k0w, k1w;
+  wg_range(a, lw, k0w, k1w);
   const int kb = k0w & ~(kTile - 1);
   const int nrounds = (k1w > kb) ? (k1w - kb + kAdjStep - 1) / kAdjStep : 0;
   const uint32_t bytes = static_cast<uint32_t>((((k1w + kTile - 1) & ~(kTile - 1)) - kb) * 4);
@@ -616,7 +627,7 @@ int launch_adjoint(const imrt_ctx* ctx, const imrt_dose* D, const AdjArgs& a, in
   if (rc) return rc;
   rc = check_launch("adj_kernel");
   if (rc) return rc;
-  if (!a.solve) {
+  if (!a.solve && a.wg_k == nullptr) {
     // shared columns completed here (in a solve the next forward pass
     // completes them while it stages its trial points)
     const int g2 = (a.nb + kThreads - 1) / kThreads;

@@ -339,7 +339,26 @@ int finish_columns(imrt_dose* D, const std::vector<int32_t>& col_ptr) {
     D->fwd_st = (D->storage == ST_F32 && D->nb <= 65536 && D->ctx->tune.fwd_col16) ? ST_F32C16 : D->storage;
   const int G = adjoint_grid_for(D->ctx, D->nnz, D->adj_min_nnz);
   const int64_t nnz = D->nnz;
-  auto kw = [&](int64_t w) { return w * nnz / G; };
+  // Where no column is longer than half a share, the bounds go to the nearest
+  // column starts: no column is then shared, and a product needs no second
+  // launch to complete such columns, for shares a quarter off at most (13.5 ->
+  // 10.9 us for 3,333 columns of 490 nonzeros, shares of 1,600).  Longer columns
+  // keep equal shares: uneven ones cost a large matrix more than the launch.
+  int32_t longest = 0;
+  for (int c = 0; c < D->nb; ++c) longest = std::max(longest, col_ptr[c + 1] - col_ptr[c]);
+  std::vector<int32_t> wg_k;
+  if (2 * static_cast<int64_t>(longest) * G <= nnz) {
+    wg_k.resize(static_cast<size_t>(G) + 1);
+    int c = 0;
+    for (int64_t w = 0; w < G; ++w) {
+      const int64_t share = w * nnz / G;
+      while (c < D->nb && col_ptr[c + 1] <= share) ++c;   // share lies in [col_ptr[c], col_ptr[c + 1])
+      const bool up = c < D->nb && 2 * share >= static_cast<int64_t>(col_ptr[c]) + col_ptr[c + 1];
+      wg_k[w] = w == 0 ? 0 : col_ptr[up ? c + 1 : c];
+    }
+    wg_k[G] = static_cast<int32_t>(nnz);
+  }
+  auto kw = [&](int64_t w) { return wg_k.empty() ? w * nnz / G : static_cast<int64_t>(wg_k[w]); };
   std::vector<int32_t> wg_c0(G, 0), wg_c1(G, 0), col_wlo(D->nb), col_whi(D->nb);
   for (int w = 0; w < G; ++w) {
     wg_c0[w] = D->nb;
@@ -382,7 +401,7 @@ int finish_columns(imrt_dose* D, const std::vector<int32_t>& col_ptr) {
   D->part_epoch += 1;
   D->adj_grid = G;
   // (a repartition replaces the previous tables)
-  for (int32_t** p : {&D->wg_cols, &D->col_wlo, &D->col_whi}) dev_free(*p);
+  for (int32_t** p : {&D->wg_cols, &D->wg_k, &D->col_wlo, &D->col_whi}) dev_free(*p);
   dev_free(D->col_kind);
   dev_free(D->pieces);
   int rc;
@@ -393,6 +412,10 @@ int finish_columns(imrt_dose* D, const std::vector<int32_t>& col_ptr) {
       (rc = dev_alloc(&D->pieces, 2 * static_cast<size_t>(G))))
     return rc;
   hipStream_t s = D->ctx->stream;
+  if (!wg_k.empty()) {
+    if ((rc = dev_alloc(&D->wg_k, wg_k.size()))) return rc;
+    IMRT_HIP(hipMemcpyAsync(D->wg_k, wg_k.data(), sizeof(int32_t) * wg_k.size(), hipMemcpyHostToDevice, s));
+  }
   IMRT_HIP(hipMemcpyAsync(D->wg_cols, wg_cols.data(), sizeof(int32_t) * wg_cols.size(), hipMemcpyHostToDevice, s));
   IMRT_HIP(hipMemcpyAsync(D->col_wlo, col_wlo.data(), sizeof(int32_t) * D->nb, hipMemcpyHostToDevice, s));
   IMRT_HIP(hipMemcpyAsync(D->col_whi, col_whi.data(), sizeof(int32_t) * D->nb, hipMemcpyHostToDevice, s));
@@ -428,6 +451,7 @@ void free_dose(imrt_dose* D) {
   dev_free(D->wblock_k0);
   dev_free(D->wblock_end);
   dev_free(D->wg_cols);
+  dev_free(D->wg_k);
   dev_free(D->col_wlo);
   dev_free(D->col_whi);
   dev_free(D->col_kind);
@@ -720,6 +744,7 @@ AdjArgs base_adj(const imrt_dose* D) {
   a.storage = D->storage;
   a.col_ptr = D->col_ptr;
   a.wg_cols = D->wg_cols;
+  a.wg_k = D->wg_k;
   a.col_wlo = D->col_wlo;
   a.col_whi = D->col_whi;
   a.col_kind = D->col_kind;

@@ -220,7 +220,8 @@ struct FwdArgs {
 };
 
 // Adjoint work partition: workgroup w owns nonzeros [w*nnz/G, (w+1)*nnz/G)
-// of the CSC arrays, i.e. columns [c0, c1) in part or whole, where
+// of the CSC arrays, or where columns are short against that [wg_k[w],
+// wg_k[w + 1]), the same rounded to column starts: columns [c0, c1) in part or whole, where
 // wg_cols[4w..4w+3] = {c0, c1, lo, hi} and [lo, hi) is the part of column c0
 // inside the range (c0 = c1 = lo = hi = 0 without columns).
 // Column c is shared by workgroups col_wlo[c]..col_whi[c]; a shared column is
@@ -235,6 +236,7 @@ struct AdjArgs {
   int32_t stream_cp;         // host side: cache policy of a solve pass's matrix streams (0 or 2)
   const int32_t* col_ptr;
   const int32_t* wg_cols;
+  const int32_t* wg_k;       // nullable
   const int32_t* col_wlo;
   const int32_t* col_whi;
   const uint8_t* col_kind;   // 0: one adjoint workgroup, 1: two, 2: more
@@ -343,6 +345,7 @@ struct imrt_dose {
   int64_t part_epoch = 0;
   int32_t adj_grid = 0;        // workgroups of the adjoint partition
   int32_t* wg_cols = nullptr;
+  int32_t* wg_k = nullptr;     // bounds at column starts (null: equal shares)
   int32_t* col_wlo = nullptr;
   int32_t* col_whi = nullptr;
   uint8_t* col_kind = nullptr; // per column: 0 one adjoint workgroup, 1 two, 2 more
