@@ -198,11 +198,12 @@ def test_row_blocks_made_when_first_needed():
 
 
 @pytest.mark.parametrize("storage", ["f32", "bf16", "f16"])
-@pytest.mark.parametrize("nv,nb,longest", [(9, 2, 2), (403, 17, 9), (1501, 211, 40), (2003, 1024, 25)])
+@pytest.mark.parametrize("nv,nb,longest", [(9, 2, 2), (403, 17, 9), (1501, 211, 40), (2003, 1024, 25), (20003, 130, 25)])
 def test_one_launch_per_iteration_equals_two(nv, nb, longest, storage):
     """A small plan's launch that decides, steps and passes in one gives the
     bits of the two launches that a profiled solve keeps; with the stopping
-    rule, backtracks and resumption too.  (1,024 beamlets: one per thread.)"""
+    rule, backtracks and resumption too.  (1,024 beamlets: one per thread;
+    20,003 rows: several rounds of column sums.)"""
     D, sid = _matrix(nv, nb, longest, seed=nv)
     ctx, lib, plan = _plan(D, sid, storage, 2)
     x1 = np.ones(nb, np.float32)
