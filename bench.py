@@ -19,7 +19,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
-KERNEL_SOURCES = tuple("paper_0908_4421_amd/csrc/" + f for f in ("forward.hip", "adjoint.hip", "pass_common.h", "imrt_internal.h"))
+KERNEL_SOURCES = tuple("paper_0908_4421_amd/csrc/" + f for f in (
+    "forward.hip", "adjoint.hip", "onepass.hip", "decide.h", "pass_common.h", "imrt_internal.h"))
 # counter summaries per workload (by phantom name)
 TRAFFIC_PROFILES = {
     "prostate_160x104x80_2.5mm_9field": os.path.join(ROOT, "profiles", "hbm_traffic_fwd_adj_prostate_160x104x80.txt"),
@@ -71,6 +72,36 @@ def adjoint_bytes16(nr, nb, nnz):
     """The same with 16-bit storage: int32 row index and 16-bit code, plus the
     beamlet scales."""
     return 6 * nnz + 4 * (nb + 1) + 4 * nr + 8 * nb
+
+
+def pass_model(ctx, dose, nr, nt=1, code=0):
+    """(kernel names, algorithmic bytes per launch) of a solve's two launches
+    per iteration.  One-read pass: the quad form's entries once, structure ids
+    of the rows with nonzeros, trial points, column sums out; then its step:
+    the column sums of one trial in, iterate, gradient and trials in and out.
+    Otherwise the forward and adjoint passes."""
+    from paper_0908_4421_amd.imrt import imrt_dose_one_read
+    nb, nnz = dose.nb, dose.nnz
+    entries, wgs = imrt_dose_one_read(dose.handle)
+    if entries and ctx.get_option("fwd_wave"):
+        names = {"forward": f"quad_kernel<{nt}, 0, {16 if nt <= 2 else 8}, {code}, ", "adjoint": f"step_kernel<{nt}>("}
+        sums = wgs * nb * 8
+        return names, {"forward": entries * (10 if code else 18) + nr + 4 * nb * nt + sums * nt,
+                       "adjoint": sums + 4 * nb * (2 * nt + 4)}
+    lay, fwd_model = f32_forward(ctx, nb)
+    if code:
+        lay, fwd_model = code, forward_bytes16
+    wave = ctx.get_option("fwd_wave")
+    names = {"forward": f"fwd_wave_kernel<{nt}, 0, {16 if nt <= 2 else 8}, {lay}, " if wave else f"fwd_kernel<{nt}>(",
+             "adjoint": f"adj_kernel<{nt}, true, {code}, "}
+    return names, {"forward": fwd_model(nr, nb, nnz),
+                   "adjoint": (adjoint_bytes16 if code else adjoint_bytes)(nr, nb, nnz)}
+
+
+def plan_bytes(ctx, res, dose, nr, nt=1):
+    """Algorithmic bytes of a finished solve's launches."""
+    _, b = pass_model(ctx, dose, nr, nt)
+    return res.forward_passes * b["forward"] + res.adjoint_passes * b["adjoint"]
 
 
 def nonempty_rows(dose):
@@ -153,12 +184,9 @@ def storage_form(ctx, spec, st, args, storage, plan32, res32, ms32):
           flush=True)
     nt = args.trials_per_pass
     code = {"bf16": 1, "f16": 2}[storage]
-    names = {"forward": f"fwd_wave_kernel<{nt}, 0, {16 if nt <= 2 else 8}, {code}, ",
-             "adjoint": f"adj_kernel<{nt}, true, {code}, "}
     nv, nb, nnz = dose.nv, dose.nb, dose.nnz
-    nr = nonempty_rows(dose)
-    kern = kernel_table(runs, res, names, {"forward": forward_bytes16(nr, nb, nnz),
-                                           "adjoint": adjoint_bytes16(nr, nb, nnz)})
+    names, nbytes = pass_model(ctx, dose, nonempty_rows(dose), nt, code)
+    kern = kernel_table(runs, res, names, nbytes)
     d16 = torch.empty(nv, dtype=torch.float32, device="cuda")
     d32 = torch.empty(nv, dtype=torch.float32, device="cuda")
     G16 = pl.objective(x, d16)
@@ -263,8 +291,7 @@ def batch_form(ctx, args):
     same = all(a.iterations == b.iterations and a.G_final == b.G_final and torch.equal(xa, xb)
                for a, b, xa, xb in zip(rs, rb, x_solo, xs))
     nrs = [nonempty_rows(d) for d in doses]
-    nbytes = sum(r.forward_passes * f32_forward(ctx, d.nb)[1](nr, d.nb, d.nnz) +
-                 r.adjoint_passes * adjoint_bytes(nr, d.nb, d.nnz) for r, d, nr in zip(rb, doses, nrs))
+    nbytes = sum(plan_bytes(ctx, r, d, nr) for r, d, nr in zip(rb, doses, nrs))
     iters = sum(r.iterations for r in rb)
     print(f"[bench] batch of {len(specs)}: {iters} iterations, {batch_s * 1e3:.1f} ms batched, "
           f"{solo_default_s * 1e3:.1f} ms one by one", file=sys.stderr, flush=True)
@@ -366,8 +393,7 @@ def replan_form(ctx, plan, x, spec, st, args):
                                          "forward_passes": rw.forward_passes, "G_final": rw.G_final,
                                          "target_voxels_within_3pct": float(np.mean(relw <= 0.03))}
     nr = nonempty_rows(dose)
-    nbytes = res.forward_passes * f32_forward(ctx, dose.nb)[1](nr, dose.nb, dose.nnz) + \
-        res.adjoint_passes * adjoint_bytes(nr, dose.nb, dose.nnz)
+    nbytes = plan_bytes(ctx, res, dose, nr)
     print(f"[bench] re-plan on {day.name}: {res.iterations} iterations, {ms:.2f} ms", file=sys.stderr, flush=True)
     return {
         "workload": f"{day.name}: targets = original plan's dose (per voxel), x0 = {st.x0}",
@@ -414,10 +440,8 @@ def shape_form(ctx, args, spec=None, note=SCENARIO3_NOTE):
     nv, nb, nnz = dose.nv, dose.nb, dose.nnz
     nr = nonempty_rows(dose)
     nt = args.trials_per_pass
-    lay, fwd_model = f32_forward(ctx, nb)
-    names = {"forward": f"fwd_wave_kernel<{nt}, 0, {16 if nt <= 2 else 8}, {lay}, ",
-             "adjoint": f"adj_kernel<{nt}, true, 0, "}
-    kern = kernel_table(runs, res, names, {"forward": fwd_model(nr, nb, nnz), "adjoint": adjoint_bytes(nr, nb, nnz)})
+    names, nbytes = pass_model(ctx, dose, nr, nt)
+    kern = kernel_table(runs, res, names, nbytes)
     print(f"[bench] {spec.name}: {res.iterations} iterations, {ms:.2f} ms per plan, forward "
           f"{kern['forward']['frac_of_peak']:.2f} / adjoint {kern['adjoint']['frac_of_peak']:.2f} of peak",
           file=sys.stderr, flush=True)
@@ -494,8 +518,8 @@ def shard_form(ctx, dose, spec, iters=100):
         res, _ = p.solve(x, **kw)
         tf, ta = 1e3 * res.forward_kernel_ms, 1e3 * res.adjoint_kernel_ms
         nr = nonempty_rows(d)
-        bf = f32_forward(ctx, nb)[1](nr, nb, d.nnz)
-        ba = adjoint_bytes(nr, nb, d.nnz)
+        _, b = pass_model(ctx, d, nr)
+        bf, ba = b["forward"], b["adjoint"]
         return {"rows": d.nv, "nnz": d.nnz, "forward_us": tf, "adjoint_us": ta,
                 "forward_GB_s": bf / (tf * 1e-6) / 1e9, "adjoint_GB_s": ba / (ta * 1e-6) / 1e9}
 
@@ -582,13 +606,9 @@ def serve_stream(ctx, reqs, budget, paced, st, storage):
 
     def pct(v):
         return {"n": len(v), "p50": _pct(v, 50), "p99": _pct(v, 99), "max": max(v) if v else None}
-    # (the server does not report a plan's rows with nonzeros: its voxel
-    # count stands in, which overstates the bytes of plans with empty rows)
-    def fb(nv, nb, nnz):
-        return f32_forward(ctx, nb)[1](nv, nb, nnz) if storage == "f32" else forward_bytes16(nv, nb, nnz)
-    ab = adjoint_bytes if storage == "f32" else adjoint_bytes16
-    nbytes = sum(x.forward_passes * fb(t.nv, t.nb, t.nnz) + x.adjoint_passes * ab(t.nv, t.nb, t.nnz)
-                 for x, t in zip(res, times))
+    # (the server does not report the entries that its passes read: a value
+    # per nonzero once an iteration stands in, which understates their bytes)
+    nbytes = sum(x.forward_passes * (4 if storage == "f32" else 2) * t.nnz for x, t in zip(res, times))
     its = sorted(x.iterations for x in res)
     status = {}
     for x in res:
@@ -608,7 +628,7 @@ def serve_stream(ctx, reqs, budget, paced, st, storage):
         "iterations_total": sum(its),
         "iterations": {"p50": _pct(its, 50), "p99": _pct(its, 99), "max": its[-1]},
         "status_counts": status,
-        "GB_s_voxel_count_bound": nbytes / span / 1e9,
+        "GB_s_values_once": nbytes / span / 1e9,
         "peak_resident_GB": stats["peak_bytes"] / 1e9,
         "resident_matrices": stats["resident_matrices"],
     }
@@ -884,13 +904,9 @@ def main():
 
     nv, nb, nnz = dose.nv, dose.nb, dose.nnz
     nr = nonempty_rows(dose)
-    wave = ctx.get_option("fwd_wave")
     nt = args.trials_per_pass
-    lay, fwd_model = f32_forward(ctx, nb)
-    names = {"forward": f"fwd_wave_kernel<{nt}, 0, {16 if nt <= 2 else 8}, {lay}, " if wave else f"fwd_kernel<{nt}>(",
-             "adjoint": f"adj_kernel<{nt}, true, 0, "}
-    kern = kernel_table(runs, res, names, {"forward": fwd_model(nr, nb, nnz),
-                                           "adjoint": adjoint_bytes(nr, nb, nnz)})
+    names, nbytes = pass_model(ctx, dose, nr, nt)
+    kern = kernel_table(runs, res, names, nbytes)
     dom = max(kern, key=lambda k: kern[k]["total_ms"])
     probe = read_probe(ctx)
     roofline = {"bound": "hbm", "achieved": kern[dom]["GB_s"], "peak": HBM_PEAK_GBS, "unit": "GB/s",

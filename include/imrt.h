@@ -211,17 +211,24 @@ IMRT_API int imrt_ctx_stream(const imrt_ctx* ctx, void** hip_stream_out);
  *   "serve_shared_adjoint"  1: live solves of a server created afterwards
  *                    that share a resident dose matrix (re-plans of one
  *                    patient) take their gradients from one pass over its
- *                    CSC, up to four solves per pass, each solve's
+ *                    CSC (or its quad form), up to four solves per pass, each solve's
  *                    arithmetic unchanged; 0 (default): one pass per solve.
  *                    Sharing saves the matrix's reads but puts several
  *                    solves' work in each workgroup: for matrices that stay
  *                    in the last-level cache one pass per solve is faster
+ *   "one_read"       1 (default): matrices created afterwards, of at most 8,191
+ *                    beamlets, also keep the quad form (four rows share one
+ *                    list of columns) where reading it once costs no more
+ *                    bytes than the CSR and the CSC together; objectives,
+ *                    gradients, step sizes, solves and doses then take the
+ *                    one-read pass.  2: wherever it fits; 0: never
  *   "stream_nt"      cache policy of the matrix streams in the passes of
  *                    imrt_solve and imrt_solve_batch: 0 default policy, 1
  *                    non-temporal, 2 (default) non-temporal when the CSR and
- *                    CSC bytes one iteration reads (a batch: its unfinished
- *                    plans' distinct matrices together) exceed the 256 MB
- *                    last-level cache.  Results are the same under every
+ *                    CSC bytes one iteration of the two separate passes reads
+ *                    (a batch: its unfinished plans' distinct matrices
+ *                    together) exceed the 256 MB last-level cache; one-read
+ *                    passes then keep the default policy.  Results are the same under every
  *                    policy; a server's passes keep the default policy
  *   "fwd_wave"       1: each wave of a forward workgroup streams its own row
  *                    blocks; 0: the whole workgroup shares each row block
@@ -230,8 +237,8 @@ IMRT_API int imrt_ctx_stream(const imrt_ctx* ctx, void** hip_stream_out);
  *                    which the wave forward pass reads (6 instead of 8 bytes
  *                    per nonzero, 768-entry row blocks); 0: 32-bit indices
  *   "batch_iters"    solver iterations enqueued between host polls (>= 1)
- * "adj_wg_per_cu", "adj_min_nnz", "fwd_blocks_per_wave", "fwd_col16" and
- * "fwd_wg_per_cu" are read when a dose matrix is created (its work
+ * "adj_wg_per_cu", "adj_min_nnz", "fwd_blocks_per_wave", "fwd_col16",
+ * "one_read" and "fwd_wg_per_cu" are read when a dose matrix is created (its work
  * partitions and layout);
  * "fwd_wg_per_cu" and "adj_wg_per_cu" also at launch.
  * Results are deterministic for given settings; the settings change only the
@@ -281,6 +288,12 @@ IMRT_API int imrt_dose_export_codes(const imrt_dose* dose, uint16_t* val_code, u
 /* The imrt_dtype D is stored in. */
 IMRT_API int imrt_dose_storage(const imrt_dose* dose, int32_t* storage);
 
+/* Entries of D's quad form (18 bytes each of float32 values, 10 of 16-bit
+ * codes, read once by a one-read pass) and the workgroups of its pass with one
+ * trial, each of which writes nb 8-byte column sums; both 0 when the matrix
+ * keeps the two separate passes (option "one_read").  Either may be NULL. */
+IMRT_API int imrt_dose_one_read(const imrt_dose* dose, int64_t* entries, int32_t* workgroups);
+
 /* d = D x (CSR, voxel-parallel).  x_dev: nb floats; d_dev: nv floats. */
 IMRT_API int imrt_dose_apply(const imrt_dose* dose, const float* x_dev, float* d_dev);
 /* y = D^T r (CSC, beamlet-parallel).  r_dev: nv floats; y_dev: nb floats. */
@@ -320,7 +333,8 @@ IMRT_API int imrt_gradient(imrt_plan* plan, const float* x_dev, float* g_dev, do
 
 /* Size of the per-device scratch of imrt_gradient_noalloc (bytes): the
  * residual (4 nv bytes) plus a few kilobytes of partial sums, so plans of up
- * to about 4 million voxels. */
+ * to about 4 million voxels.  (A one-read pass keeps no residual but its
+ * workgroups' column sums there, which its partition keeps within it.) */
 #define IMRT_NOALLOC_SCRATCH_BYTES (16u << 20)
 
 /* imrt_gradient for callers that cannot allocate device memory (code under

@@ -1213,6 +1213,13 @@ int imrt_dose_storage(const imrt_dose* D, int32_t* storage) {
   return IMRT_OK;
 }
 
+int imrt_dose_one_read(const imrt_dose* D, int64_t* entries, int32_t* workgroups) {
+  if (!D) return set_error(IMRT_EINVAL, "dose is NULL");
+  if (entries) *entries = D->q_waves > 0 ? D->nent : 0;
+  if (workgroups) *workgroups = D->q_waves > 0 ? quad_grid(D, 1) : 0;
+  return IMRT_OK;
+}
+
 int imrt_dose_apply(const imrt_dose* D, const float* x_dev, float* d_dev) {
   if (!D || !x_dev || !d_dev) return set_error(IMRT_EINVAL, "dose, x or d is NULL");
   int rc = use_device(D->ctx);

@@ -93,6 +93,7 @@ SIGNATURES = {
     "imrt_dose_export": (C.c_int, [_vp, _i32p, _i32p, _f32p, _i32p, _i32p, _f32p, _u8p]),
     "imrt_dose_export_codes": (C.c_int, [_vp, _u16p, _u16p, _f32p]),
     "imrt_dose_storage": (C.c_int, [_vp, _i32p]),
+    "imrt_dose_one_read": (C.c_int, [_vp, C.POINTER(C.c_int64), _i32p]),
     "imrt_dose_apply": (C.c_int, [_vp, _vp, _vp]),
     "imrt_dose_apply_transpose": (C.c_int, [_vp, _vp, _vp]),
     "imrt_dose_destroy": (C.c_int, [_vp]),
@@ -239,6 +240,13 @@ def imrt_dose_storage(dose) -> int:
     out = C.c_int32()
     _check(load().imrt_dose_storage(dose, C.byref(out)), "imrt_dose_storage")
     return out.value
+
+
+def imrt_dose_one_read(dose):
+    """(entries of the quad form, workgroups of its pass); (0, 0) without it."""
+    entries, wgs = C.c_int64(), C.c_int32()
+    _check(load().imrt_dose_one_read(dose, C.byref(entries), C.byref(wgs)), "imrt_dose_one_read")
+    return entries.value, wgs.value
 
 
 def imrt_solve_batch(n: int, plans, params, x_devs, results):
