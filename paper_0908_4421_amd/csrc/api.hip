@@ -674,17 +674,38 @@ void set_quad_dose(FwdArgs& a, const imrt_dose* D, float* d) {
   a.nzero = D->nzero;
 }
 
-// The plan's penalties and the bound |r| <= pen_w (|z| + pen_T) on the
-// residual they give: both sides of a voxel may be active.
+// The plan's penalties and the bound |r| <= pen_w |z| + pen_r0 on the
+// residuals they give.  With weights w_u, w_o >= 0 a voxel's residual is at
+// most w_u (|z| + max(T_under, 0)) + w_o (|z| + max(-T_over, 0)): an upper
+// threshold, however large ("no limit"), and a lower one below zero add
+// nothing, nor does any threshold of a side without weight, of a structure
+// without voxels, or that per-voxel targets replace.
 void set_quad_penalties(FwdArgs& a, const imrt_plan* P) {
   set_plan_penalties(a, P);
-  double w = 0.0, T = 0.0;
-  for (const PenaltyDev& t : P->table_host) {
-    w = std::max(w, std::max(t.w_u, t.w_o));
-    T = std::max(T, std::max(std::fabs(t.T_u), std::fabs(t.T_o)));
+  const bool targets = !P->Tu_host.empty();
+  double w = 0.0, r0 = 0.0;
+  for (int s = 0; s < P->nstruct; ++s) {
+    if (!P->present[s]) continue;
+    const PenaltyDev& t = P->table_host[s];
+    const double Tu = targets ? P->Tu_top[s] : t.T_u, To = targets ? P->To_low[s] : t.T_o;
+    w = std::max(w, t.w_u + t.w_o);
+    r0 = std::max(r0, (t.w_u > 0.0 ? t.w_u * std::max(Tu, 0.0) : 0.0) + (t.w_o > 0.0 ? t.w_o * std::max(-To, 0.0) : 0.0));
   }
-  a.pen_w = 2.0 * w;
-  a.pen_T = std::max(T, P->T_vox);
+  a.pen_w = w;
+  a.pen_r0 = r0;
+}
+
+// The range of the per-voxel targets over each structure's voxels, once both
+// are set.
+void range_targets(imrt_plan* P) {
+  if (P->Tu_host.empty() || P->sid_host.empty()) return;
+  std::fill_n(P->Tu_top, kMaxStruct, -INFINITY);
+  std::fill_n(P->To_low, kMaxStruct, INFINITY);
+  for (size_t j = 0; j < P->sid_host.size(); ++j) {
+    double &top = P->Tu_top[P->sid_host[j]], &low = P->To_low[P->sid_host[j]];
+    top = std::max(top, static_cast<double>(P->Tu_host[j]));
+    low = std::min(low, static_cast<double>(P->To_host[j]));
+  }
 }
 
 // Step (or reduction) over the column sums of a pass of nt trials.
@@ -1321,6 +1342,8 @@ int imrt_set_structures(imrt_plan* P, const uint8_t* voxel_struct, int32_t nstru
   }
   IMRT_HIP(hipMemcpy(P->sid, ids.data(), D->nv, hipMemcpyHostToDevice));
   P->sid_host.swap(ids);
+  std::copy(present.begin(), present.end(), P->present);
+  range_targets(P);
   for (auto& K : P->skip) K.epoch = K.hist_epoch = -1;
   P->nstruct = nstruct;
   P->have_struct = true;
@@ -1367,7 +1390,6 @@ int imrt_set_voxel_targets(imrt_plan* P, const float* T_under, const float* T_ov
     dev_free(P->To_vox);
     P->Tu_host.clear();
     P->To_host.clear();
-    P->T_vox = 0.0;
     for (auto& K : P->skip) K.epoch = -1;
     return IMRT_OK;
   }
@@ -1396,9 +1418,7 @@ int imrt_set_voxel_targets(imrt_plan* P, const float* T_under, const float* T_ov
   IMRT_HIP(hipMemcpy(P->To_vox, T_over, sizeof(float) * nv, hipMemcpyHostToDevice));
   P->Tu_host.assign(T_under, T_under + nv);
   P->To_host.assign(T_over, T_over + nv);
-  P->T_vox = 0.0;
-  for (int j = 0; j < nv; ++j)
-    P->T_vox = std::max(P->T_vox, static_cast<double>(std::max(std::fabs(T_under[j]), std::fabs(T_over[j]))));
+  range_targets(P);
   for (auto& K : P->skip) K.epoch = -1;
   return IMRT_OK;
 }

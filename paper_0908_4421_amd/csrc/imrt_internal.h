@@ -206,7 +206,7 @@ struct FwdArgs {
   const void* q_val;
   int32_t q_nblocks, q_kmax; // blocks, and of each wave (absent ones at its end)
   double q_rowsum, q_colsum; // largest row and column sum of D (16-bit storage: of the codes)
-  double pen_w, pen_T;       // |r| <= pen_w (|z| + pen_T)
+  double pen_w, pen_r0;      // |r| <= pen_w |z| + pen_r0
   double* q_unit;            // per trial: unit of the column sums (0: they are float64)
   unsigned long long* q_acc; // [workgroup][trial][nb] column sums
   double* q_steps;           // [trial][step_grid] step norms of the trials, then the last step's, copied there
@@ -418,7 +418,9 @@ struct imrt_plan {
   std::vector<uint8_t> sid_host;
   std::vector<imrt::PenaltyDev> table_host;
   std::vector<float> Tu_host, To_host;
-  double T_vox = 0.0;                     // largest |target| of them
+  bool present[imrt::kMaxStruct] = {};    // structures with voxels
+  double Tu_top[imrt::kMaxStruct] = {};   // per structure: highest T_under and lowest T_over of its voxels'
+  double To_low[imrt::kMaxStruct] = {};   // targets, where there are any
   struct Skip {
     double G = 0.0;
     int64_t epoch = -1;                   // dose partition the constant was computed for (-1: stale)

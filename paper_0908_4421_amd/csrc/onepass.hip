@@ -484,7 +484,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
     for (int k = 0; k < WAVES; ++k) b = max(b, mx[q][k]);
     const FwdArgs& aq = P(q);
     const double zmax = a.q_rowsum * static_cast<double>(__uint_as_float(b));
-    const double R = PEN ? aq.pen_w * (zmax + aq.pen_T) : zmax;
+    const double R = PEN ? aq.pen_w * zmax + aq.pen_r0 : zmax;
     wild[q] = uniform(R < 1e38 && zmax < 1e38 ? 0 : 1) != 0;
     any_wild = any_wild || wild[q];
     const double bound = fmax(R * a.q_colsum, 1e-200);
