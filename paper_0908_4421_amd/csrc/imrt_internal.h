@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "imrt.h"
+#include "quad_layout.h"
 
 namespace imrt {
 
@@ -64,6 +65,7 @@ struct SolverState {
 struct PenaltyDev {
   double T_u, T_o, w_u, w_o;
 };
+static_assert(sizeof(PenaltyDev) == kPenaltyBytes, "penalty tables in LDS");
 
 // Layout-compatible with imrt_trace_entry.
 struct TraceDev {
@@ -133,21 +135,9 @@ __host__ __device__ inline int quad_part(int n, int full, int before, int k) {
 constexpr int kQuadPad = 512;          // entries past the last one that loads may name
 constexpr int kQuadFirst = 1 << 12, kQuadDose = 1 << 13, kQuadFinish = 1 << 14, kQuadAdjoint = 1 << 15;
 __host__ __device__ inline int quad_log2(int flags) { return (flags >> 8) & 0xF; }
-// LDS stride of a staged vector or of a trial's column sums (slot 0: no column)
-__host__ __device__ inline int quad_stride(int nb) { return (nb + 1 + 3) & ~3; }
 constexpr int kStepCols = 16;          // columns of one step workgroup
 constexpr int kStepThreads = 512;
 __host__ __device__ inline int step_grid(int nb) { return (nb + kStepCols - 1) / kStepCols; }
-enum QuadMode : int32_t {
-  QM_SOLVE = 0,   // trials of a solve, with their gradients
-  QM_EVAL = 1,    // objective of x, dose optional
-  QM_GRAD = 2,    // objective and gradient of x
-  QM_PLAIN = 3,   // dose of x, partials of sum d^2
-  QM_POWER = 4,   // D^T D of w / ||w||, partials of sum d^2
-  QM_WHOLE = 5    // a small plan's step and pass in one
-};
-constexpr bool quad_grad(int mode) { return mode != QM_EVAL && mode != QM_PLAIN; }
-
 // A small plan's iteration state, of which a launch reads one copy and writes
 // the other: iterate, gradient and trial, step norms (per 16 columns), unit,
 // objective partials and column sums of its pass, solver state.
@@ -500,7 +490,6 @@ int launch_permute(const imrt_ctx* ctx, const float* in, const int32_t* vox, int
 int store16(imrt_dose* D, int storage);
 
 // one-read pass (onepass.hip)
-size_t quad_lds_bytes(int nb, int ntrials, int nstruct, int mode);
 int launch_quad(const imrt_ctx* ctx, const FwdArgs& a, int ntrials, int waves, int grid, hipEvent_t before = nullptr,
                 hipEvent_t after = nullptr);
 int launch_whole(const imrt_ctx* ctx, const FwdArgs& a, const WholeArgs& w, int grid);

@@ -235,6 +235,7 @@ __device__ __forceinline__ Whole whole_step(const FwdArgs& a, const WholeArgs& W
   __shared__ double lam_sh;
   __shared__ int ctl[2];   // phase, accepted
   __shared__ unsigned long long sh[THREADS];
+  static_assert(sizeof(lam_sh) + sizeof(ctl) + sizeof(sh) + kQuadFixedLds - 32 <= kWholeFixedLds, "counted by quad_fits");
   const int tid = threadIdx.x, lane = tid & 63, nb = a.nb, sg = step_grid(nb);
   // Thread (first, c) adds column c's sums of workgroups first, first + groups,
   // ...: a thread to a column leaves most threads idle and takes several
@@ -340,6 +341,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
   __shared__ double red[WAVES];
   __shared__ uint32_t mx[NT][WAVES];
   __shared__ double gsum[NT][WAVES];
+  static_assert(sizeof(red) + sizeof(mx) + sizeof(gsum) <= kQuadFixedLds, "counted by quad_fits");
   const int tid = threadIdx.x, wv = uniform(tid >> 6), lane = tid & 63;
 
   // this wave's blocks: heads (lane i: block i) and the first two blocks' records
@@ -1059,16 +1061,11 @@ int launch_quad_batch_st(const FwdArgs* args, const int32_t* slots, int nslots, 
 
 }  // namespace
 
-size_t quad_lds_bytes(int nb, int ntrials, int nstruct, int mode) {
-  const size_t n = static_cast<size_t>(ntrials) * quad_stride(nb);
-  return static_cast<size_t>(nstruct) * sizeof(PenaltyDev) + n * (quad_grad(mode) ? 12 : 4);
-}
-
 int launch_quad(const imrt_ctx* ctx, const FwdArgs& a, int ntrials, int waves, int grid, hipEvent_t before,
                 hipEvent_t after) {
   clear_stale_error();
   const size_t lds = quad_lds_bytes(a.nb, ntrials, a.nstruct, a.mode);
-  if (lds > ctx->max_lds) return set_error(IMRT_EUNSUPPORTED, "one-read pass: LDS budget exceeded");
+  if (!quad_fits(ctx->max_lds, lds)) return set_error(IMRT_EUNSUPPORTED, "one-read pass: LDS budget exceeded");
   if (a.mode != QM_SOLVE && ntrials != 1) return set_error(IMRT_EINVAL, "evaluation passes take one trial");
   int rc;
   switch (a.storage) {
@@ -1083,7 +1080,7 @@ int launch_quad(const imrt_ctx* ctx, const FwdArgs& a, int ntrials, int waves, i
 int launch_quad_batch(const imrt_ctx* ctx, const FwdArgs* args, const int32_t* slots, int nslots, int ntrials,
                       int storage, int waves, size_t lds, int stream_cp) {
   if (nslots <= 0) return IMRT_OK;
-  if (lds > ctx->max_lds) return set_error(IMRT_EUNSUPPORTED, "batched one-read pass: LDS budget exceeded");
+  if (!quad_fits(ctx->max_lds, lds)) return set_error(IMRT_EUNSUPPORTED, "batched one-read pass: LDS budget exceeded");
   hipStream_t s = ctx->stream;
   int rc;
   switch (storage) {
@@ -1108,7 +1105,7 @@ int launch_quad_shared(const imrt_ctx* ctx, const FwdArgs* args, const int32_t* 
                        const int32_t* slots, int nslots, int storage, int nb, int nstruct) {
   if (nslots <= 0) return IMRT_OK;
   const size_t lds = quad_lds_bytes(nb, group_k, group_k * nstruct, QM_SOLVE);
-  if (lds > ctx->max_lds) return set_error(IMRT_EUNSUPPORTED, "shared one-read pass: LDS budget exceeded");
+  if (!quad_fits(ctx->max_lds, lds)) return set_error(IMRT_EUNSUPPORTED, "shared one-read pass: LDS budget exceeded");
   if (group_k != 2 && group_k != 4) return set_error(IMRT_EINVAL, "shared-matrix groups hold 2 or 4 solves");
   const dim3 gd(nslots), bd(8 * 64);
   hipStream_t s = ctx->stream;
@@ -1128,7 +1125,7 @@ int launch_quad_shared(const imrt_ctx* ctx, const FwdArgs* args, const int32_t* 
 int launch_whole(const imrt_ctx* ctx, const FwdArgs& a, const WholeArgs& w, int grid) {
   clear_stale_error();
   const size_t lds = quad_lds_bytes(a.nb, 1, a.nstruct, QM_SOLVE);
-  if (lds > ctx->max_lds) return set_error(IMRT_EUNSUPPORTED, "one-read pass: LDS budget exceeded");
+  if (!quad_fits(ctx->max_lds, lds, QM_WHOLE)) return set_error(IMRT_EUNSUPPORTED, "one-read pass: LDS budget exceeded");
   if (a.nb > 16 * 64) return set_error(IMRT_EINVAL, "internal: more columns than threads");
   const dim3 gd(grid), bd(16 * 64);
   hipStream_t s = ctx->stream;

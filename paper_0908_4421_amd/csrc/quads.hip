@@ -177,7 +177,7 @@ int lanes_for(int n, int storage) {
 // Whether a pass of nt trials over D is the one-read pass: the matrix keeps
 // its quad form, and the trials with their column sums fit LDS.
 bool one_read(const imrt_ctx* C, const imrt_dose* D, int nt, int nstruct) {
-  return D->q_waves > 0 && C->tune.fwd_wave != 0 && quad_lds_bytes(D->nb, nt, nstruct, QM_SOLVE) <= C->max_lds;
+  return D->q_waves > 0 && C->tune.fwd_wave != 0 && quad_fits(C->max_lds, quad_lds_bytes(D->nb, nt, nstruct, QM_SOLVE));
 }
 
 int quad_grid(const imrt_dose* D, int nt) { return D->q_waves / forward_waves(nt, D->fwd_waves); }
@@ -188,7 +188,7 @@ int64_t quad_bytes(const imrt_dose* D) { return D->nent * (D->storage == ST_F32 
 int build_quads(imrt_dose* D) {
   if (!D->ctx->tune.one_read || D->nb > 8191 || D->nnz == 0 || (D->storage == ST_F32 && D->fwd_st != ST_F32C16))
     return IMRT_OK;
-  if (quad_lds_bytes(D->nb, 1, kMaxStruct, QM_SOLVE) > D->ctx->max_lds) return IMRT_OK;
+  if (!quad_fits(D->ctx->max_lds, quad_lds_bytes(D->nb, 1, kMaxStruct, QM_SOLVE))) return IMRT_OK;
   hipStream_t s = D->ctx->stream;
   const int nqa = (D->nv + 3) / 4;
   Scratch cnt, ord, sums;

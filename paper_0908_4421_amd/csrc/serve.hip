@@ -399,7 +399,8 @@ void worker_main(imrt_server* S) {
     // group.  Each group takes the matrix's adjoint grid of slots.  One-read
     // passes likewise, where the group's vectors and column sums fit LDS.
     size_t most = kShareMax;
-    while (most > 1 && quad_lds_bytes(qnb, static_cast<int>(most), static_cast<int>(most) * qns, QM_SOLVE) > C->max_lds)
+    while (most > 1 &&
+           !quad_fits(C->max_lds, quad_lds_bytes(qnb, static_cast<int>(most), static_cast<int>(most) * qns, QM_SOLVE)))
       most /= 2;
     int gk[2];
     size_t ngroups = 0, nshared = 0;
