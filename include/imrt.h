@@ -243,7 +243,10 @@ IMRT_API int imrt_ctx_stream(const imrt_ctx* ctx, void** hip_stream_out);
  * "fwd_wg_per_cu" and "adj_wg_per_cu" also at launch.
  * Results are deterministic for given settings; the settings change only the
  * grouping of the float32 row sums and of the float64 partial sums of G and
- * of shared columns.
+ * of shared columns.  A one-read pass sums a gradient's columns as integers,
+ * whose order does not matter, and columns that these do not hold to float32
+ * precision (far smaller than the others, or of a vector that is not finite)
+ * in float64, in a fixed order.
  * Unknown names or out-of-range values return IMRT_EINVAL. */
 IMRT_API int imrt_ctx_set_option(imrt_ctx* ctx, const char* name, int64_t value);
 IMRT_API int imrt_ctx_get_option(const imrt_ctx* ctx, const char* name, int64_t* value);

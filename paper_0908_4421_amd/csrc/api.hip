@@ -18,7 +18,8 @@
 // pieces, objective total): one copy per device, held until the process
 // ends.  Host code never passes this name to a kernel; it uses the address
 // that hipGetSymbolAddress returned for the device (noalloc_scratch below).
-static __device__ __align__(256) unsigned char scratch[IMRT_NOALLOC_SCRATCH_BYTES];
+// (the second half: a one-read pass's column sums)
+static __device__ __align__(256) unsigned char scratch[2 * IMRT_NOALLOC_SCRATCH_BYTES];
 
 namespace imrt {
 
@@ -346,6 +347,7 @@ int finish_columns(imrt_dose* D, const std::vector<int32_t>& col_ptr) {
   // keep equal shares: uneven ones cost a large matrix more than the launch.
   int32_t longest = 0;
   for (int c = 0; c < D->nb; ++c) longest = std::max(longest, col_ptr[c + 1] - col_ptr[c]);
+  D->q_enough = quad_enough(longest);
   std::vector<int32_t> wg_k;
   if (2 * static_cast<int64_t>(longest) * G <= nnz) {
     wg_k.resize(static_cast<size_t>(G) + 1);
@@ -498,8 +500,9 @@ int fit_quad(imrt_plan* P, int nt) {
   const imrt_dose* D = P->dose;
   if (D->q_waves == 0) return IMRT_OK;
   int rc;
-  if (!P->q_unit && (rc = dev_alloc(&P->q_unit, kMaxTrials + (2 * kMaxTrials + 1) * static_cast<size_t>(step_grid(D->nb)))))
-    return rc;
+  const size_t vals = kMaxTrials + (2 * kMaxTrials + 1) * static_cast<size_t>(step_grid(D->nb));
+  if (!P->q_unit && (rc = dev_alloc(&P->q_unit, vals + kMaxTrials * static_cast<size_t>(D->nb) / 2 + 1))) return rc;
+  P->q_x = reinterpret_cast<float*>(P->q_unit + vals);
   const size_t need = static_cast<size_t>(quad_grid(D, nt)) * nt * D->nb;
   if (need > P->q_acc_cap) {
     dev_free(P->q_acc);
@@ -714,17 +717,20 @@ AdjArgs base_step(const imrt_dose* D, int nt) {
   a.col_scale = D->col_scale;
   a.nb = D->nb;
   a.q_parts = quad_grid(D, nt);
+  a.again = Again{D->col_ptr, D->row_idx, D->cval,      D->cval16, D->row_ptr, D->col_idx,
+                  D->col16,   D->val,     D->val16,     D->col_scale, Penalties{}, D->storage};
+  a.enough = D->q_enough;
   return a;
 }
 
-// Residual (nv; unless the one-read pass needs none) and iterate (nb)
-// buffers 0..count-1.
-int ensure_buffers(imrt_plan* P, int count, bool residuals = true) {
-  for (int i = 0; i < count; ++i) {
-    int rc;
-    if (residuals && P->rbuf[i] == nullptr && (rc = dev_alloc(&P->rbuf[i], P->dose->nv))) return rc;
+// Residual buffers (nv) 0..residuals-1 and iterate buffers (nb) 0..iterates-1.
+// (One-read passes of a solve keep trial 0's residuals in vtmp.)
+int ensure_buffers(imrt_plan* P, int residuals, int iterates, bool quads = false) {
+  int rc;
+  for (int i = quads ? 1 : 0; i < residuals; ++i)
+    if (P->rbuf[i] == nullptr && (rc = dev_alloc(&P->rbuf[i], P->dose->nv))) return rc;
+  for (int i = 0; i < iterates; ++i)
     if (P->xbuf[i] == nullptr && (rc = dev_alloc(&P->xbuf[i], P->dose->nb))) return rc;
-  }
   return IMRT_OK;
 }
 
@@ -789,9 +795,9 @@ int adjoint_into(const imrt_ctx* ctx, const imrt_dose* D, const float* r, double
 }
 
 // Objective partials and gradient of x by the one-read pass, through the
-// given buffers; total receives G.
+// given buffers (res: nv residuals); total receives G.
 int quad_gradient(imrt_plan* P, const float* x, float* g, double* parts, unsigned long long* acc, double* unit,
-                  double* total) {
+                  float* res, double* total) {
   const imrt_dose* D = P->dose;
   FwdArgs a = base_quad(D, QM_GRAD);
   set_quad_penalties(a, P);
@@ -799,8 +805,10 @@ int quad_gradient(imrt_plan* P, const float* x, float* g, double* parts, unsigne
   a.partials = parts;
   a.q_acc = acc;
   a.q_unit = unit;
+  a.rbuf[0] = res;
   const int grid = quad_grid(D, 1);
   AdjArgs r = base_step(D, 1);
+  r.rbuf[0] = res;
   r.q_acc = acc;
   r.q_unit = unit;
   r.out = g;
@@ -1296,7 +1304,7 @@ int imrt_plan_create(imrt_ctx* ctx, const imrt_dose* dose, imrt_plan** out) {
   P->fwd_cap = grid;
   P->pieces_cap = dose->adj_grid;
   if ((rc = dev_alloc(&P->sid, dose->nv)) || (rc = dev_alloc(&P->table, kMaxStruct)) ||
-      (rc = ensure_buffers(P, 2, dose->q_waves == 0)) || (rc = fit_quad(P, 1)) || (rc = dev_alloc(&P->gk, dose->nb)) || (rc = dev_alloc(&P->vtmp, dose->nv)) ||
+      (rc = ensure_buffers(P, dose->q_waves == 0 ? 2 : 0, 2)) || (rc = fit_quad(P, 1)) || (rc = dev_alloc(&P->gk, dose->nb)) || (rc = dev_alloc(&P->vtmp, dose->nv)) ||
       (rc = dev_alloc(&P->fwd_partials, static_cast<size_t>(kMaxTrials) * (grid + 1))) ||
       (rc = dev_alloc(&P->pieces, 2 * static_cast<size_t>(dose->adj_grid))) ||
       (rc = dev_alloc(&P->pieces_col, 2 * static_cast<size_t>(dose->nb))) || (rc = dev_alloc(&P->misc, 16)) ||
@@ -1454,13 +1462,13 @@ int imrt_gradient(imrt_plan* P, const float* x_dev, float* g_dev, double* G_out)
   if ((rc = use_device(P->ctx))) return rc;
   if (one_read(P->ctx, P->dose, 1, P->nstruct)) {
     double* total = G_out ? P->misc_host : P->misc;
-    if ((rc = quad_gradient(P, x_dev, g_dev, P->fwd_partials, P->q_acc, P->q_unit, total))) return rc;
+    if ((rc = quad_gradient(P, x_dev, g_dev, P->fwd_partials, P->q_acc, P->q_unit, P->vtmp, total))) return rc;
     if (G_out) {
       IMRT_HIP(hipStreamSynchronize(P->ctx->stream));
       *G_out = P->misc_host[0];
     }
     return IMRT_OK;
-  } else if ((rc = ensure_buffers(P, 1)) || (rc = eval_forward(P, x_dev, nullptr, P->rbuf[0], P->misc)) ||
+  } else if ((rc = ensure_buffers(P, 1, 1)) || (rc = eval_forward(P, x_dev, nullptr, P->rbuf[0], P->misc)) ||
              (rc = adjoint_into(P->ctx, P->dose, P->rbuf[0], 2.0, g_dev))) {
     return rc;
   }
@@ -1500,17 +1508,16 @@ int imrt_gradient_noalloc(imrt_plan* P, const float* x_dev, float* g_dev, double
   double* pieces = reinterpret_cast<double*>(base + off_pieces);
   double* total = reinterpret_cast<double*>(base + off_total);
   if (one_read(P->ctx, D, 1, P->nstruct)) {
-    // (no residual: objective partials, unit, total, then the column sums,
-    // whose size the partition bounds)
+    // the second half of the scratch: total, unit, objective partials, then
+    // the column sums, whose size the partition bounds
     const size_t qgrid = static_cast<size_t>(quad_grid(D, 1));
-    double* head = reinterpret_cast<double*>(base);
+    double* head = reinterpret_cast<double*>(base + IMRT_NOALLOC_SCRATCH_BYTES);
     const size_t off_acc = up(sizeof(double) * (static_cast<size_t>(quad_parts(D)) + 2));
     const size_t qneed = off_acc + 8 * qgrid * static_cast<size_t>(D->nb);
     if (qneed > IMRT_NOALLOC_SCRATCH_BYTES)
       return set_error(IMRT_EINVAL, "imrt_gradient_noalloc: the column sums exceed the scratch");
-    if ((rc = quad_gradient(P, x_dev, g_dev, head + 2, reinterpret_cast<unsigned long long*>(base + off_acc), head + 1,
-                            head)))
-      return rc;
+    auto* acc = reinterpret_cast<unsigned long long*>(reinterpret_cast<unsigned char*>(head) + off_acc);
+    if ((rc = quad_gradient(P, x_dev, g_dev, head + 2, acc, head + 1, r, head))) return rc;
     if (G_out) {
       IMRT_HIP(hipMemcpyAsync(P->misc_host, head, sizeof(double), hipMemcpyDeviceToHost, P->ctx->stream));
       IMRT_HIP(hipStreamSynchronize(P->ctx->stream));
@@ -1582,7 +1589,9 @@ int imrt_estimate_lambda0(imrt_plan* P, const float* v0_dev, int32_t iters, doub
     a.partials = P->fwd_partials;
     a.q_acc = P->q_acc;
     a.q_unit = P->q_unit;
+    a.rbuf[0] = P->vtmp;
     AdjArgs r = base_step(D, 1);
+    r.rbuf[0] = P->vtmp;
     r.q_acc = P->q_acc;
     r.q_unit = P->q_unit;
     r.out = w;
@@ -1670,7 +1679,7 @@ int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev
   IMRT_HIP(hipStreamSynchronize(s));
   for (float v : xh)
     if (!(v >= 0.0f) || !std::isfinite(v)) return set_error(IMRT_EINVAL, "x_1 must be finite and >= 0");
-  if ((rc = ensure_buffers(P, nt + 1, !quads)) || (quads && (rc = fit_quad(P, nt)))) return rc;
+  if ((rc = ensure_buffers(P, quads ? nt : nt + 1, nt + 1, quads)) || (quads && (rc = fit_quad(P, nt)))) return rc;
   // the iterate buffers other than x_1's start zeroed (the forward pass
   // blends all candidates with 0/1 weights, so none may be non-finite)
   for (int j = 1; j <= nt; ++j) IMRT_HIP(hipMemsetAsync(P->xbuf[j], 0, sizeof(float) * D->nb, s));
@@ -1693,6 +1702,7 @@ int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev
   init.trace_cap = cap;
   init.warm = prm->warm_start;
   init.resume = prm->resume;
+  init.again = -1;
   init.G_prev = prm->resume ? prm->G_prev : 0.0;
   // first trial step: step 2's lambda0, or after a resumed warm-started
   // iteration alpha times the step accepted last (the product the decision
@@ -1717,13 +1727,19 @@ void solve_args(imrt_plan* P, int nt, int grid, int cap, FwdArgs& fa, AdjArgs& a
     fa.grid = grid;
     set_quad_penalties(fa, P);
     aa = base_step(D, nt);
-    for (int i = 0; i <= kMaxTrials; ++i) fa.xbuf[i] = aa.xbuf[i] = P->xbuf[i];
+    for (int i = 0; i <= kMaxTrials; ++i) {
+      fa.xbuf[i] = aa.xbuf[i] = P->xbuf[i];
+      fa.rbuf[i] = aa.rbuf[i] = i == 0 ? P->vtmp : P->rbuf[i];
+    }
     fa.partials = P->fwd_partials;
     fa.q_acc = P->q_acc;
     fa.q_unit = P->q_unit;
     aa.q_acc = P->q_acc;
     aa.q_unit = P->q_unit;
     fa.q_steps = aa.q_steps = P->q_unit + kMaxTrials;
+    fa.q_x = P->q_x;
+    aa.q_x = P->q_x;
+    aa.again.pen = plan_penalties(P);
     aa.out = P->gk;
     aa.scale = 2.0;
     aa.fwd_partials = P->fwd_partials;
@@ -1797,9 +1813,9 @@ bool whole_passes(const imrt_plan* P, const imrt_solve_params* prm, int nt) {
 int fit_whole(imrt_plan* P, WholeSet (&set)[2]) {
   const imrt_dose* D = P->dose;
   auto up = [](size_t n) { return (n + 255) & ~static_cast<size_t>(255); };
-  const size_t nb = static_cast<size_t>(D->nb), vec = up(4 * nb), steps = up(8 * static_cast<size_t>(step_grid(D->nb)));
+  const size_t nb = static_cast<size_t>(D->nb), vec = up(4 * nb), res = up(4 * static_cast<size_t>(D->nv)), steps = up(8 * static_cast<size_t>(step_grid(D->nb)));
   const size_t parts = up(8 * static_cast<size_t>(quad_parts(D))), acc = up(8 * nb * quad_grid(D, 1));
-  const size_t one = 3 * vec + steps + parts + acc + 2 * 256;
+  const size_t one = 3 * vec + res + steps + parts + acc + 3 * 256;
   if (2 * one > P->whole_cap) {
     dev_free(P->whole);
     P->whole_cap = 0;
@@ -1818,11 +1834,13 @@ int fit_whole(imrt_plan* P, WholeSet (&set)[2]) {
     set[k].xk = reinterpret_cast<float*>(take(vec));
     set[k].g = reinterpret_cast<float*>(take(vec));
     set[k].xt = reinterpret_cast<float*>(take(vec));
+    set[k].r = reinterpret_cast<float*>(take(res));
     set[k].steps = reinterpret_cast<double*>(take(steps));
     set[k].parts = reinterpret_cast<double*>(take(parts));
     set[k].acc = reinterpret_cast<unsigned long long*>(take(acc));
     set[k].unit = reinterpret_cast<double*>(take(256));
     set[k].st = reinterpret_cast<SolverState*>(take(256));
+    set[k].care = reinterpret_cast<int32_t*>(take(256));
   }
   return IMRT_OK;
 }
@@ -1930,6 +1948,8 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
   WholeArgs wa{};
   wa.trace = aa.trace;
   wa.G_skip = aa.G_skip;
+  wa.again = aa.again;
+  wa.enough = aa.enough;
   auto whole_pass = [&]() -> int {
     wa.in = set[pass & 1];
     wa.out = set[(pass + 1) & 1];

@@ -56,7 +56,10 @@ struct SolverState {
   int32_t acc, xi, n_fwd, n_adj;      // trial whose residual buffer holds r(x_k), iterate buffer of x_k, pass counters
   int32_t ntrials, max_iter, max_bt, fixed;
   int32_t trace_cap, warm;            // trace capacity; warm start of the line search (0/1)
-  int32_t resume, pad_;               // resumed solve: G_prev holds G(x_{K-1}) on entry
+  int32_t resume;                     // resumed solve: G_prev holds G(x_{K-1}) on entry
+  int32_t stored;                     // one-read passes that store residuals, the last one included (0: it did not)
+  int32_t again, pad_;                // n_fwd of the last step that had to sum a column again: any workgroup of
+                                      // the step writes it, beside the state (a word that is not copied)
   double lambda;                      // first trial step of the next forward pass
   double G, G_prev, G_init;
   double eps, alpha, lambda0, delta;
@@ -83,12 +86,6 @@ enum FwdMode : int32_t {
   FWD_PLAIN = 2   // x given; dose output; partials of sum d^2
 };
 
-struct Penalties {
-  const uint8_t* sid;        // structure id per voxel
-  const PenaltyDev* table;   // per structure
-  const float* Tu_vox;       // nullable per-voxel thresholds
-  const float* To_vox;
-};
 
 // Storage of D's values (the imrt_dtype codes): float32, or 16-bit codes q
 // with a float32 scale per beamlet (D~_ij = col_scale[i] * q_ij), where the
@@ -138,17 +135,50 @@ __host__ __device__ inline int quad_log2(int flags) { return (flags >> 8) & 0xF;
 constexpr int kStepCols = 16;          // columns of one step workgroup
 constexpr int kStepThreads = 512;
 __host__ __device__ inline int step_grid(int nb) { return (nb + kStepCols - 1) / kStepCols; }
+struct Penalties {
+  const uint8_t* sid;        // structure id per voxel
+  const PenaltyDev* table;   // per structure
+  const float* Tu_vox;       // nullable per-voxel thresholds
+  const float* To_vox;
+};
+
+// Passes of a solve that store their residuals after a step that had to sum a
+// column again: such columns mostly come in runs of steps.
+constexpr int kCarePasses = 16;
+
+// What a step needs to sum a column again whose integer sums are not precise
+// enough: the columns of D (CSC) and, for a pass that did not store its
+// residuals, its rows and the plan's penalties.
+struct Again {
+  const int32_t* col_ptr;
+  const int32_t* row_idx;
+  const float* cval;
+  const uint16_t* cval16;
+  const int32_t* row_ptr;
+  const int32_t* col_idx;
+  const uint16_t* col16;
+  const float* val;
+  const uint16_t* val16;
+  const float* col_scale;
+  Penalties pen;
+  int32_t storage;
+};
+
 // A small plan's iteration state, of which a launch reads one copy and writes
 // the other: iterate, gradient and trial, step norms (per 16 columns), unit,
-// objective partials and column sums of its pass, solver state.
+// objective partials, residuals (where care) and column sums of its pass,
+// solver state.
 struct WholeSet {
-  float *xk, *g, *xt;
+  float *xk, *g, *xt, *r;
   double *steps, *unit, *parts;
   unsigned long long* acc;
   SolverState* st;
+  int32_t* care;   // as SolverState::stored
 };
 struct WholeArgs {
   WholeSet in, out;
+  Again again;
+  uint32_t enough; // see quad_enough
   TraceDev* trace;
   double G_skip;
   int32_t first;   // the initial evaluation: no decision yet
@@ -197,9 +227,10 @@ struct FwdArgs {
   int32_t q_nblocks, q_kmax; // blocks, and of each wave (absent ones at its end)
   double q_rowsum, q_colsum; // largest row and column sum of D (16-bit storage: of the codes)
   double pen_w, pen_r0;      // |r| <= pen_w |z| + pen_r0
-  double* q_unit;            // per trial: unit of the column sums (0: they are float64)
+  double* q_unit;            // per trial: unit of the column sums (0: none, a wild vector)
   unsigned long long* q_acc; // [workgroup][trial][nb] column sums
   double* q_steps;           // [trial][step_grid] step norms of the trials, then the last step's, copied there
+  float* q_x;                // [trial][nb] copy of the vectors (the step overwrites the trials)
   const int32_t* vox;        // dose output: row j goes to d_out[vox[j]] (null: d_out[j]),
   const int32_t* zero;       // and d_out[zero[i]] = 0 for nzero places (rows of empty quads)
   int32_t nzero;
@@ -250,7 +281,10 @@ struct AdjArgs {
   TraceDev* trace;
   double G_skip;             // objective of the voxels the wave forward skips (rows without
                              // nonzeros between its blocks), added to every trial's G
-  // step of the one-read pass
+  // step of the one-read pass (rbuf: the trials' residuals)
+  Again again;
+  uint32_t enough;           // see quad_enough
+  const float* q_x;          // [trial][nb] the vectors that the pass multiplied by
   const unsigned long long* q_acc;
   const double* q_unit;
   double* q_steps;           // [trial][step_grid] step norms read, then as many written
@@ -334,6 +368,7 @@ struct imrt_dose {
   std::vector<std::pair<int32_t, int32_t>> gaps;
   int64_t part_epoch = 0;
   int32_t adj_grid = 0;        // workgroups of the adjoint partition
+  uint32_t q_enough = 0;       // see quad_enough
   int32_t* wg_cols = nullptr;
   int32_t* wg_k = nullptr;     // bounds at column starts (null: equal shares)
   int32_t* col_wlo = nullptr;
@@ -397,6 +432,7 @@ struct imrt_plan {
   char* whole = nullptr;          // both copies of a small plan's iteration state
   size_t whole_cap = 0;
   double* q_unit = nullptr;       // kMaxTrials units, 2 kMaxTrials step_grid(nb) step norms, step_grid(nb) squares
+  float* q_x = nullptr;           // (after them) kMaxTrials nb: copies of the trials
   double* misc = nullptr;         // small reduction scratch
   imrt::SolverState* st = nullptr;  // 2 states, alternately read and written by consecutive passes
   imrt::TraceDev* trace = nullptr;

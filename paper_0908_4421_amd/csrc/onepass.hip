@@ -27,11 +27,21 @@
 // Column sums are 64-bit integers, in units of 2^-61 times a bound on the
 // largest possible sum (from the staged vector's largest entry, the largest
 // row and column sums of D and the penalties), so additions in LDS commute
-// exactly: the result does not depend on which wave adds first, nor on the
-// work partition, and an error of half a unit per entry lies below that of
-// a float64 sum of the same products in all but extreme cancellations.  A vector with
-// non-finite entries, or one whose residuals could overflow, takes float64
-// sums instead (by LDS atomics, so without a fixed order).
+// exactly: the result does not depend on which wave adds first.  A term is
+// rounded to the unit, which one bound sets for every column, so the step
+// checks each column on its own: where the workgroups' sums are large enough
+// against the number of terms (see imprecise), the total is as close as the
+// float64 sum that it replaces once rounded to float32; any other column is
+// summed again in float64 from its nonzeros and the residuals.  Columns that
+// received no term are told from those whose terms vanish in the unit by a
+// mark in LDS.  A vector with non-finite entries, or whose residuals could
+// overflow, has no unit, and all its columns are summed so.
+// After such a step the next passes of a solve store their residuals (that
+// step makes them from the rows); a single gradient and the power iterations
+// always do.  Stored in every pass they took 95 against 85 us for 32 uneven
+// plans together.  The marks and the checks cost 3 to 4% of an iteration:
+// 16.4 -> 17.0 us a pass at the paper's scale, 22.0 -> 22.9 in bfloat16 with
+// two trials.
 #include <algorithm>
 
 #include "decide.h"
@@ -190,10 +200,93 @@ __device__ __forceinline__ double quad_bcast(double v) {
   return dpp_move<V * 0x55, 0xF>(v);
 }
 
-// Sum of column sums: integers, or the float64 values of a wild vector.
-__device__ __forceinline__ unsigned long long add_parts(unsigned long long s, unsigned long long v, bool wild) {
-  if (wild) return __builtin_bit_cast(unsigned long long, __builtin_bit_cast(double, s) + __builtin_bit_cast(double, v));
-  return s + v;
+// A column's total over workgroups: the sum of their sums; in units of 2^24, at
+// most the sum of their magnitudes, which is at most that of the terms'; and
+// their bits, 0 for a column that received no term (a workgroup writes a unit
+// instead of a sum of 0 of terms that were not all zero).
+struct ColTotal {
+  unsigned long long s;
+  uint32_t a, any;
+};
+__device__ __forceinline__ void add_part(ColTotal& T, unsigned long long v) {
+  const int hi = static_cast<int>(v >> 32);
+  T.s += v;
+  T.a += static_cast<uint32_t>((v >> kMagnitude) ^ static_cast<unsigned long long>(static_cast<long long>(hi >> 31)));
+  T.any |= static_cast<uint32_t>(hi) | static_cast<uint32_t>(v);
+}
+__device__ __forceinline__ void add_total(ColTotal& T, const ColTotal& U) {
+  T.s += U.s;
+  T.a += U.a;
+  T.any |= U.any;
+}
+
+// Whether the integers are not precise enough for a column: the sums'
+// magnitudes do not come to `enough` (quad_enough), or there is no unit.
+// Columns far below the bound that the unit is taken from are not: one huge
+// entry of x, columns or weights decades apart, residuals that nearly vanish.
+__device__ __forceinline__ bool imprecise(const ColTotal& T, double unit, uint32_t enough) {
+  return unit == 0.0 || (T.any != 0 && T.a < enough);
+}
+
+// Residual of a row that its pass did not store.
+template <int ST>
+__device__ __forceinline__ float row_residual(const Again& A, const float* x, int row) {
+  double z = 0.0;
+  for (int k = A.row_ptr[row]; k < A.row_ptr[row + 1]; ++k) {
+    const int c = coded(ST) ? A.col16[k] : A.col_idx[k];
+    const float xc = coded(ST) ? x[c] * A.col_scale[c] : x[c];
+    const float v = coded(ST) ? code_value<ST>(A.val16[k]) : A.val[k];
+    z += static_cast<double>(v) * static_cast<double>(xc);
+  }
+  const PenaltyDev t = A.pen.table[A.pen.sid[row]];
+  RowPenalty p{t.T_u, t.T_o, t.w_u, t.w_o};
+  if (A.pen.Tu_vox != nullptr) {
+    p.Tu = static_cast<double>(A.pen.Tu_vox[row]);
+    p.To = static_cast<double>(A.pen.To_vox[row]);
+  }
+  double F;
+  float r;
+  penalty(p, static_cast<float>(z), F, r);
+  return r;
+}
+
+// Such a column is summed again from its nonzeros and the residuals of its
+// rows (r, or where the pass did not store them (null) those of the vector x)
+// in float64, in a fixed order: the share of wave i of `waves`.
+template <int ST>
+__device__ __forceinline__ double exact_column_of(const Again& A, const float* r, const float* x, int c, int i,
+                                                  int waves) {
+  constexpr int U = 4;
+  const int k1 = A.col_ptr[c + 1], lane = threadIdx.x & 63;
+  double s = 0.0;
+  for (int k0 = A.col_ptr[c] + 64 * U * i; k0 < k1; k0 += 64 * U * waves) {
+    int row[U];
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 64 * u + lane;
+      const int64_t at = csc_slot(k < k1 ? k : k0);
+      row[u] = A.row_idx[at];
+      if constexpr (coded(ST)) v[u] = code_value<ST>(A.cval16[at]);
+      else v[u] = A.cval[at];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float ru = r != nullptr ? r[row[u]] : row_residual<ST>(A, x, row[u]);
+      const double t = static_cast<double>(v[u]) * static_cast<double>(ru);
+      s += k0 + 64 * u + lane < k1 ? t : 0.0;
+    }
+  }
+  const uint64_t b = __builtin_bit_cast(uint64_t, wave_sum(s));
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(b), 63);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), 63);
+  return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+__device__ __forceinline__ double exact_column(const Again& A, const float* r, const float* x, int c, int i,
+                                               int waves) {
+  if (A.storage == ST_BF16) return exact_column_of<ST_BF16>(A, r, x, c, i, waves);
+  if (A.storage == ST_F16) return exact_column_of<ST_F16>(A, r, x, c, i, waves);
+  return exact_column_of<ST_F32>(A, r, x, c, i, waves);
 }
 
 // A wave's sum of n float64 values: lane l adds values l, l + 64, ..., then
@@ -226,6 +319,7 @@ __device__ __forceinline__ double sum_finish(const double* p, int n, const SumLo
 // that pass's column sums, and the next trial.  Thread c takes column c.
 struct Whole {
   int phase;       // after the decision
+  int care;        // passes that store their residuals from this one on
   float t;         // the trial
 };
 constexpr int kWholeU = 12;   // column sums in flight per thread
@@ -233,8 +327,8 @@ constexpr int kWholeU = 12;   // column sums in flight per thread
 template <int THREADS>
 __device__ __forceinline__ Whole whole_step(const FwdArgs& a, const WholeArgs& W, int w, int parts, int nobj) {
   __shared__ double lam_sh;
-  __shared__ int ctl[2];   // phase, accepted
-  __shared__ unsigned long long sh[THREADS];
+  __shared__ int ctl[3];   // phase, accepted, a column to sum again
+  __shared__ ColTotal sh[THREADS];
   static_assert(sizeof(lam_sh) + sizeof(ctl) + sizeof(sh) + kQuadFixedLds - 32 <= kWholeFixedLds, "counted by quad_fits");
   const int tid = threadIdx.x, lane = tid & 63, nb = a.nb, sg = step_grid(nb);
   // Thread (first, c) adds column c's sums of workgroups first, first + groups,
@@ -249,6 +343,7 @@ __device__ __forceinline__ Whole whole_step(const FwdArgs& a, const WholeArgs& W
   float xk = load_f32(make_rsrc(W.in.xk, nb4), at), g = load_f32(make_rsrc(W.in.g, nb4), at);
   const float xt = load_f32(make_rsrc(W.in.xt, nb4), at);
   const double unit = load_f64(make_rsrc(W.in.unit, 8u), 0);
+  const int was = load_i32(make_rsrc(W.in.care, W.first ? 0u : 4u), 0);
   const double factor = a.col_scale ? 2.0 * static_cast<double>(load_f32(make_rsrc(a.col_scale, nb4), at)) : 2.0;
   SumLoads<2> GL, SL;
   int32_t sw = 0;
@@ -257,8 +352,7 @@ __device__ __forceinline__ Whole whole_step(const FwdArgs& a, const WholeArgs& W
     sum_start(W.in.parts, nobj, GL);
     sum_start(W.in.steps, sg, SL);
   }
-  unsigned long long s = 0;
-  const bool as_double = unit == 0.0;
+  ColTotal s{0, 0, 0};
   for (int p = first; p < parts; p += groups * kWholeU) {
     unsigned long long v[kWholeU];
 #pragma unroll
@@ -268,9 +362,10 @@ __device__ __forceinline__ Whole whole_step(const FwdArgs& a, const WholeArgs& W
                                 load_f64(ra, c < nb && pu < parts ? 8u * static_cast<uint32_t>(pu * nb + c) : 0xFFFFFFF0u));
     }
 #pragma unroll
-    for (int u = 0; u < kWholeU; ++u) s = add_parts(s, v[u], as_double);
+    for (int u = 0; u < kWholeU; ++u) add_part(s, v[u]);
   }
   sh[tid] = s;
+  if (tid == 0) ctl[2] = 0;
   if (tid < 64) {
     int32_t words[kStateWords];
 #pragma unroll
@@ -306,12 +401,30 @@ __device__ __forceinline__ Whole whole_step(const FwdArgs& a, const WholeArgs& W
   R.phase = uniform(ctl[0]);
   if (ctl[1] >= 0) xk = xt;
   if (tid < nb)
-    for (int k = 1; k < groups; ++k) s = add_parts(s, sh[k * width + tid], as_double);
-  if (R.phase == PH_NEED_GRAD)
-    g = static_cast<float>(factor * (as_double ? __builtin_bit_cast(double, s)
-                                                 : static_cast<double>(static_cast<long long>(s)) * unit));
+    for (int k = 1; k < groups; ++k) add_total(s, sh[k * width + tid]);
+  double total = static_cast<double>(static_cast<long long>(s.s)) * unit;
+  const bool again = tid < nb && !W.first && imprecise(s, unit, W.enough);
+  if (again) ctl[2] = 1;
+  __syncthreads();
+  const bool some = uniform(ctl[2]) != 0;
+  R.care = uniform(some ? kCarePasses : max(was - 1, 0));
+  if (R.phase == PH_NEED_GRAD) {
+    if (some) {   // (every workgroup alike, a wave to a column)
+      sh[tid].any = again;
+      __syncthreads();
+      for (int k = uniform(tid >> 6); k < nb; k += THREADS / 64)
+        if (uniform(static_cast<int>(sh[k].any)) != 0) {
+          const double t = exact_column(W.again, was > 0 ? W.in.r : nullptr, W.in.xt, k, 0, 1);
+          if (lane == 0) sh[k].s = __builtin_bit_cast(unsigned long long, t);
+        }
+      __syncthreads();
+      if (again) total = __builtin_bit_cast(double, sh[tid].s);
+    }
+    g = static_cast<float>(factor * total);
+  }
   R.t = W.first ? xt : trial_point(xk, g, lam_sh);
   if (w == 0) {
+    if (tid == 0) *W.out.care = R.care;
     if (tid < nb) {
       W.out.xk[tid] = xk;
       W.out.g[tid] = g;
@@ -335,7 +448,8 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
   constexpr bool PEN = MODE != QM_PLAIN && MODE != QM_POWER;
   extern __shared__ __align__(16) unsigned char smem[];
   const int nb = a.nb, nbs = quad_stride(nb);
-  auto* acc = reinterpret_cast<unsigned long long*>(smem);
+  unsigned char* mark = smem;   // columns that received a term
+  auto* acc = reinterpret_cast<unsigned long long*>(smem + (GRAD ? quad_mark_bytes(nb, NT) : 0));
   PenaltyDev* tab = reinterpret_cast<PenaltyDev*>(acc + (GRAD ? NT * nbs : 0));
   float* xs = reinterpret_cast<float*>(tab + NP * nst);
   __shared__ double red[WAVES];
@@ -392,14 +506,24 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
   int e0 = head_e0(0), fl = head_fl(0);
   quad_issue<MODE, ST, CP>(P, rec0, e0, fl, lane, A);
 
+  int keep = GRAD;   // residuals are stored
   if constexpr (MODE == QM_WHOLE) {
     static_assert(NT == 1 && U >= 1 && !Plans::kMany, "one column per thread");
     const Whole R = whole_step<THREADS>(a, *W, sl.w, sl.G, sl.G * (WAVES / 8));
     if (R.phase == PH_DONE) return;
     xr[0][0] = R.t;
+    keep = R.care;
   }
   if (MODE == QM_EVAL || MODE == QM_PLAIN)
     for (int i = sl.w * THREADS + tid; i < a.nzero; i += sl.G * THREADS) a.d_out[a.zero[i]] = 0.0f;
+
+  int care[NP];   // (a solve's plans each have their own)
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+    care[p] = MODE != QM_SOLVE ? keep
+              : state_int(sw[p], offsetof(SolverState, again)) == state_int(sw[p], offsetof(SolverState, n_fwd))
+                  ? kCarePasses
+                  : max(state_int(sw[p], offsetof(SolverState, stored)) - 1, 0);
 
   bool on[NP];   // plans that are not done
 #pragma unroll
@@ -411,7 +535,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
       on[p] = P.has(p) && state_int(sw[p], offsetof(SolverState, phase)) != PH_DONE;
       any = any || on[p];
       if (P.has(p) && sl.w == 0 && wv == 0 && lane < kStateWords)
-        reinterpret_cast<int32_t*>(P(p).st_out)[lane] = sw[p];
+        reinterpret_cast<int32_t*>(P(p).st_out)[lane] = lane == static_cast<int>(offsetof(SolverState, stored) / 4) ? care[p] : sw[p];
     }
     if (!any) return;
     // the last step's norms, moved to where the next step reads them
@@ -447,6 +571,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
   uint32_t big[NT];   // largest magnitude's bits (orders NaN above infinity)
 #pragma unroll
   for (int q = 0; q < NT; ++q) big[q] = 0;
+  auto copy_of = [&](int q) { return P(q).q_x + (Plans::kMany ? 0 : static_cast<size_t>(q) * nb); };
   auto put = [&](int q, int i, float x, float s) {
     if (MODE == QM_POWER && a.norm_parts > 0)
       x = nrm > 0.0 ? static_cast<float>(static_cast<double>(x) / nrm) : 0.0f;
@@ -459,15 +584,24 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
     const int i = tid + u * THREADS;
     if (i < nb) {
 #pragma unroll
-      for (int q = 0; q < NT; ++q) put(q, i, xr[q][u], sc[u]);
+      for (int q = 0; q < NT; ++q) {
+        put(q, i, xr[q][u], sc[u]);
+        if (MODE == QM_SOLVE && active(q) && min(u, sl.G - 1) == sl.w) copy_of(q)[i] = xr[q][u];
+      }
     }
   }
-  for (int i = tid + U * THREADS; i < nb && MODE != QM_WHOLE; i += THREADS)
+  for (int i = tid + U * THREADS, u = U; i < nb && MODE != QM_WHOLE; i += THREADS, ++u)
 #pragma unroll
-    for (int q = 0; q < NT; ++q) put(q, i, vec(q)[i], coded(ST) ? a.col_scale[i] : 1.0f);
+    for (int q = 0; q < NT; ++q) {
+      const float x = vec(q)[i];
+      put(q, i, x, coded(ST) ? a.col_scale[i] : 1.0f);
+      if (MODE == QM_SOLVE && active(q) && min(u, sl.G - 1) == sl.w) copy_of(q)[i] = x;
+    }
   if (tid < NT) xs[tid * nbs] = 0.0f;
-  if (GRAD)
+  if (GRAD) {
     for (int i = tid; i < NT * nbs; i += THREADS) acc[i] = 0;
+    for (int i = tid; i < NT * nbs / 4; i += THREADS) reinterpret_cast<uint32_t*>(mark)[i] = 0;
+  }
 #pragma unroll
   for (int q = 0; q < NT; ++q) {
     big[q] = wave_max(big[q]);
@@ -477,7 +611,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
 
   // the unit of each vector's column sums
   double up[NT];    // residuals times up: in units
-  bool wild[NT];    // float64 sums instead
+  bool wild[NT];    // no integer sums: the step sums every column from the residuals
   bool any_wild = false;
 #pragma unroll
   for (int q = 0; q < NT; ++q) {
@@ -499,6 +633,10 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
 
   const uint32_t vbytes = 4u * static_cast<uint32_t>(a.nv);
   const rsrc_t dout = make_rsrc(a.d_out, a.d_out ? vbytes : 0u);
+  rsrc_t rout[NT];
+#pragma unroll
+  for (int q = 0; q < NT; ++q)
+    rout[q] = make_rsrc(MODE == QM_WHOLE ? W->out.r : P(q).rbuf[Plans::kMany ? 0 : q], active(q) ? vbytes : 0u);
   double pacc[NT];
   float z[NT][4];
   double rd[NT];    // residual of the lane's voxel, in units
@@ -538,6 +676,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
     if (MODE == QM_EVAL || MODE == QM_PLAIN) {
       if (q == 0 && count) store_f32(dout, 4u * (a.vox ? vox : row), d);
     }
+    if (GRAD && care[Plans::kMany ? q : 0] > 0 && count) store_f32(rout[q], 4u * row, r);
     return own ? r : 0.0f;
   };
   auto penalty_of = [&](int p, uint32_t sid, float tu, float to) {
@@ -548,6 +687,15 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
       pen.To = static_cast<double>(to);
     }
     return pen;
+  };
+
+  auto add_fixed = [&](int q, uint32_t c, double t) {
+    __hip_atomic_fetch_add(sum_at(acc + q * nbs, c), to_fixed(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  auto add_term = [&](int q, uint32_t c, double t) {
+    if (t == 0.0) return;
+    add_fixed(q, c, t);
+    mark[(Plans::kMany ? q * nbs : 0) + (c >> 2)] = 1;
   };
 
   auto compute = [&](const QuadStage<ST, NP>& S, const uint2 rec, int flags) {
@@ -584,24 +732,40 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (GRAD && (flags & kQuadAdjoint)) {
+    bool some = false;
+#pragma unroll
+    for (int q = 0; q < NT; ++q) some = some || live[q];
+    if (GRAD && (flags & kQuadAdjoint) && some) {
+      double r4[NT][4];
 #pragma unroll
       for (int q = 0; q < NT; ++q) {
-        if (!live[q]) continue;
-        const double r4[4] = {quad_bcast<0>(rd[q]), quad_bcast<1>(rd[q]), quad_bcast<2>(rd[q]), quad_bcast<3>(rd[q])};
+        r4[q][0] = quad_bcast<0>(rd[q]);
+        r4[q][1] = quad_bcast<1>(rd[q]);
+        r4[q][2] = quad_bcast<2>(rd[q]);
+        r4[q][3] = quad_bcast<3>(rd[q]);
+      }
 #pragma unroll
-        for (int m = 0; m < M; ++m) {
-          const uint32_t c = quad_col(S, m);
-          if (c != 0) {
-            QuadVal<ST> v = S.v[m];
-            // (codes are decoded again: keeping the dose's floats costs registers)
-            if constexpr (coded(ST)) asm("" : "+v"(v.x), "+v"(v.y));
-            double t = static_cast<double>(val_of<ST>(v, 0)) * r4[0];
+      for (int m = 0; m < M; ++m) {
+        const uint32_t c = quad_col(S, m);
+        if (c != 0) {   // (steps that no lane takes are passed over)
+          QuadVal<ST> v = S.v[m];
+          // (codes are decoded again: keeping the dose's floats costs registers)
+          if constexpr (coded(ST)) asm("" : "+v"(v.x), "+v"(v.y));
+          bool term = false;
 #pragma unroll
-            for (int u = 1; u < 4; ++u) t = __builtin_fma(static_cast<double>(val_of<ST>(v, u)), r4[u], t);
-            __hip_atomic_fetch_add(sum_at(acc + q * nbs, c), to_fixed(t), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+          for (int q = 0; q < NT; ++q) {
+            if (NT > 1 && !live[q]) continue;
+            double t = static_cast<double>(val_of<ST>(v, 0)) * r4[q][0];
+#pragma unroll
+            for (int u = 1; u < 4; ++u) t = __builtin_fma(static_cast<double>(val_of<ST>(v, u)), r4[q][u], t);
+            if (Plans::kMany || NT == 1) {
+              add_term(q, c, t);
+            } else {
+              add_fixed(q, c, t);
+              term = term || t != 0.0;
+            }
           }
+          if (!Plans::kMany && NT > 1 && term) mark[c >> 2] = 1;
         }
       }
     }
@@ -646,7 +810,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
         r4[2] = quad_bcast<2>(r);
         r4[3] = quad_bcast<3>(r);
       }
-      if (GRAD && (flags & kQuadAdjoint))
+      if (GRAD && (flags & kQuadAdjoint) && !wild[q])
         for (int j = sub; j < n / R; j += 1 << e)
           for (int k = R * j; k < R * j + R; ++k) {
             const QuadVal<ST> v = ev[k];
@@ -654,11 +818,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
 #pragma unroll
             for (int u = 0; u < 4; ++u)
               if (!quad_hole<ST>(v, u)) t = __builtin_fma(static_cast<double>(val_of<ST>(v, u)), r4[u], t);
-            unsigned long long* to = sum_at(acc + q * nbs, ec[k]);
-            if (wild[q])
-              __hip_atomic_fetch_add(reinterpret_cast<double*>(to), t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            else
-              __hip_atomic_fetch_add(to, to_fixed(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            add_term(q, ec[k], t);
           }
     }
   };
@@ -718,7 +878,10 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
     for (int q = 0; q < NT; ++q) {
       if (!active(q)) continue;
       unsigned long long* out = (MODE == QM_WHOLE ? W->out.acc : P(q).q_acc) + static_cast<size_t>(Plans::kMany ? sl.w : sl.w * NT + q) * nb;
-      for (int c = tid; c < nb; c += THREADS) out[c] = acc[q * nbs + c + 1];
+      for (int c = tid; c < nb; c += THREADS) {
+        const unsigned long long s = acc[q * nbs + c + 1];
+        out[c] = s == 0 ? mark[(Plans::kMany ? q * nbs : 0) + c + 1] : s;
+      }
     }
   }
 }
@@ -783,7 +946,7 @@ __global__ __launch_bounds__(WAVES * 64, (quad_waves_per_simd<K, WAVES>())) void
 // taken by whole waves in registers (no barrier: the first wave alone, or
 // every wave where the accepted trial picks the column sums to add), and one
 // barrier separates the partial sums from the totals.
-constexpr int kStepRows = kStepThreads / kStepCols;
+constexpr int kStepRows = kStepThreads / kStepCols, kStepWaves = kStepThreads / 64;
 constexpr int kStepU = 8;    // column sums per thread and round
 
 struct ColParts {
@@ -801,16 +964,16 @@ __device__ __forceinline__ void col_load(const AdjArgs& a, rsrc_t r, int nt, int
   }
 }
 
-__device__ __forceinline__ unsigned long long col_sum(const AdjArgs& a, rsrc_t r, int nt, int q, int c, int p0,
-                                                      const ColParts& P, bool wild) {
-  unsigned long long s = 0;
+__device__ __forceinline__ ColTotal col_sum(const AdjArgs& a, rsrc_t r, int nt, int q, int c, int p0,
+                                            const ColParts& P) {
+  ColTotal s{0, 0, 0};
 #pragma unroll
-  for (int u = 0; u < kStepU; ++u) s = add_parts(s, P.v[u], wild);
+  for (int u = 0; u < kStepU; ++u) add_part(s, P.v[u]);
   for (int p = p0 + kStepU * kStepRows; p < a.q_parts; p += kStepU * kStepRows) {
     ColParts R;
     col_load(a, r, nt, q, c, p, R);
 #pragma unroll
-    for (int u = 0; u < kStepU; ++u) s = add_parts(s, R.v[u], wild);
+    for (int u = 0; u < kStepU; ++u) add_part(s, R.v[u]);
   }
   return s;
 }
@@ -819,17 +982,63 @@ __device__ __forceinline__ rsrc_t acc_rsrc(const AdjArgs& a, int nt) {
   return make_rsrc(a.q_acc, 8u * static_cast<uint32_t>(a.q_parts) * static_cast<uint32_t>(nt * a.nb));
 }
 
-// First wave: the column's total (columns lane % kStepCols, in every lane)
-// from the partial sums in LDS, in the products' own scale.
-__device__ __forceinline__ double col_total(const unsigned long long* sh, double unit) {
-  const int lane = threadIdx.x & 63, c = lane & (kStepCols - 1), p0 = lane / kStepCols;
-  const bool wild = unit == 0.0;
-  unsigned long long s = 0;
+// Partial totals of a workgroup's columns in LDS.  w: `a`, saturated, above
+// six bits that count the partial totals with `any` set (32 at most).
+struct StepSums {
+  unsigned long long s[kStepThreads];
+  uint32_t w[kStepThreads];
+  double exact[kStepWaves][kStepCols];
+  uint32_t bad;
+};
+__device__ __forceinline__ void put_sum(StepSums& sh, const ColTotal& T) {
+  sh.s[threadIdx.x] = T.s;
+  sh.w[threadIdx.x] = min(T.a, 1u << 20) << 6 | (T.any != 0);
+}
+
+// After put_sum by all, in the first wave: the total of column c = sl.w * 16 +
+// lane % 16 in every lane, in the products' own scale.  Columns whose integers
+// are not precise enough (again: there are some) are summed again by all
+// waves.
+__device__ __forceinline__ double col_total(const AdjArgs& a, StepSums& sh, double unit, const float* r, const float* x,
+                                            int c, bool& again) {
+  const int lane = threadIdx.x & 63, wv = uniform(threadIdx.x >> 6), i = lane & (kStepCols - 1), p0 = lane / kStepCols;
+  __syncthreads();
+  bool bad = false;
+  double total = 0.0;
+  if (wv == 0) {
+    unsigned long long s = 0;
+    uint32_t w = 0;
 #pragma unroll
-  for (int p = 0; p < kStepRows; p += 64 / kStepCols) s = add_parts(s, sh[(p + p0) * kStepCols + c], wild);
+    for (int p = 0; p < kStepRows; p += 64 / kStepCols) {
+      s += sh.s[(p + p0) * kStepCols + i];
+      w += sh.w[(p + p0) * kStepCols + i];
+    }
 #pragma unroll
-  for (int d = kStepCols; d < 64; d <<= 1) s = add_parts(s, __shfl_xor(s, d), wild);
-  return wild ? __builtin_bit_cast(double, s) : static_cast<double>(static_cast<long long>(s)) * unit;
+    for (int d = kStepCols; d < 64; d <<= 1) {
+      s += __shfl_xor(s, d);
+      w += __shfl_xor(w, d);
+    }
+    bad = c < a.nb && imprecise(ColTotal{s, w >> 6, w & 63}, unit, a.enough);
+    total = static_cast<double>(static_cast<long long>(s)) * unit;
+    const uint64_t mask = __ballot(bad);
+    if (lane == 0) sh.bad = static_cast<uint32_t>(mask) & ((1u << kStepCols) - 1);
+  }
+  __syncthreads();
+  const uint32_t mask = uniform(static_cast<int>(sh.bad));
+  again = mask != 0;
+  if (again) {
+    for (int k = 0; k < kStepCols; ++k)
+      if (mask >> k & 1) {
+        const double t = exact_column(a.again, r, x, c - i + k, wv, kStepWaves);
+        if (lane == 0) sh.exact[wv][k] = t;
+      }
+    __syncthreads();
+    if (bad) {
+      total = 0.0;
+      for (int k = 0; k < kStepWaves; ++k) total += sh.exact[k][i];
+    }
+  }
+  return total;
 }
 
 __device__ __forceinline__ double col_factor(const AdjArgs& a, int c) {
@@ -844,9 +1053,20 @@ __global__ __launch_bounds__(64) void wave_sum_kernel(const double* parts, int n
   if (threadIdx.x == 0) *out = s + add;
 }
 
+// The state but for `again`, which another workgroup may be writing.
+__device__ __forceinline__ void put_state(SolverState* to, const SolverState& st) {
+  struct Words {
+    int32_t w[kStateWords];
+  };
+  const Words v = __builtin_bit_cast(Words, st);
+#pragma unroll
+  for (int i = 0; i < kStateWords; ++i)
+    if (i != static_cast<int>(offsetof(SolverState, again) / 4)) reinterpret_cast<int32_t*>(to)[i] = v.w[i];
+}
+
 template <int NT>
 __device__ __forceinline__ void step_pass(const AdjArgs& a, const Slot sl) {
-  __shared__ unsigned long long sh[kStepThreads];
+  __shared__ StepSums sh;
   const int tid = threadIdx.x, lane = tid & 63, wv = uniform(tid >> 6);
   const int c = sl.w * kStepCols + (tid & (kStepCols - 1)), p0 = tid / kStepCols;
   const bool decides = NT > 1 || wv == 0;
@@ -869,6 +1089,7 @@ __device__ __forceinline__ void step_pass(const AdjArgs& a, const Slot sl) {
   const rsrc_t ru = make_rsrc(a.q_unit, 8u * NT);
 #pragma unroll
   for (int q = 0; q < NT; ++q) unit[q] = load_f64(ru, 8u * q);
+  const int stored = load_i32(make_rsrc(a.st_in, static_cast<uint32_t>(sizeof(SolverState))), offsetof(SolverState, stored));
   if (wv == 0) {
     const uint32_t nb4 = 4u * static_cast<uint32_t>(a.nb), at = 4u * static_cast<uint32_t>(c);
     xk = load_f32(make_rsrc(a.xbuf[NT], nb4), at);
@@ -906,11 +1127,16 @@ __device__ __forceinline__ void step_pass(const AdjArgs& a, const Slot sl) {
   double u = unit[0];
 #pragma unroll
   for (int k = 1; k < NT; ++k) u = (q == k) ? unit[k] : u;
-  sh[tid] = col_sum(a, ra, NT, q, c, p0, CP, u == 0.0);
-  __syncthreads();
+  const float* r = a.rbuf[0];
+#pragma unroll
+  for (int k = 1; k < NT; ++k) r = (q == k) ? a.rbuf[k] : r;
+  put_sum(sh, col_sum(a, ra, NT, q, c, p0, CP));
+  bool again;
+  const double total = col_total(a, sh, u, uniform(stored) > 0 ? r : nullptr, a.q_x + static_cast<size_t>(q) * a.nb, c, again);
   if (wv != 0) return;
+  if (again && lane == 0) a.st_out->again = st.n_fwd;   // (the passes decided on so far)
   if (sl.w == 0 && lane == 0) {
-    *a.st_out = st;
+    put_state(a.st_out, st);
     if (v.accepted >= 0 && a.trace != nullptr && st.k - 1 < st.trace_cap) {
       TraceDev e;
       e.k = st.k;
@@ -930,7 +1156,7 @@ __device__ __forceinline__ void step_pass(const AdjArgs& a, const Slot sl) {
   }
   if (st.phase == PH_DONE) return;
   if (st.phase == PH_NEED_GRAD) {
-    g = static_cast<float>(factor * col_total(sh, u));
+    g = static_cast<float>(factor * total);
     if (mine) a.out[c] = g;
   }
   double lam = st.lambda;
@@ -950,13 +1176,18 @@ __device__ __forceinline__ void step_pass(const AdjArgs& a, const Slot sl) {
   }
 }
 
+// (one trial: 64 registers, so that four workgroups run side by side; with the
+// 72 that the compiler would take, 32 plans' steps took 9.5 against 8.5 us)
 template <int NT>
-__global__ __launch_bounds__(kStepThreads) void step_kernel(AdjArgs a) {
+constexpr int step_waves() { return NT == 1 ? 8 : 1; }
+
+template <int NT>
+__global__ __launch_bounds__(kStepThreads, step_waves<NT>()) void step_kernel(AdjArgs a) {
   step_pass<NT>(a, Slot{static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x)});
 }
 
 template <int NT>
-__global__ __launch_bounds__(kStepThreads) void step_batch_kernel(const AdjArgs* __restrict__ args,
+__global__ __launch_bounds__(kStepThreads, step_waves<NT>()) void step_batch_kernel(const AdjArgs* __restrict__ args,
                                                                   const int32_t* __restrict__ slots) {
   const int sv = uniform(slots[blockIdx.x]);
   if (sv < 0) return;
@@ -969,7 +1200,7 @@ __global__ __launch_bounds__(kStepThreads) void step_batch_kernel(const AdjArgs*
 // With `sum` one more workgroup adds parts[0..n) as wave_sum_kernel does.
 __global__ __launch_bounds__(kStepThreads) void reduce_kernel(AdjArgs a, double* norm, double* sum,
                                                               const double* parts, int n, double add) {
-  __shared__ unsigned long long sh[kStepThreads];
+  __shared__ StepSums sh;
   if (static_cast<int>(blockIdx.x) == step_grid(a.nb)) {
     if (threadIdx.x >= 64) return;
     SumLoads<8> L;
@@ -984,10 +1215,11 @@ __global__ __launch_bounds__(kStepThreads) void reduce_kernel(AdjArgs a, double*
   col_load(a, ra, 1, 0, c, p0, CP);
   const double unit = load_f64(make_rsrc(a.q_unit, 8u), 0);
   const double factor = col_factor(a, c);
-  sh[tid] = col_sum(a, ra, 1, 0, c, p0, CP, unit == 0.0);
-  __syncthreads();
+  put_sum(sh, col_sum(a, ra, 1, 0, c, p0, CP));
+  bool again;
+  const double total = col_total(a, sh, unit, a.rbuf[0], nullptr, c, again);
   if (tid >= 64) return;
-  const float g = static_cast<float>(factor * col_total(sh, unit));
+  const float g = static_cast<float>(factor * total);
   double sq = 0.0;
   if (tid < kStepCols && c < a.nb) {
     a.out[c] = g;
