@@ -449,7 +449,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
   extern __shared__ __align__(16) unsigned char smem[];
   const int nb = a.nb, nbs = quad_stride(nb);
   unsigned char* mark = smem;   // columns that received a term
-  auto* acc = reinterpret_cast<unsigned long long*>(smem + (GRAD ? quad_mark_bytes(nb, NT) : 0));
+  auto* acc = reinterpret_cast<unsigned long long*>(smem + (GRAD ? quad_mark_bytes(nb, NP) : 0));
   PenaltyDev* tab = reinterpret_cast<PenaltyDev*>(acc + (GRAD ? NT * nbs : 0));
   float* xs = reinterpret_cast<float*>(tab + NP * nst);
   __shared__ double red[WAVES];
@@ -600,7 +600,7 @@ __device__ __forceinline__ void quad_pass(const Plans& P, const Slot sl, int nst
   if (tid < NT) xs[tid * nbs] = 0.0f;
   if (GRAD) {
     for (int i = tid; i < NT * nbs; i += THREADS) acc[i] = 0;
-    for (int i = tid; i < NT * nbs / 4; i += THREADS) reinterpret_cast<uint32_t*>(mark)[i] = 0;
+    for (int i = tid; i < NP * nbs / 4; i += THREADS) reinterpret_cast<uint32_t*>(mark)[i] = 0;
   }
 #pragma unroll
   for (int q = 0; q < NT; ++q) {
@@ -1336,7 +1336,7 @@ int launch_quad_batch(const imrt_ctx* ctx, const FwdArgs* args, const int32_t* s
 int launch_quad_shared(const imrt_ctx* ctx, const FwdArgs* args, const int32_t* groups, int group_k,
                        const int32_t* slots, int nslots, int storage, int nb, int nstruct) {
   if (nslots <= 0) return IMRT_OK;
-  const size_t lds = quad_lds_bytes(nb, group_k, group_k * nstruct, QM_SOLVE);
+  const size_t lds = quad_lds_bytes(nb, group_k, group_k * nstruct, QM_SOLVE, group_k);
   if (!quad_fits(ctx->max_lds, lds)) return set_error(IMRT_EUNSUPPORTED, "shared one-read pass: LDS budget exceeded");
   if (group_k != 2 && group_k != 4) return set_error(IMRT_EINVAL, "shared-matrix groups hold 2 or 4 solves");
   const dim3 gd(nslots), bd(8 * 64);

@@ -22,13 +22,14 @@ constexpr int quad_stride(int nb) { return (nb + 1 + 3) & ~3; }
 
 constexpr size_t kPenaltyBytes = 32;   // of a structure's thresholds and weights
 
-// Bytes that the launch asks for: column marks (a byte each), column sums,
-// penalty tables (nstruct: of all plans together) and staged vectors.
-constexpr size_t quad_mark_bytes(int nb, int ntrials) {
-  return (static_cast<size_t>(ntrials) * static_cast<size_t>(quad_stride(nb)) + 15) & ~static_cast<size_t>(15);
+// Bytes that the launch asks for: column marks (a byte each, shared by a
+// plan's trials), column sums, penalty tables (nstruct: of all plans together)
+// and staged vectors.
+constexpr size_t quad_mark_bytes(int nb, int plans) {
+  return (static_cast<size_t>(plans) * static_cast<size_t>(quad_stride(nb)) + 15) & ~static_cast<size_t>(15);
 }
-constexpr size_t quad_lds_bytes(int nb, int ntrials, int nstruct, int mode) {
-  return static_cast<size_t>(nstruct) * kPenaltyBytes + (quad_grad(mode) ? quad_mark_bytes(nb, ntrials) : 0) +
+constexpr size_t quad_lds_bytes(int nb, int ntrials, int nstruct, int mode, int plans = 1) {
+  return static_cast<size_t>(nstruct) * kPenaltyBytes + (quad_grad(mode) ? quad_mark_bytes(nb, plans) : 0) +
          static_cast<size_t>(ntrials) * static_cast<size_t>(quad_stride(nb)) * (quad_grad(mode) ? 12 : 4);
 }
 
@@ -38,7 +39,7 @@ constexpr size_t quad_lds_bytes(int nb, int ntrials, int nstruct, int mode) {
 constexpr size_t kQuadFixedLds = 512;
 constexpr size_t kWholeFixedLds = 16384 + 512;
 
-// A workgroup's LDS holds both: two trials of about 6,290 beamlets are beyond
+// A workgroup's LDS holds both: two trials of about 6,530 beamlets are beyond
 // 160 KB only with the second, and keep the two separate passes.
 constexpr bool quad_fits(size_t max_lds, size_t lds_bytes, int mode = QM_SOLVE) {
   return lds_bytes + (mode == QM_WHOLE ? kWholeFixedLds : kQuadFixedLds) <= max_lds;

@@ -398,16 +398,14 @@ void worker_main(imrt_server* S) {
     // pass (shared-matrix adjoint); without sharing every solve is its own
     // group.  Each group takes the matrix's adjoint grid of slots.  One-read
     // passes likewise, where the group's vectors and column sums fit LDS.
-    size_t most = kShareMax;
-    while (most > 1 &&
-           !quad_fits(C->max_lds, quad_lds_bytes(qnb, static_cast<int>(most), static_cast<int>(most) * qns, QM_SOLVE)))
-      most /= 2;
+    int most = static_cast<int>(kShareMax);
+    while (most > 1 && !quad_fits(C->max_lds, quad_lds_bytes(qnb, most, most * qns, QM_SOLVE, most))) most /= 2;
     int gk[2];
     size_t ngroups = 0, nshared = 0;
     for (int one = 0; one < 2; ++one) {
       std::vector<std::vector<int>> groups;
       const bool share = S->ctx.tune.serve_shared_adj && (one == 0 || (nt == 1 && fwv == 8));
-      const size_t cap = one ? most : kShareMax;
+      const size_t cap = one ? static_cast<size_t>(most) : kShareMax;
       std::vector<const imrt_dose*> order;
       std::map<const imrt_dose*, std::vector<int>> by_dose;
       for (int i : active) {

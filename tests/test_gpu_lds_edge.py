@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 # (16-bit matrices of so many beamlets solve with two trials only once they are
 # partitioned for shared dispatches; four trials are refused before the line)
-@pytest.mark.parametrize("nt,nb,storage", [(2, nb, st) for nb in (6799, 6800, 6804, 6811, 6823, 6824)
+@pytest.mark.parametrize("nt,nb,storage", [(2, nb, st) for nb in (6527, 6528, 6799, 6804, 6811, 6823, 6824)
                                            for st in ("f32", "bf16")] +
                          [(4, nb, "f32") for nb in (3001, 3399, 3404, 3411)])
 def test_solve_at_the_edge(nt, nb, storage):

@@ -53,7 +53,7 @@ def test_both_sides_of_the_edge(rule):
         assert last + fixed <= MAX_LDS, (nt, ns, mode, nb)
         assert nb == 20000 or beyond + fixed > MAX_LDS, (nt, ns, mode, nb)
         # a vector's bytes and its column sums', at least
-        assert last >= nt * nb * (12 if mode in (0, 2, 4) else 4) + 32 * ns
+        assert last >= nt * nb * (12 if mode in (0, 2, 4) else 4) + (nb if mode in (0, 2, 4) else 0) + 32 * ns
     assert whole_bytes + whole <= 64 << 10
 
 
