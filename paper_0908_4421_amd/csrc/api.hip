@@ -457,11 +457,7 @@ void free_dose(imrt_dose* D) {
   dev_free(D->col_wlo);
   dev_free(D->col_whi);
   dev_free(D->col_kind);
-  dev_free(D->q_col);
-  if (D->q_val) (void)hipFree(D->q_val);
-  dev_free(D->q_head);
-  dev_free(D->q_zero);
-  dev_free(D->q_rec);
+  drop_quads(D);
   dev_free(D->vox);
   dev_free(D->vscratch);
   dev_free(D->pieces);
@@ -2451,6 +2447,7 @@ int repartition(imrt_dose* D, int32_t adj_min_nnz, int32_t fwd_blocks_per_wave, 
     D->fwd_waves = fwd_waves;
     int r = finish_columns(D, cp);
     if (!r && D->nwblocks > 0) r = finish_rows(D, rp);
+    if (!r && !one_read(D->ctx, D, 1, 0)) r = ensure_rows(D);
     return r ? r : fit_partials(D);
   } catch (const std::bad_alloc&) {
     return set_error(IMRT_ENOMEM, "host allocation failed");

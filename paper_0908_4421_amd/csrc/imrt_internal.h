@@ -543,9 +543,10 @@ int launch_reduce(const imrt_ctx* ctx, const AdjArgs& a, double* norm, double* s
                   const double* parts = nullptr, int n = 0, double add = 0.0);
 // out = (sum of parts[0..n) in the step's order) + add
 int launch_wave_sum(const imrt_ctx* ctx, const double* parts, int n, double* out, double add);
-// The quad form of a finished matrix (quads.hip), where it pays; its blocks
-// for the matrix's partition.
+// The quad form of a finished matrix (quads.hip), where it pays and the device
+// has room for it; its blocks for the matrix's partition.
 int build_quads(imrt_dose* D);
+void drop_quads(imrt_dose* D);
 int partition_quads(imrt_dose* D);
 bool one_read(const imrt_ctx* C, const imrt_dose* D, int nt, int nstruct);
 int quad_grid(const imrt_dose* D, int nt);

@@ -2,6 +2,7 @@
 // imrt_internal.h for its layout): built on the device from the CSR arrays,
 // its work partition on the host.
 #include <algorithm>
+#include <new>
 
 #include "pass_common.h"
 
@@ -185,8 +186,52 @@ int quad_grid(const imrt_dose* D, int nt) { return D->q_waves / forward_waves(nt
 // Bytes of the entries that a one-read pass reads.
 int64_t quad_bytes(const imrt_dose* D) { return D->nent * (D->storage == ST_F32 ? 18 : 10); }
 
-int build_quads(imrt_dose* D) {
-  if (!D->ctx->tune.one_read || D->nb > 8191 || D->nnz == 0 || (D->storage == ST_F32 && D->fwd_st != ST_F32C16))
+// The matrix without its quad form: the two separate passes.
+void drop_quads(imrt_dose* D) {
+  for (void* p : {static_cast<void*>(D->q_col), D->q_val, static_cast<void*>(D->q_head), static_cast<void*>(D->q_rec),
+                  static_cast<void*>(D->q_zero)})
+    if (p) (void)hipFree(p);
+  D->q_col = nullptr;
+  D->q_val = nullptr;
+  D->q_head = nullptr;
+  D->q_rec = nullptr;
+  D->q_zero = nullptr;
+  D->nent = 0;
+  D->nzero = 0;
+  D->q_nblocks = D->q_kmax = D->q_waves = 0;
+  D->qn.clear();
+  D->qrow.clear();
+  D->qgaps.clear();
+}
+
+namespace {
+
+// Waits for a stream's copies from and to what was declared before it, also
+// where an exception ends the function.
+struct Drain {
+  hipStream_t s;
+  ~Drain() { (void)hipStreamSynchronize(s); }
+};
+
+// The form is extra: a matrix whose device has no room for it goes without.
+template <typename Make>
+int quads_or_none(imrt_dose* D, Make make) {
+  int rc;
+  try {
+    rc = make();
+  } catch (const std::bad_alloc&) {
+    rc = IMRT_ENOMEM;
+  }
+  if (rc != IMRT_ENOMEM) return rc;
+  (void)hipGetLastError();
+  drop_quads(D);
+  return IMRT_OK;
+}
+
+int place_quads(imrt_dose* D);
+
+int make_quads(imrt_dose* D) {
+  if (!D->ctx->tune.one_read || D->nb > 8191 || D->nv >= (1 << 30) || D->nnz == 0 || (D->storage == ST_F32 && D->fwd_st != ST_F32C16))
     return IMRT_OK;
   if (!quad_fits(D->ctx->max_lds, quad_lds_bytes(D->nb, 1, kMaxStruct, QM_SOLVE))) return IMRT_OK;
   hipStream_t s = D->ctx->stream;
@@ -266,6 +311,8 @@ int build_quads(imrt_dose* D) {
       (rc = alloc(reinterpret_cast<void**>(&D->q_col), 2 * ents)) || (rc = alloc(&D->q_val, vb * ents)))
     return rc;
   auto* d_row = static_cast<int32_t*>(ord.p);
+  unsigned long long bits[2] = {0, 0};
+  const Drain drain{s};
   IMRT_HIP(hipMemcpyAsync(d_row, order.data(), sizeof(int32_t) * order.size(), hipMemcpyHostToDevice, s));
   IMRT_HIP(hipMemsetAsync(D->q_col + nent, 0, 2 * kQuadPad, s));
   IMRT_HIP(hipMemsetAsync(static_cast<char*>(D->q_val) + vb * nent, 0, vb * kQuadPad, s));
@@ -279,13 +326,12 @@ int build_quads(imrt_dose* D) {
   else if (D->storage == ST_BF16) fill(quad_fill_kernel<ST_BF16, uint16_t>, D->col16, column_sum_kernel<ST_BF16>);
   else fill(quad_fill_kernel<ST_F16, uint16_t>, D->col16, column_sum_kernel<ST_F16>);
   IMRT_HIP(hipGetLastError());
-  unsigned long long bits[2] = {0, 0};
   IMRT_HIP(hipMemcpyAsync(bits, d_sums, sizeof(bits), hipMemcpyDeviceToHost, s));
   D->nent = nent;
   D->qn.swap(qn);
   D->qrow.swap(qrow);
   D->qgaps.swap(gaps);
-  rc = partition_quads(D);
+  rc = place_quads(D);
   IMRT_HIP(hipStreamSynchronize(s));
   // (a little over the sums: they are rounded)
   D->q_rowsum = __builtin_bit_cast(double, bits[0]) * (1.0 + 1e-9);
@@ -296,7 +342,7 @@ int build_quads(imrt_dose* D) {
 // Waves get runs of quads of about equal cost; each wave's run is cut into
 // blocks.  As in the wave forward, a matrix solved alone spreads over up to
 // 16 waves of every compute unit, one with per-plan targets over fewer.
-int partition_quads(imrt_dose* D) {
+int place_quads(imrt_dose* D) {
   const int full = quad_full(D->storage), run = quad_run(D->storage), nq = static_cast<int>(D->qn.size());
   const std::vector<int32_t>& qn = D->qn;
   constexpr int kQuadCost = 8;   // of a quad beside its entries, in entries
@@ -399,6 +445,16 @@ int partition_quads(imrt_dose* D) {
   D->q_kmax = kmax;
   D->q_waves = static_cast<int32_t>(waves);
   return IMRT_OK;
+}
+
+}  // namespace
+
+int build_quads(imrt_dose* D) {
+  return quads_or_none(D, [&] { return make_quads(D); });
+}
+
+int partition_quads(imrt_dose* D) {
+  return quads_or_none(D, [&] { return place_quads(D); });
 }
 
 }  // namespace imrt

@@ -1,0 +1,74 @@
+"""The quad form of a matrix is extra: where the device has no room for it the
+matrix goes without."""
+import gc
+
+import numpy as np
+import pytest
+
+from gpu_util import banner, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrix(nv, nb, row):
+    """Four consecutive rows share their columns (full quads)."""
+    start = (np.arange(nv) // 4 * 7) % (nb - row)
+    cols = (start[:, None] + np.arange(row)[None, :]).astype(np.int32).ravel()
+    rng = np.random.default_rng(1)
+    return (np.arange(nv + 1) * row).astype(np.int32), cols, rng.uniform(0.1, 1.0, nv * row).astype(np.float32)
+
+
+def _gradient(dose, sid):
+    from paper_0908_4421_amd.imrt import Plan
+    plan = Plan(dose.ctx, dose)
+    plan.set_structures(sid, 2)
+    plan.set_penalties([(2.0, 3.0, 1.0, 0.5), (0.0, 1.5, 0.0, 0.3)])
+    x = to_dev(np.full(dose.nb, 0.05, np.float32))
+    g, G = plan.gradient(x)
+    return to_host(g), G
+
+
+def test_a_device_without_room_for_the_form():
+    import torch
+    from paper_0908_4421_amd import imrt
+    from paper_0908_4421_amd.imrt import Context, Dose
+    nv, nb, row = 200000, 700, 120
+    rp, ci, v = _matrix(nv, nb, row)
+    sid = (np.arange(nv) % 2).astype(np.uint8)
+
+    def build(mode):
+        return Dose.from_csr(Context(0, one_read=mode), nv, nb, rp, ci, v)
+
+    def free():
+        torch.cuda.synchronize()
+        gc.collect()
+        torch.cuda.empty_cache()
+        return torch.cuda.mem_get_info()[0]
+
+    build(2)   # (code objects and the like)
+    f0 = free()
+    dose = build(0)
+    base = f0 - free()
+    want = _gradient(dose, sid)
+    del dose
+    f1 = free()
+    dose = build(2)
+    full = f1 - free()
+    assert imrt.imrt_dose_one_read(dose.handle)[0] > 0 and full - base > 80 << 20
+    got = _gradient(dose, sid)
+    assert abs(got[1] - want[1]) <= 1e-5 * want[1]
+    del dose
+    free()
+    # room for the matrix and half of its form
+    goal, hold = base + (full - base) // 2, []
+    while len(hold) < 16 and torch.cuda.mem_get_info()[0] > goal + (8 << 20):
+        hold.append(torch.empty(torch.cuda.mem_get_info()[0] - goal, dtype=torch.uint8, device="cuda"))
+    banner(f"matrix {base >> 20} MiB, form {(full - base) >> 20} MiB, {torch.cuda.mem_get_info()[0] >> 20} MiB left")
+    dose = build(2)
+    assert imrt.imrt_dose_one_read(dose.handle) == (0, 0)
+    del hold
+    free()
+    got = _gradient(dose, sid)
+    assert got[1] == want[1] and np.array_equal(got[0], want[0])   # the two separate passes
+    dose.repartition_targets(128, 32)
+    assert np.array_equal(_gradient(dose, sid)[0], _gradient(dose, sid)[0])
