@@ -83,18 +83,23 @@ struct Finished {
 
 // Device bytes of a dose matrix (values, indices, partition tables) and of a
 // plan's buffers, as allocated by this library.
+int64_t form_bytes(const imrt_dose* D) {
+  return (D->q_waves > 0) ? quad_bytes(D) + 136 * static_cast<int64_t>(D->q_nblocks) : 0;
+}
+
 int64_t dose_bytes(const imrt_dose* D) {
   const int64_t nnz = D->nnz, nv = D->nv, nb = D->nb;
   const int64_t per_nz = (D->storage == ST_F32) ? (D->col16 ? 18 : 16) : 10;
-  const int64_t quads = (D->q_waves > 0) ? quad_bytes(D) + 136 * static_cast<int64_t>(D->q_nblocks) : 0;
-  return quads + per_nz * nnz + 4 * (nv + 1) + 4 * (nb + 1) + 2 * nv /* ids, order */ + 4 * nv /* permutation scratch */ +
+  return form_bytes(D) + per_nz * nnz + 4 * (nv + 1) + 4 * (nb + 1) + 2 * nv /* ids, order */ + 4 * nv /* permutation scratch */ +
          4 * static_cast<int64_t>(D->nwblocks + D->nblocks) * 2 + 16 * D->adj_grid + 9 * nb;
 }
 
 int64_t plan_bytes(const imrt_dose* D, int nt) {
-  const int64_t nv = D->nv, nb = D->nb;
-  const int64_t quads = (D->q_waves > 0) ? 8 * (static_cast<int64_t>(quad_grid(D, nt)) * nt * nb + nb) : 0;
-  return quads + (4 * (nt + 1) + 4 + 1) * nv + (4 * (nt + 1) + 4 + 16) * nb + 16 * D->adj_grid + 8 * 4096;
+  const int64_t nv = D->nv, nb = D->nb, rest = 16 * D->adj_grid + 8 * 4096;
+  if (D->q_waves > 0)   // trials but the first keep residuals of their own; column sums, units, norms, copies of the trials
+    return (4 * nt + 1) * nv + (4 * (nt + 1) + 4 + 16 + 4 * kMaxTrials) * nb + 8 * static_cast<int64_t>(quad_grid(D, nt)) * nt * nb +
+           8 * (2 * kMaxTrials + 1) * step_grid(D->nb) + rest;
+  return (4 * (nt + 1) + 4 + 1) * nv + (4 * (nt + 1) + 4 + 16) * nb + rest;
 }
 
 }  // namespace
@@ -146,14 +151,45 @@ int grow_slots(imrt_server* S, int32_t** p, size_t* cap, size_t need) {
   return IMRT_OK;
 }
 
+// A matrix that nobody uses, without its quad form; returns the bytes that
+// this frees.
+int64_t drop_form(Resident& r) {
+  const int64_t before = r.bytes;
+  drop_quads(r.dose);
+  (void)ensure_rows(r.dose);   // (else made when first needed)
+  r.bytes = dose_bytes(r.dose);
+  return before - r.bytes;
+}
+
+// The least recently used of the resident matrices that nobody uses (`forms`:
+// of those that keep the quad form).
+std::map<int64_t, Resident>::iterator find_victim(imrt_server* S, bool forms) {
+  auto victim = S->residents.end();
+  for (auto it = S->residents.begin(); it != S->residents.end(); ++it)
+    if (it->second.users == 0 && (!forms || it->second.dose->q_waves > 0) &&
+        (victim == S->residents.end() || it->second.last_use < victim->second.last_use))
+      victim = it;
+  return victim;
+}
+
+// `need` more bytes fit the budget once quad forms that nobody uses are gone.
+// These go before any matrix does, so that the budget holds the matrices and
+// requests that it holds without them.
+bool make_room_of_forms(imrt_server* S, int64_t need) {
+  while (S->used + need > S->budget) {
+    const auto victim = find_victim(S, true);
+    if (victim == S->residents.end()) return false;
+    S->used -= drop_form(victim->second);
+  }
+  return true;
+}
+
 // Evict resident matrices nobody uses, least recently used first, until
 // `need` more bytes fit the budget (caller holds no lock; worker only).
 bool make_room(imrt_server* S, int64_t need) {
+  if (make_room_of_forms(S, need)) return true;
   while (S->used + need > S->budget) {
-    auto victim = S->residents.end();
-    for (auto it = S->residents.begin(); it != S->residents.end(); ++it)
-      if (it->second.users == 0 && (victim == S->residents.end() || it->second.last_use < victim->second.last_use))
-        victim = it;
+    const auto victim = find_victim(S, false);
     if (victim == S->residents.end()) return false;
     (void)imrt_dose_destroy(victim->second.dose);
     S->used -= victim->second.bytes;
@@ -196,7 +232,8 @@ bool admit(imrt_server* S, Pending& p, int slot) {
     Resident r;
     r.dose = D;
     r.bytes = dose_bytes(D);
-    S->reserve = std::max(S->reserve, r.bytes);
+    S->reserve = std::max(S->reserve, r.bytes - form_bytes(D));
+    if (D->q_waves > 0 && !make_room_of_forms(S, r.bytes)) (void)drop_form(r);
     if (!make_room(S, r.bytes)) {   // larger than foreseen: wait until it fits
       (void)imrt_dose_destroy(D);
       return false;
@@ -214,12 +251,18 @@ bool admit(imrt_server* S, Pending& p, int slot) {
     if (LD->storage != D->storage || LD->fwd_st != D->fwd_st || LD->fwd_waves != D->fwd_waves || S->live[i].nt != nt)
       return false;
   }
-  const int64_t pb = plan_bytes(D, nt) + (p.params.trace ? static_cast<int64_t>(sizeof(imrt_trace_entry)) *
-                                                              std::max(0, p.params.max_iter) : 0);
+  const int64_t tb = p.params.trace ? static_cast<int64_t>(sizeof(imrt_trace_entry)) * std::max(0, p.params.max_iter) : 0;
+  int64_t pb = plan_bytes(D, nt) + tb;
   if (S->used + pb > S->budget) {
-    rit->second.users += 1;   // keep it while making room for the plan
-    const bool ok = make_room(S, pb);
-    rit->second.users -= 1;
+    Resident& own = rit->second;
+    own.users += 1;   // keep it while making room for the plan
+    bool ok = make_room_of_forms(S, pb);
+    if (!ok && own.users == 1 && D->q_waves > 0) {
+      S->used -= drop_form(own);
+      pb = plan_bytes(D, nt) + tb;
+    }
+    ok = ok || make_room(S, pb);
+    own.users -= 1;
     if (!ok) return false;
   }
   Live L;

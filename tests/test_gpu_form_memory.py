@@ -1,11 +1,13 @@
-"""The quad form of a matrix is extra: where the device has no room for it the
-matrix goes without."""
+"""The quad form of a matrix is extra: where there is no room for it, on the
+device or in a server's budget, the matrix goes without and everything that is
+served without the form still is."""
 import gc
 
 import numpy as np
 import pytest
 
 from gpu_util import banner, to_dev, to_host
+from workloads import SMALL, draw_batch_instance, penalty_table
 
 pytestmark = pytest.mark.gpu
 
@@ -72,3 +74,43 @@ def test_a_device_without_room_for_the_form():
     assert got[1] == want[1] and np.array_equal(got[0], want[0])   # the two separate passes
     dose.repartition_targets(128, 32)
     assert np.array_equal(_gradient(dose, sid)[0], _gradient(dose, sid)[0])
+
+
+def _serve(one_read, budget, specs):
+    from paper_0908_4421_amd.imrt import Context, Server
+    srv = Server(Context(0, one_read=one_read), budget_bytes=budget, max_live=4)
+    out = []
+    try:
+        for i, sp in enumerate(specs):
+            t = srv.submit(i, sp, penalty_table(sp), max_iter=20, fixed_iters=True)
+            out.append(srv.wait(t)[0])
+        st = srv.stats()
+    finally:
+        srv.close()
+    return out, st
+
+
+def test_a_budget_that_holds_one_request():
+    """The smallest budget that serves a request without the form."""
+    _, st = _serve(0, 8 << 30, [SMALL])
+    budget = st["peak_bytes"]
+    banner(f"budget {budget} bytes")
+    for one_read in (0, 1):
+        out, st = _serve(one_read, budget, [SMALL])
+        assert out[0].iterations == 20 and st["served"] == 1 and st["peak_bytes"] <= budget
+
+
+def test_a_budget_keeps_as_many_matrices():
+    specs = [draw_batch_instance(s) for s in (1000, 1001, 1002, 1003)]
+    _, st = _serve(0, 8 << 30, specs)
+    budget = st["peak_bytes"]
+    got = {}
+    for one_read in (0, 1):
+        out, st = _serve(one_read, budget, specs)
+        assert all(r.iterations == 20 for r in out) and st["peak_bytes"] <= budget
+        got[one_read] = st["resident_matrices"]
+        banner(f"one_read {one_read}: {got[one_read]} resident of {len(specs)}")
+    assert got[1] == got[0] >= 3
+    # forms are kept where there is room
+    big = _serve(1, 8 << 30, specs)[1]
+    assert big["used_bytes"] > budget * 0.9 and big["resident_matrices"] == len(specs)
