@@ -55,16 +55,10 @@ int use_device(const imrt_ctx* ctx) {
 }
 
 // Largest forward grid of either forward variant at the current settings.
-int forward_grid_cap(imrt_ctx* ctx, const imrt_dose* D) {
-  const int saved = ctx->tune.fwd_wave;
-  int g = 1;
-  for (int wave = 0; wave <= 1; ++wave)
-    for (int nt : {1, 2}) {
-      ctx->tune.fwd_wave = wave;
-      g = std::max(g, forward_grid(ctx, D, nt));
-    }
-  g = std::max(g, D->q_waves / 8);
-  ctx->tune.fwd_wave = saved;
+int forward_grid_cap(const imrt_ctx* ctx, const imrt_dose* D) {
+  int g = std::max(1, D->q_waves / 8);
+  for (const bool wave : {false, true})
+    for (int nt : {1, 2}) g = std::max(g, forward_grid(ctx, D, nt, wave));
   if (D->nwblocks == 0) g = std::max(g, kWaves * ctx->tune.fwd_grid_per_cu * ctx->num_cu);   // (blocks yet to come)
   return g;
 }
@@ -165,7 +159,7 @@ int fit_partials(imrt_dose* D) {
 
 // Row blocks for the forward pass: at most kFwdPartNnz nonzeros and
 // kFwdRowsMax rows each, or one longer row alone.
-int finish_rows(imrt_dose* D, const std::vector<int32_t>& row_ptr) {
+int finish_rows(imrt_dose* D, const std::vector<int32_t>& row_ptr, hipStream_t s) {
   std::vector<int32_t> blocks, block_k0;
   blocks.push_back(0);
   int r = 0;
@@ -274,7 +268,7 @@ int finish_rows(imrt_dose* D, const std::vector<int32_t>& row_ptr) {
 
   D->nblocks = static_cast<int32_t>(blocks.size()) - 1;
   D->gaps.swap(gaps);
-  D->part_epoch += 1;
+  D->row_epoch += 1;
   // (a repartition replaces the previous tables)
   for (int32_t** p : {&D->block_row, &D->block_k0, &D->wblock_row, &D->wblock_k0, &D->wblock_end}) dev_free(*p);
   int rc;
@@ -282,7 +276,6 @@ int finish_rows(imrt_dose* D, const std::vector<int32_t>& row_ptr) {
       (rc = dev_alloc(&D->wblock_row, wblocks.size())) || (rc = dev_alloc(&D->wblock_k0, wblock_k0.size())) ||
       (rc = dev_alloc(&D->wblock_end, std::max<size_t>(wblock_end.size(), 1))))
     return rc;
-  hipStream_t s = D->ctx->stream;
   auto upload = [&](int32_t* to, const std::vector<int32_t>& v) {
     return hipMemcpyAsync(to, v.data(), sizeof(int32_t) * v.size(), hipMemcpyHostToDevice, s);
   };
@@ -292,23 +285,34 @@ int finish_rows(imrt_dose* D, const std::vector<int32_t>& row_ptr) {
   IMRT_HIP(upload(D->wblock_k0, wblock_k0));
   IMRT_HIP(upload(D->wblock_end, wblock_end));
   IMRT_HIP(hipStreamSynchronize(s));
-  D->nwblocks = static_cast<int32_t>(wblocks.size()) - 1;   // (the blocks are there)
-  return fit_partials(D);
+  D->nwblocks = static_cast<int32_t>(wblocks.size()) - 1;
+  return IMRT_OK;
 }
 
 // The row blocks of a matrix that keeps the quad form are made when a pass
 // first needs them (a solve whose trials do not fit the one-read pass, or the
-// workgroup-wide forward): its one-read passes never do.
+// workgroup-wide forward): its one-read passes never do.  Any plan's thread
+// may come first, so they are made on a stream of their own, and nothing that
+// other passes of the matrix use is replaced (its partial sums have room for
+// them from the start).
 int ensure_rows(const imrt_dose* dose) {
   auto* D = const_cast<imrt_dose*>(dose);
   std::lock_guard<std::mutex> lock(D->late);
   if (D->nwblocks > 0) return IMRT_OK;
   const int rc = use_device(D->ctx);
   if (rc) return rc;
+  struct Own {
+    hipStream_t s = nullptr;
+    ~Own() {
+      if (s) (void)hipStreamDestroy(s);
+    }
+  } own;
   try {
     std::vector<int32_t> rp(static_cast<size_t>(D->nv) + 1);
-    IMRT_HIP(hipMemcpy(rp.data(), D->row_ptr, sizeof(int32_t) * rp.size(), hipMemcpyDeviceToHost));
-    return finish_rows(D, rp);
+    IMRT_HIP(hipStreamCreateWithFlags(&own.s, hipStreamNonBlocking));
+    IMRT_HIP(hipMemcpyAsync(rp.data(), D->row_ptr, sizeof(int32_t) * rp.size(), hipMemcpyDeviceToHost, own.s));
+    IMRT_HIP(hipStreamSynchronize(own.s));
+    return finish_rows(D, rp, own.s);
   } catch (const std::bad_alloc&) {
     return set_error(IMRT_ENOMEM, "host allocation failed");
   }
@@ -400,7 +404,6 @@ int finish_columns(imrt_dose* D, const std::vector<int32_t>& col_ptr) {
     const int qrc = partition_quads(D);
     if (qrc) return qrc;
   }
-  D->part_epoch += 1;
   D->adj_grid = G;
   // (a repartition replaces the previous tables)
   for (int32_t** p : {&D->wg_cols, &D->wg_k, &D->col_wlo, &D->col_whi}) dev_free(*p);
@@ -554,15 +557,16 @@ int plan_use(imrt_plan* P, int nt = 1) {
 double plan_skip_objective(imrt_plan* P, bool quads) {
   const imrt_dose* D = P->dose;
   if (P->ctx->tune.fwd_wave == 0) return 0.0;
+  const int64_t epoch = quads ? D->quad_epoch : D->row_epoch;
   imrt_plan::Skip& K = P->skip[quads ? 1 : 0];
   const auto& gaps = quads ? D->qgaps : D->gaps;
-  if (K.epoch == D->part_epoch) return K.G;
+  if (K.epoch == epoch) return K.G;
   // skipped rows per structure (kept until the structures or the partition change)
-  if (K.hist_epoch != D->part_epoch) {
+  if (K.hist_epoch != epoch) {
     K.hist.assign(kMaxStruct, 0);
     for (const auto& gap : gaps)
       for (int32_t j = gap.first; j < gap.second; ++j) ++K.hist[P->sid_host[j]];
-    K.hist_epoch = D->part_epoch;
+    K.hist_epoch = epoch;
   }
   auto F0 = [](double Tu, double To, double wu, double wo) {
     const double under = std::fmin(0.0 - Tu, 0.0);
@@ -586,7 +590,7 @@ double plan_skip_objective(imrt_plan* P, bool quads) {
       }
   }
   K.G = G;
-  K.epoch = D->part_epoch;
+  K.epoch = epoch;
   return G;
 }
 
@@ -2446,7 +2450,7 @@ int repartition(imrt_dose* D, int32_t adj_min_nnz, int32_t fwd_blocks_per_wave, 
     D->fwd_bpw = fwd_blocks_per_wave;
     D->fwd_waves = fwd_waves;
     int r = finish_columns(D, cp);
-    if (!r && D->nwblocks > 0) r = finish_rows(D, rp);
+    if (!r && D->nwblocks > 0) r = finish_rows(D, rp, s);
     if (!r && !one_read(D->ctx, D, 1, 0)) r = ensure_rows(D);
     return r ? r : fit_partials(D);
   } catch (const std::bad_alloc&) {

@@ -1052,9 +1052,12 @@ size_t forward_lds_bytes(int nb, int ntrials, int nstruct, bool wave, int storag
 
 int forward_waves(int ntrials, int dose_waves) { return (ntrials <= 2 && dose_waves == 16) ? 16 : 8; }
 
-int forward_grid(const imrt_ctx* ctx, const imrt_dose* D, int ntrials) {
-  if (ctx->tune.fwd_wave) return wave_grid(ctx, D->nwblocks, ntrials, D->fwd_bpw, D->nb, D->fwd_st, D->fwd_waves);
+int forward_grid(const imrt_ctx* ctx, const imrt_dose* D, int ntrials, bool wave) {
+  if (wave) return wave_grid(ctx, D->nwblocks, ntrials, D->fwd_bpw, D->nb, D->fwd_st, D->fwd_waves);
   return grid_for(D->nblocks, kWaves * ctx->tune.fwd_grid_per_cu * ctx->num_cu);
+}
+int forward_grid(const imrt_ctx* ctx, const imrt_dose* D, int ntrials) {
+  return forward_grid(ctx, D, ntrials, ctx->tune.fwd_wave != 0);
 }
 
 // Forward workgroups per compute unit: the setting, but no more than fit

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <mutex>
 #include <string>
@@ -358,15 +359,15 @@ struct imrt_dose {
   int32_t nblocks = 0;
   int32_t* block_row = nullptr;
   int32_t* block_k0 = nullptr;
-  int32_t nwblocks = 0;
+  std::atomic<int32_t> nwblocks{0};   // (set once the blocks are there)
   int32_t* wblock_row = nullptr;
   int32_t* wblock_k0 = nullptr;
   int32_t* wblock_end = nullptr;
   // runs of empty rows the wave blocks skip, [first, end) in internal row
-  // order, and a counter of partitions (a plan's constant for the skipped
-  // rows follows it)
+  // order, and a counter of row partitions (a plan's constant for the skipped
+  // rows follows it); read after ensure_rows
   std::vector<std::pair<int32_t, int32_t>> gaps;
-  int64_t part_epoch = 0;
+  int64_t row_epoch = 0;
   int32_t adj_grid = 0;        // workgroups of the adjoint partition
   uint32_t q_enough = 0;       // see quad_enough
   int32_t* wg_cols = nullptr;
@@ -387,6 +388,7 @@ struct imrt_dose {
   double q_rowsum = 0.0, q_colsum = 0.0;
   std::vector<int32_t> qn, qrow;
   std::vector<std::pair<int32_t, int32_t>> qgaps;
+  int64_t quad_epoch = 0;      // of qgaps, likewise
   int32_t* q_zero = nullptr;   // the voxels of those rows, in the caller's order
   int32_t nzero = 0;
   // internal voxel order (nullable: the caller's order): row p of D is voxel
@@ -394,7 +396,8 @@ struct imrt_dose {
   int32_t* vox = nullptr;
   std::vector<int32_t> vox_host;   // downloaded when first needed (host_order)
   // guards what a matrix gets on first use: vox_host, and the row blocks of
-  // a matrix that keeps the quad form (ensure_rows)
+  // a matrix that keeps the quad form (ensure_rows): plans of several contexts
+  // and threads may share a matrix
   std::mutex late;
   float* vscratch = nullptr;   // nv floats for permuted products
   // structure ids from the phantom builder (nullable; internal order)
@@ -475,6 +478,7 @@ int check_launch(const char* what);
 void clear_stale_error();
 // forward grid: wave-granular pass, fwd_grid_per_cu workgroups of 16 waves
 // (8 for several trials) per CU; workgroup-granular pass, 4x as many of 4 waves
+int forward_grid(const imrt_ctx* ctx, const imrt_dose* D, int ntrials, bool wave);
 int forward_grid(const imrt_ctx* ctx, const imrt_dose* D, int ntrials = 1);
 int wave_grid(const imrt_ctx* ctx, int nwblocks, int ntrials, int blocks_per_wave, int nb, int storage,
               int dose_waves);
@@ -565,7 +569,7 @@ void apply_partition_targets(const imrt_ctx* ctx, imrt_dose* D);
 // host preprocessing (api.hip)
 int alloc_nonzeros(imrt_dose* D);
 int finish_columns(imrt_dose* D, const std::vector<int32_t>& col_ptr);
-int finish_rows(imrt_dose* D, const std::vector<int32_t>& row_ptr);
+int finish_rows(imrt_dose* D, const std::vector<int32_t>& row_ptr, hipStream_t s);
 int ensure_rows(const imrt_dose* D);
 int fit_partials(imrt_dose* D);
 

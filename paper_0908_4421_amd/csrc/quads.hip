@@ -202,6 +202,7 @@ void drop_quads(imrt_dose* D) {
   D->qn.clear();
   D->qrow.clear();
   D->qgaps.clear();
+  D->quad_epoch += 1;
 }
 
 namespace {
@@ -331,6 +332,7 @@ int make_quads(imrt_dose* D) {
   D->qn.swap(qn);
   D->qrow.swap(qrow);
   D->qgaps.swap(gaps);
+  D->quad_epoch += 1;
   rc = place_quads(D);
   IMRT_HIP(hipStreamSynchronize(s));
   // (a little over the sums: they are rounded)
