@@ -541,10 +541,32 @@ int plan_fit(imrt_plan* P) {
   return fit_quad(P, 1);
 }
 
-int plan_use(imrt_plan* P, int nt = 1) {
+// Row blocks for the forward passes of a context over D.  (The workgroup-wide
+// forward refuses 16-bit storage, with or without them.)
+int rows_for(const imrt_ctx* C, const imrt_dose* D) {
+  return C->tune.fwd_wave == 0 && D->storage != ST_F32 ? IMRT_OK : ensure_rows(D);
+}
+
+// Whether a single product takes the one-read pass: by the rule, or because
+// the row blocks that the other route needs (after fwd_wave was set to 0) are
+// not there and must not be made: the call allocates nothing, or its stream
+// is being captured.
+bool one_product(const imrt_ctx* C, const imrt_dose* D, int nstruct, bool no_alloc) {
+  if (one_read(C, D, 1, nstruct)) return true;
+  if (D->q_waves == 0 || D->storage != ST_F32 || D->nwblocks > 0) return false;
+  if (no_alloc) return true;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(C->stream, &st) != hipSuccess) (void)hipGetLastError();
+  return st == hipStreamCaptureStatusActive;
+}
+
+// `quads`: the route of the plan's passes (of one trial, or as solve_prepare
+// finds it for more), taken once a call.
+int plan_use(imrt_plan* P, bool* quads) {
   int rc = plan_ready(P);
   if (rc) return rc;
-  if (!one_read(P->ctx, P->dose, nt, P->nstruct) && (rc = ensure_rows(P->dose))) return rc;
+  *quads = one_product(P->ctx, P->dose, P->nstruct, false);
+  if (!*quads && (rc = rows_for(P->ctx, P->dose))) return rc;
   return plan_fit(P);
 }
 
@@ -556,7 +578,7 @@ int plan_use(imrt_plan* P, int nt = 1) {
 // partition.  The workgroup-wide forward visits every row: no constant then.
 double plan_skip_objective(imrt_plan* P, bool quads) {
   const imrt_dose* D = P->dose;
-  if (P->ctx->tune.fwd_wave == 0) return 0.0;
+  if (!quads && P->ctx->tune.fwd_wave == 0) return 0.0;
   const int64_t epoch = quads ? D->quad_epoch : D->row_epoch;
   imrt_plan::Skip& K = P->skip[quads ? 1 : 0];
   const auto& gaps = quads ? D->qgaps : D->gaps;
@@ -737,9 +759,9 @@ int ensure_buffers(imrt_plan* P, int residuals, int iterates, bool quads = false
 // Objective (and optionally dose/residual) of x on the plan's stream, the
 // float64 total into *total.  The one-read pass writes the dose in the
 // caller's voxel order and no residual, the forward pass in its own order.
-int eval_forward(imrt_plan* P, const float* x, float* dose_out, float* r_out, double* total) {
+int eval_forward(imrt_plan* P, bool quads, const float* x, float* dose_out, float* r_out, double* total) {
   const imrt_dose* D = P->dose;
-  if (one_read(P->ctx, D, 1, P->nstruct)) {
+  if (quads) {
     FwdArgs a = base_quad(D, QM_EVAL);
     set_quad_penalties(a, P);
     a.x = x;
@@ -1253,15 +1275,14 @@ int imrt_dose_apply(const imrt_dose* D, const float* x_dev, float* d_dev) {
   if (!D || !x_dev || !d_dev) return set_error(IMRT_EINVAL, "dose, x or d is NULL");
   int rc = use_device(D->ctx);
   if (rc) return rc;
-  const bool quads = one_read(D->ctx, D, 1, 0);
-  if (quads) {
+  if (one_product(D->ctx, D, 0, false)) {
     FwdArgs a = base_quad(D, QM_PLAIN);
     a.x = x_dev;
     a.partials = D->partials;
     set_quad_dose(a, D, d_dev);
     return launch_quad(D->ctx, a, 1, forward_waves(1, D->fwd_waves), quad_grid(D, 1));
   }
-  if ((rc = ensure_rows(D))) return rc;
+  if ((rc = rows_for(D->ctx, D))) return rc;
   FwdArgs a = base_fwd(D);
   a.mode = FWD_PLAIN;
   a.x = x_dev;
@@ -1432,14 +1453,14 @@ int imrt_set_voxel_targets(imrt_plan* P, const float* T_under, const float* T_ov
 }
 
 int imrt_evaluate_objective(imrt_plan* P, const float* x_dev, double* G_out, float* dose_dev) {
-  int rc = plan_use(P);
+  bool quads = false;
+  int rc = plan_use(P, &quads);
   if (rc) return rc;
   if (!x_dev || !G_out) return set_error(IMRT_EINVAL, "x or G_out is NULL");
   const imrt_dose* D = P->dose;
-  const bool quads = one_read(P->ctx, D, 1, P->nstruct);
   if (quads) {
     // (the total goes to pinned host memory, with no copy of its own)
-    if ((rc = eval_forward(P, x_dev, dose_dev, nullptr, P->misc_host))) return rc;
+    if ((rc = eval_forward(P, true, x_dev, dose_dev, nullptr, P->misc_host))) return rc;
     IMRT_HIP(hipStreamSynchronize(P->ctx->stream));
     *G_out = P->misc_host[0];
     return IMRT_OK;
@@ -1448,7 +1469,7 @@ int imrt_evaluate_objective(imrt_plan* P, const float* x_dev, double* G_out, flo
   if ((rc = use_device(P->ctx))) return rc;
   // rows the wave blocks skip have no nonzeros: their dose is 0
   if (d_int && !D->gaps.empty() && P->ctx->tune.fwd_wave && (rc = launch_zero(P->ctx, d_int, D->nv))) return rc;
-  if ((rc = eval_forward(P, x_dev, d_int, nullptr, P->misc))) return rc;
+  if ((rc = eval_forward(P, false, x_dev, d_int, nullptr, P->misc))) return rc;
   if (dose_dev && D->vox && (rc = launch_permute(P->ctx, P->vtmp, D->vox, D->nv, dose_dev, true))) return rc;
   if ((rc = fetch_misc(P, 1))) return rc;
   *G_out = P->misc_host[0];
@@ -1456,11 +1477,12 @@ int imrt_evaluate_objective(imrt_plan* P, const float* x_dev, double* G_out, flo
 }
 
 int imrt_gradient(imrt_plan* P, const float* x_dev, float* g_dev, double* G_out) {
-  int rc = plan_use(P);
+  bool quads = false;
+  int rc = plan_use(P, &quads);
   if (rc) return rc;
   if (!x_dev || !g_dev) return set_error(IMRT_EINVAL, "x or g is NULL");
   if ((rc = use_device(P->ctx))) return rc;
-  if (one_read(P->ctx, P->dose, 1, P->nstruct)) {
+  if (quads) {
     double* total = G_out ? P->misc_host : P->misc;
     if ((rc = quad_gradient(P, x_dev, g_dev, P->fwd_partials, P->q_acc, P->q_unit, P->vtmp, total))) return rc;
     if (G_out) {
@@ -1468,7 +1490,7 @@ int imrt_gradient(imrt_plan* P, const float* x_dev, float* g_dev, double* G_out)
       *G_out = P->misc_host[0];
     }
     return IMRT_OK;
-  } else if ((rc = ensure_buffers(P, 1, 1)) || (rc = eval_forward(P, x_dev, nullptr, P->rbuf[0], P->misc)) ||
+  } else if ((rc = ensure_buffers(P, 1, 1)) || (rc = eval_forward(P, false, x_dev, nullptr, P->rbuf[0], P->misc)) ||
              (rc = adjoint_into(P->ctx, P->dose, P->rbuf[0], 2.0, g_dev))) {
     return rc;
   }
@@ -1487,7 +1509,7 @@ int imrt_gradient_noalloc(imrt_plan* P, const float* x_dev, float* g_dev, double
   unsigned char* base = noalloc_scratch(P->ctx->device);
   if (!base) return set_error(IMRT_EINVAL, "no scratch for this device (create the context first)");
   const imrt_dose* D = P->dose;
-  if (!one_read(P->ctx, D, 1, P->nstruct) && (rc = ensure_rows(D))) return rc;   // (there, but after an option's change)
+  const bool quads = one_product(P->ctx, D, P->nstruct, true);
   const int grid = forward_grid(P->ctx, D, 1);
   // scratch layout, every part 256-byte aligned: residual (nv floats),
   // forward objective partials (grid doubles), adjoint pieces (2 per
@@ -1507,7 +1529,7 @@ int imrt_gradient_noalloc(imrt_plan* P, const float* x_dev, float* g_dev, double
   double* parts = reinterpret_cast<double*>(base + off_part);
   double* pieces = reinterpret_cast<double*>(base + off_pieces);
   double* total = reinterpret_cast<double*>(base + off_total);
-  if (one_read(P->ctx, D, 1, P->nstruct)) {
+  if (quads) {
     // the second half of the scratch: total, unit, objective partials, then
     // the column sums, whose size the partition bounds
     const size_t qgrid = static_cast<size_t>(quad_grid(D, 1));
@@ -1569,7 +1591,8 @@ int imrt_project(imrt_plan* P, const float* x_dev, const float* g_dev, double la
 
 int imrt_estimate_lambda0(imrt_plan* P, const float* v0_dev, int32_t iters, double* lambda0_out,
                           double* sigma_out) {
-  int rc = plan_use(P);
+  bool quads = false;
+  int rc = plan_use(P, &quads);
   if (rc) return rc;
   if (!v0_dev || iters < 0) return set_error(IMRT_EINVAL, "v0 is NULL or iters < 0");
   if ((rc = use_device(P->ctx))) return rc;
@@ -1578,7 +1601,6 @@ int imrt_estimate_lambda0(imrt_plan* P, const float* v0_dev, int32_t iters, doub
   float* v = P->xbuf[0];
   float* w = P->gk;
   if ((rc = launch_normalize(C, v0_dev, D->nb, v, P->misc + 1))) return rc;
-  const bool quads = one_read(C, D, 1, P->nstruct);
   if (quads) {
     // D^T D v and its squared norm's partial sums in two launches; the next
     // pass divides by the norm while it stages the vector
@@ -1642,8 +1664,9 @@ void number_trace(const imrt_solve_params* prm, int n) {
 // Checks of a solve's arguments, x_1 >= 0 (host copy), the plan's buffers and
 // trace, and the initial solver state.
 int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev, int* nt_out, int* cap_out,
-                  SolverState* init_out) {
-  int rc = plan_use(P);
+                  bool* quads_out, SolverState* init_out) {
+  bool quads = false;
+  int rc = plan_use(P, &quads);
   if (rc) return rc;
   if (!prm || !x_dev) return set_error(IMRT_EINVAL, "params or x is NULL");
   if (!(prm->eps > 0.0 && prm->eps < 1.0)) return set_error(IMRT_EINVAL, "eps must lie in (0, 1)");
@@ -1668,8 +1691,8 @@ int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev
   const imrt_dose* D = P->dose;
   imrt_ctx* C = P->ctx;
   hipStream_t s = C->stream;
-  const bool quads = one_read(C, D, nt, P->nstruct);
-  if (!quads && (rc = plan_use(P, nt))) return rc;
+  quads = one_read(C, D, nt, P->nstruct);
+  if (!quads && ((rc = rows_for(C, D)) || (rc = plan_fit(P)))) return rc;
   if (forward_lds_bytes(D->nb, nt, P->nstruct, C->tune.fwd_wave != 0, D->fwd_st, D->fwd_waves) > C->max_lds)
     return set_error(IMRT_EUNSUPPORTED, "nb * trials_per_pass exceeds the LDS budget of the forward pass");
 
@@ -1714,15 +1737,16 @@ int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev
   init.delta = prm->delta;
   *nt_out = nt;
   *cap_out = cap;
+  *quads_out = quads;
   *init_out = init;
   return IMRT_OK;
 }
 
 // The forward and adjoint arguments of a plan's solve passes (without the
 // state pointers, which depend on the pass).
-void solve_args(imrt_plan* P, int nt, int grid, int cap, FwdArgs& fa, AdjArgs& aa) {
+void solve_args(imrt_plan* P, bool quads, int nt, int grid, int cap, FwdArgs& fa, AdjArgs& aa) {
   const imrt_dose* D = P->dose;
-  if (one_read(P->ctx, D, nt, P->nstruct)) {
+  if (quads) {
     fa = base_quad(D, QM_SOLVE);
     fa.grid = grid;
     set_quad_penalties(fa, P);
@@ -1780,17 +1804,16 @@ void solve_args(imrt_plan* P, int nt, int grid, int cap, FwdArgs& fa, AdjArgs& a
 }
 
 // Workgroups of a solve's forward (or one-read) pass.
-int solve_grid(const imrt_plan* P, int nt) {
-  return one_read(P->ctx, P->dose, nt, P->nstruct) ? quad_grid(P->dose, nt)
-                                                    : std::min(forward_grid(P->ctx, P->dose, nt), P->fwd_cap);
+int solve_grid(const imrt_plan* P, bool quads, int nt) {
+  return quads ? quad_grid(P->dose, nt) : std::min(forward_grid(P->ctx, P->dose, nt), P->fwd_cap);
 }
 
 // x_1 into the buffers a solve starts from: iterate 0, which in the one-read
 // pass is also the trial that the initial evaluation takes (x_k: buffer nt).
-hipError_t solve_start(imrt_plan* P, int nt, const float* x) {
+hipError_t solve_start(imrt_plan* P, bool quads, int nt, const float* x) {
   const size_t bytes = sizeof(float) * P->dose->nb;
   hipError_t e = hipMemcpyAsync(P->xbuf[0], x, bytes, hipMemcpyDeviceToDevice, P->ctx->stream);
-  if (e == hipSuccess && one_read(P->ctx, P->dose, nt, P->nstruct))
+  if (e == hipSuccess && quads)
     e = hipMemcpyAsync(P->xbuf[nt], x, bytes, hipMemcpyDeviceToDevice, P->ctx->stream);
   return e;
 }
@@ -1803,9 +1826,9 @@ hipError_t solve_start(imrt_plan* P, int nt, const float* x) {
 // 16,060.
 constexpr int64_t kWholeSums = 1 << 14;
 
-bool whole_passes(const imrt_plan* P, const imrt_solve_params* prm, int nt) {
+bool whole_passes(const imrt_plan* P, bool quads, const imrt_solve_params* prm, int nt) {
   const imrt_dose* D = P->dose;
-  return nt == 1 && prm->profile == 0 && one_read(P->ctx, D, 1, P->nstruct) && D->fwd_waves == 16 && D->nb <= 16 * 64 &&
+  return nt == 1 && prm->profile == 0 && quads && D->fwd_waves == 16 && D->nb <= 16 * 64 &&
          static_cast<int64_t>(quad_grid(D, 1)) * D->nb <= kWholeSums;
 }
 
@@ -1848,13 +1871,14 @@ int fit_whole(imrt_plan* P, WholeSet (&set)[2]) {
 int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_solve_result* res) {
   if (!res) return set_error(IMRT_EINVAL, "result is NULL");
   int nt = 1, cap = 0, rc;
+  bool quads = false;
   SolverState init{};
-  if ((rc = solve_prepare(P, prm, x_dev, &nt, &cap, &init))) return rc;
+  if ((rc = solve_prepare(P, prm, x_dev, &nt, &cap, &quads, &init))) return rc;
   const imrt_dose* D = P->dose;
   imrt_ctx* C = P->ctx;
   hipStream_t s = C->stream;
   P->st_host[0] = init;
-  const bool whole = whole_passes(P, prm, nt);
+  const bool whole = whole_passes(P, quads, prm, nt);
   WholeSet set[2];
   if (whole && (rc = fit_whole(P, set))) return rc;
 
@@ -1900,7 +1924,7 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
   if (e == hipSuccess) e = hipEventRecord(ev_start, s);
   if (e == hipSuccess) e = hipMemcpyAsync(P->st, &P->st_host[0], sizeof(SolverState), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(P->st + 1, &P->st_host[0], sizeof(SolverState), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = solve_start(P, nt, x_dev);
+  if (e == hipSuccess) e = solve_start(P, quads, nt, x_dev);
   if (whole) {
     // the first copy: x_1 as iterate and as the trial of the initial evaluation
     const size_t nb4 = sizeof(float) * D->nb;
@@ -1913,11 +1937,10 @@ int imrt_solve(imrt_plan* P, const imrt_solve_params* prm, float* x_dev, imrt_so
     return hip_error(e, "solve setup");
   }
 
-  const bool quads = one_read(C, D, nt, P->nstruct);
-  const int grid = solve_grid(P, nt);
+  const int grid = solve_grid(P, quads, nt);
   FwdArgs fa;
   AdjArgs aa;
-  solve_args(P, nt, grid, cap, fa, aa);
+  solve_args(P, quads, nt, grid, cap, fa, aa);
 
   // The two state copies alternate: pass n reads st[n % 2] and writes st[(n + 1) % 2].
   long long pass = 0;
@@ -2178,7 +2201,9 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
   std::vector<SolverState> init(n);
   int rc;
   for (int i = 0; i < n; ++i) {
-    if ((rc = solve_prepare(plans[i], &params[i], x_dev[i], &nt[i], &cap[i], &init[i]))) return rc;
+    bool one = false;
+    if ((rc = solve_prepare(plans[i], &params[i], x_dev[i], &nt[i], &cap[i], &one, &init[i]))) return rc;
+    quads[i] = one;
     if (nt[i] != nt[0]) return set_error(IMRT_EINVAL, "all plans of a batch must use the same trials_per_pass");
     if (plans[i]->dose->adj_grid >= 65536) return set_error(IMRT_EUNSUPPORTED, "adjoint grid too large for a batch");
   }
@@ -2213,8 +2238,7 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
   size_t lds = 0, qlds = 0;
   for (int i = 0; i < n; ++i) {
     imrt_plan* P = plans[i];
-    quads[i] = one_read(C, P->dose, nt[i], P->nstruct);
-    fgrid[i] = solve_grid(P, nt[i]);
+    fgrid[i] = solve_grid(P, quads[i], nt[i]);
     agrid[i] = quads[i] ? step_grid(P->dose->nb) : P->dose->adj_grid;
     if (quads[i]) qlds = std::max(qlds, quad_lds_bytes(P->dose->nb, nt[i], P->nstruct, QM_SOLVE));
     else lds = std::max(lds, forward_lds_bytes(P->dose->nb, nt[i], P->nstruct, true, fst, fwv));
@@ -2237,7 +2261,7 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
   if (dev_alloc(&B.st, 2 * static_cast<size_t>(n)) || dev_alloc(&B.fargs, n) || dev_alloc(&B.aargs, n))
     return IMRT_ENOMEM;
   for (int i = 0; i < n; ++i) {
-    solve_args(plans[i], nt[i], fgrid[i], cap[i], fa[i], aa[i]);
+    solve_args(plans[i], quads[i], nt[i], fgrid[i], cap[i], fa[i], aa[i]);
     fa[i].st_in = B.st + 2 * i;
     fa[i].st_out = B.st + 2 * i + 1;
     aa[i].st_in = B.st + 2 * i + 1;
@@ -2293,7 +2317,7 @@ int imrt_solve_batch(int32_t n, imrt_plan* const* plans, const imrt_solve_params
   if (e == hipSuccess) e = hipMemcpyAsync(B.fargs, fa.data(), sizeof(FwdArgs) * n, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(B.aargs, aa.data(), sizeof(AdjArgs) * n, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = upload(sl);
-  for (int i = 0; i < n && e == hipSuccess; ++i) e = solve_start(plans[i], nt[i], x_dev[i]);
+  for (int i = 0; i < n && e == hipSuccess; ++i) e = solve_start(plans[i], quads[i], nt[i], x_dev[i]);
   // the host vectors above must outlive the copies
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_error(e, "batch setup");

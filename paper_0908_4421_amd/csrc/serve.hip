@@ -21,10 +21,10 @@
 // Shared with imrt_solve (api.hip, which defines them with C linkage).
 extern "C" {
 int solve_prepare(imrt_plan* P, const imrt_solve_params* prm, const float* x_dev, int* nt_out, int* cap_out,
-                  imrt::SolverState* init_out);
-void solve_args(imrt_plan* P, int nt, int grid, int cap, imrt::FwdArgs& fa, imrt::AdjArgs& aa);
-int solve_grid(const imrt_plan* P, int nt);
-hipError_t solve_start(imrt_plan* P, int nt, const float* x);
+                  bool* quads_out, imrt::SolverState* init_out);
+void solve_args(imrt_plan* P, bool quads, int nt, int grid, int cap, imrt::FwdArgs& fa, imrt::AdjArgs& aa);
+int solve_grid(const imrt_plan* P, bool quads, int nt);
+hipError_t solve_start(imrt_plan* P, bool quads, int nt, const float* x);
 }
 
 using namespace imrt;
@@ -297,13 +297,12 @@ bool admit(imrt_server* S, Pending& p, int slot) {
   int cap = 0;
   SolverState init{};
   p.params.profile = 0;
-  if ((rc = solve_prepare(L.plan, &p.params, L.x, &L.nt, &cap, &init))) return fail(rc);
+  if ((rc = solve_prepare(L.plan, &p.params, L.x, &L.nt, &cap, &L.quads, &init))) return fail(rc);
   if (S->ctx.tune.fwd_wave == 0) return fail(set_error(IMRT_EUNSUPPORTED, "serving needs fwd_wave = 1"));
-  L.quads = one_read(C, D, L.nt, L.plan->nstruct);
-  L.grid = solve_grid(L.plan, L.nt);
+  L.grid = solve_grid(L.plan, L.quads, L.nt);
   FwdArgs fa;
   AdjArgs aa;
-  solve_args(L.plan, L.nt, L.grid, cap, fa, aa);
+  solve_args(L.plan, L.quads, L.nt, L.grid, cap, fa, aa);
   L.trace_dst = p.params.trace;
   L.trace_cap = cap;
   L.resume = p.params.resume;
@@ -317,7 +316,7 @@ bool admit(imrt_server* S, Pending& p, int slot) {
   e = hipMemcpyAsync(S->st + 2 * slot, two, sizeof(two), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(S->fargs + slot, &fa, sizeof(fa), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(S->aargs + slot, &aa, sizeof(aa), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = solve_start(L.plan, L.nt, L.x);
+  if (e == hipSuccess) e = solve_start(L.plan, L.quads, L.nt, L.x);
   if (e != hipSuccess) return fail(hip_error(e, "admission upload"));
   // the initial evaluation G(x_1), alone (the batch then continues with
   // (adjoint, forward) groups)

@@ -1,13 +1,14 @@
 """What a matrix with the quad form gets on first use (the row blocks of the
-two separate passes, after fwd_wave was set to 0), while plans of several
-contexts and threads share it."""
+two separate passes, after fwd_wave was set to 0): calls that allocate nothing
+or are captured do without it, and plans of several contexts and threads share
+the matrix meanwhile."""
 import threading
 
 import numpy as np
 import pytest
 import scipy.sparse as sp
 
-from gpu_util import banner, to_dev, to_host
+from gpu_util import banner, rel_normwise, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -34,6 +35,92 @@ def _plan(ctx, dose, sid):
     plan.set_structures(sid, 2)
     plan.set_penalties(TABLE)
     return plan
+
+
+@pytest.mark.parametrize("call", ["noalloc", "gradient", "apply"])
+def test_captured_after_the_option_changed(call):
+    """Each replay of a captured call gives the eager result, with eager work
+    between the replays."""
+    import torch
+    from paper_0908_4421_amd import imrt
+    from paper_0908_4421_amd.imrt import Context
+    D, sid, x0 = _problem()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        ctx = Context(0, stream=s.cuda_stream, one_read=2)
+        dose = _dose(ctx, D)
+        plan = _plan(ctx, dose, sid)
+        x = to_dev(x0)
+        plan.gradient(x)
+        out = torch.empty(D.shape[0] if call == "apply" else D.shape[1], device="cuda")
+    ctx.set_option("fwd_wave", 0)
+
+    def enqueue():
+        if call == "noalloc":
+            plan.gradient_noalloc(x, out, want_G=False)
+        elif call == "apply":
+            dose.apply(x, out)
+        else:
+            imrt._check(imrt.load().imrt_gradient(plan.handle, x.data_ptr(), out.data_ptr(), None), "imrt_gradient")
+
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        enqueue()
+    rng = np.random.default_rng(1)
+    for k in range(4):
+        xk = rng.uniform(0.0, 0.4, D.shape[1]).astype(np.float32)
+        with torch.cuda.stream(s):
+            x.copy_(torch.from_numpy(xk))
+            out.fill_(float("nan"))
+            graph.replay()
+        got = to_host(out)
+        z = D.astype(np.float64) @ xk.astype(np.float64)
+        if call == "apply":
+            want = z
+        else:
+            t = np.array(TABLE)[sid]
+            want = 2.0 * (D.T.astype(np.float64) @ (t[:, 2] * np.minimum(z - t[:, 0], 0) +
+                                                   t[:, 3] * np.maximum(z - t[:, 1], 0)))
+        assert rel_normwise(got, want) <= 8 * 28 * 2.0 ** -24
+        with torch.cuda.stream(s):   # eager work: the same call, and one that makes the row blocks
+            enqueue()
+        assert rel_normwise(to_host(out), want) <= 8 * 28 * 2.0 ** -24
+        if k == 1:
+            plan.objective(x)
+
+
+def test_noalloc_allocates_nothing():
+    import torch
+    from paper_0908_4421_amd.imrt import Context
+    D, sid, x0 = _problem(nv=400003, nb=60, row=12)
+    ctx = Context(0, one_read=2)
+    plan = _plan(ctx, _dose(ctx, D), sid)
+    x, g = to_dev(x0[:60]), torch.empty(60, device="cuda")
+    G = plan.gradient_noalloc(x, g)
+    ctx.set_option("fwd_wave", 0)
+    free = torch.cuda.mem_get_info()[0]
+    again = plan.gradient_noalloc(x, g)
+    assert torch.cuda.mem_get_info()[0] == free and again == G
+
+
+def test_sixteen_bit_storage_is_refused_as_before():
+    import torch
+    from paper_0908_4421_amd import imrt
+    from paper_0908_4421_amd.imrt import Context
+    D, sid, x0 = _problem()
+    ctx = Context(0, one_read=2)
+    dose = _dose(ctx, D, "bf16")
+    plan = _plan(ctx, dose, sid)
+    ctx.set_option("fwd_wave", 0)
+    x, g = to_dev(x0), torch.empty(D.shape[1], device="cuda")
+    for call in (lambda: plan.gradient_noalloc(x, g), lambda: plan.gradient(x), lambda: plan.objective(x),
+                 lambda: dose.apply(x)):
+        with pytest.raises(imrt.ImrtError) as e:
+            call()
+        assert e.value.code == imrt.IMRT_EUNSUPPORTED
+    ctx.set_option("fwd_wave", 1)
+    assert np.isfinite(plan.objective(x))
 
 
 def test_contexts_and_threads_share_a_matrix():
