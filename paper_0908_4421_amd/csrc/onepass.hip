@@ -90,8 +90,8 @@ __device__ __forceinline__ double pow2(int e) {
 template <int ST>
 using QuadVal = std::conditional_t<coded(ST), uint2, float4>;
 
-// A value of an entry and whether it is one of D's (an empty place of a quad
-// holds -0, which no caller's value can be told from 0 otherwise).
+// Whether a value of an entry is none of D's: an empty place of a quad holds
+// -0, and a stored -0 is kept as 0.
 template <int ST>
 __device__ __forceinline__ bool quad_hole(const QuadVal<ST>& v, int u) {
   if constexpr (coded(ST)) return half_of(v, u) == 0x8000u;

@@ -112,6 +112,7 @@ __global__ __launch_bounds__(kThreads) void quad_fill_kernel(const int32_t* row_
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           h[u] = k[u] >= 0 ? val16[k[u]] : 0x8000u;
+          if (k[u] >= 0 && h[u] == 0x8000u) h[u] = 0;   // (a stored -0 is no hole)
           if (k[u] >= 0) rs[u] += stored<ST>(val, val16, k[u]);
         }
         static_cast<uint2*>(q_val)[e] = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(kThreads) void quad_fill_kernel(const int32_t* row_
         float v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          v[u] = k[u] >= 0 ? val[k[u]] : -0.0f;
+          v[u] = k[u] >= 0 ? val[k[u]] + 0.0f : -0.0f;   // (a stored -0 is no hole)
           if (k[u] >= 0) rs[u] += static_cast<double>(v[u]);
         }
         static_cast<float4*>(q_val)[e] = make_float4(v[0], v[1], v[2], v[3]);

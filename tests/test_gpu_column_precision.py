@@ -289,3 +289,31 @@ def test_served_plans_with_weights_apart():
         x = to_dev(np.ones(nb, np.float32))
         res, _ = plan.solve(x, eps=1e-4, alpha=2.0, lambda0=lam, max_iter=60, fixed_iters=True)
         assert (res.iterations, res.status, res.G_final, to_host(x).tobytes()) == (it, status, G, xb)
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_stored_negative_zeros(storage):
+    """A stored -0 is a nonzero place like a stored 0: times infinity it is
+    NaN, as in the two separate passes, and with finite vectors it adds
+    nothing."""
+    import torch
+    rng = np.random.default_rng(13)
+    D = _blocks(14).tocsr()
+    D.data[:] = 1.0
+    zero = rng.random(D.nnz) < 0.2
+    D.data[zero] = np.where(rng.random(zero.sum()) < 0.5, -0.0, 0.0)
+    sid = rng.integers(0, 2, NV).astype(np.uint8)
+    for spike in (0.5, np.inf):
+        x = rng.uniform(0.0, 1.0, NB).astype(np.float32)
+        x[4] = x[22] = spike
+        out = {}
+        for mode in (0, 2):
+            lib, plan = _plan(D, TABLE, sid, mode, storage)
+            dose = torch.empty(NV, device="cuda")
+            G = plan.objective(to_dev(x), dose)
+            out[mode] = (to_host(dose), to_host(lib.apply(to_dev(x))), to_host(plan.gradient(to_dev(x))[0]))
+        assert np.isinf(spike) == bool(np.isnan(out[0][0]).any())
+        for a, b in zip(out[2], out[0]):
+            assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b))
+            fin = np.isfinite(b)
+            assert np.allclose(a[fin], b[fin], rtol=1e-5, atol=1e-5 * np.max(np.abs(b[fin]), initial=0.0))
