@@ -336,8 +336,9 @@ IMRT_API int imrt_gradient(imrt_plan* plan, const float* x_dev, float* g_dev, do
 
 /* Size of the per-device scratch of imrt_gradient_noalloc (bytes): the
  * residual (4 nv bytes) plus a few kilobytes of partial sums, so plans of up
- * to about 4 million voxels.  (A one-read pass keeps no residual but its
- * workgroups' column sums there, which its partition keeps within it.) */
+ * to about 4 million voxels.  (The library holds twice as much: a one-read
+ * pass keeps its workgroups' column sums in a second part of this size, which
+ * its partition keeps within it.) */
 #define IMRT_NOALLOC_SCRATCH_BYTES (16u << 20)
 
 /* imrt_gradient for callers that cannot allocate device memory (code under

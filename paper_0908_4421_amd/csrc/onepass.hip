@@ -998,9 +998,9 @@ __device__ __forceinline__ void put_sum(StepSums& sh, const ColTotal& T) {
 // After put_sum by all, in the first wave: the total of column c = sl.w * 16 +
 // lane % 16 in every lane, in the products' own scale.  Columns whose integers
 // are not precise enough (again: there are some) are summed again by all
-// waves.
+// waves, where the totals are wanted.
 __device__ __forceinline__ double col_total(const AdjArgs& a, StepSums& sh, double unit, const float* r, const float* x,
-                                            int c, bool& again) {
+                                            int c, bool want, bool& again) {
   const int lane = threadIdx.x & 63, wv = uniform(threadIdx.x >> 6), i = lane & (kStepCols - 1), p0 = lane / kStepCols;
   __syncthreads();
   bool bad = false;
@@ -1021,12 +1021,12 @@ __device__ __forceinline__ double col_total(const AdjArgs& a, StepSums& sh, doub
     bad = c < a.nb && imprecise(ColTotal{s, w >> 6, w & 63}, unit, a.enough);
     total = static_cast<double>(static_cast<long long>(s)) * unit;
     const uint64_t mask = __ballot(bad);
-    if (lane == 0) sh.bad = static_cast<uint32_t>(mask) & ((1u << kStepCols) - 1);
+    again = mask != 0;
+    if (lane == 0) sh.bad = want ? static_cast<uint32_t>(mask) & ((1u << kStepCols) - 1) : 0;
   }
   __syncthreads();
   const uint32_t mask = uniform(static_cast<int>(sh.bad));
-  again = mask != 0;
-  if (again) {
+  if (mask != 0) {
     for (int k = 0; k < kStepCols; ++k)
       if (mask >> k & 1) {
         const double t = exact_column(a.again, r, x, c - i + k, wv, kStepWaves);
@@ -1131,8 +1131,9 @@ __device__ __forceinline__ void step_pass(const AdjArgs& a, const Slot sl) {
 #pragma unroll
   for (int k = 1; k < NT; ++k) r = (q == k) ? a.rbuf[k] : r;
   put_sum(sh, col_sum(a, ra, NT, q, c, p0, CP));
-  bool again;
-  const double total = col_total(a, sh, u, uniform(stored) > 0 ? r : nullptr, a.q_x + static_cast<size_t>(q) * a.nb, c, again);
+  bool again = false;
+  const double total = col_total(a, sh, u, uniform(stored) > 0 ? r : nullptr, a.q_x + static_cast<size_t>(q) * a.nb, c,
+                                 decides && !was_done && st.phase == PH_NEED_GRAD, again);
   if (wv != 0) return;
   if (again && lane == 0) a.st_out->again = st.n_fwd;   // (the passes decided on so far)
   if (sl.w == 0 && lane == 0) {
@@ -1216,8 +1217,8 @@ __global__ __launch_bounds__(kStepThreads) void reduce_kernel(AdjArgs a, double*
   const double unit = load_f64(make_rsrc(a.q_unit, 8u), 0);
   const double factor = col_factor(a, c);
   put_sum(sh, col_sum(a, ra, 1, 0, c, p0, CP));
-  bool again;
-  const double total = col_total(a, sh, unit, a.rbuf[0], nullptr, c, again);
+  bool again = false;
+  const double total = col_total(a, sh, unit, a.rbuf[0], nullptr, c, true, again);
   if (tid >= 64) return;
   const float g = static_cast<float>(factor * total);
   double sq = 0.0;

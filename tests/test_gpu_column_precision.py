@@ -317,3 +317,42 @@ def test_stored_negative_zeros(storage):
             assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b))
             fin = np.isfinite(b)
             assert np.allclose(a[fin], b[fin], rtol=1e-5, atol=1e-5 * np.max(np.abs(b[fin]), initial=0.0))
+
+
+@pytest.mark.parametrize("nt", [1, 2])
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16"])
+def test_solves_with_targets_and_weights_apart(storage, nt):
+    """Columns summed again in every storage, with per-voxel targets: stored
+    residuals and those made from the rows."""
+    from paper_0908_4421_amd.imrt import Plan
+    rng = np.random.default_rng(15)
+    D = _blocks(16)
+    top = np.asarray(D.argmax(axis=0)).ravel()
+    D = D.tolil()
+    for c in range(NB):
+        D[top[c], c] = 1.0      # exact in 16 bits
+    D = D.tocsr()
+    D.sort_indices()
+    sid = np.where(np.arange(NV) < 3 * ROWS, 2, rng.integers(0, 2, NV)).astype(np.uint8)
+    table = TABLE + [(2.0, 2.0, 1e9, 1e9)]
+    T = rng.uniform(1.0, 3.0, NV).astype(np.float32)
+    out = {}
+    for mode in (0, 2):
+        lib, plan = _plan(D, table, sid, mode, storage)
+        plan.set_voxel_targets(T, T + 0.25)
+        lam, _ = plan.lambda0(to_dev(np.ones(NB, np.float32)), 20)
+        args = dict(eps=1e-4, alpha=2.0, max_iter=40, fixed_iters=True, trials_per_pass=nt)
+        runs = []
+        for profile in (0, 3):
+            x = to_dev(np.full(NB, 0.4, np.float32))
+            res, tr = plan.solve(x, lambda0=4 * lam, trace=True, profile=profile, **args)
+            runs.append((tr, to_host(x).tobytes(), res.G_final))
+        assert runs[0] == runs[1]
+        xs = [to_dev(np.full(NB, 0.4, np.float32))]
+        Plan.solve_batch([plan], xs, lambda0s=[4 * lam], **args)
+        assert to_host(xs[0]).tobytes() == runs[0][1]
+        out[mode] = runs[0]
+    for (k, m, s, _, G), (k2, m2, s2, _, G2) in zip(out[0][0], out[2][0]):
+        assert (k, m, s) == (k2, m2, s2) and abs(G - G2) <= 1e-5 * G2
+    a, b = (np.frombuffer(out[m][1], np.float32) for m in (0, 2))
+    assert np.allclose(a, b, rtol=1e-4, atol=1e-6)
