@@ -20,7 +20,8 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 KERNEL_SOURCES = tuple("paper_0908_4421_amd/csrc/" + f for f in (
-    "forward.hip", "adjoint.hip", "onepass.hip", "decide.h", "pass_common.h", "imrt_internal.h"))
+    "forward.hip", "adjoint.hip", "onepass.hip", "decide.h", "pass_common.h", "imrt_internal.h",
+    "quad_layout.h"))
 # counter summaries per workload (by phantom name)
 TRAFFIC_PROFILES = {
     "prostate_160x104x80_2.5mm_9field": os.path.join(ROOT, "profiles", "hbm_traffic_fwd_adj_prostate_160x104x80.txt"),

@@ -219,9 +219,10 @@ IMRT_API int imrt_ctx_stream(const imrt_ctx* ctx, void** hip_stream_out);
  *   "one_read"       1 (default): matrices created afterwards, of at most 8,191
  *                    beamlets, also keep the quad form (four rows share one
  *                    list of columns) where reading it once costs no more
- *                    bytes than the CSR and the CSC together; objectives,
- *                    gradients, step sizes, solves and doses then take the
- *                    one-read pass.  2: wherever it fits; 0: never
+ *                    bytes than the CSR and the CSC together, and the device
+ *                    has room for it beside them (a third more memory);
+ *                    objectives, gradients, step sizes, solves and doses then
+ *                    take the one-read pass.  2: wherever it fits; 0: never
  *   "stream_nt"      cache policy of the matrix streams in the passes of
  *                    imrt_solve and imrt_solve_batch: 0 default policy, 1
  *                    non-temporal, 2 (default) non-temporal when the CSR and
@@ -297,7 +298,8 @@ IMRT_API int imrt_dose_storage(const imrt_dose* dose, int32_t* storage);
  * keeps the two separate passes (option "one_read").  Either may be NULL. */
 IMRT_API int imrt_dose_one_read(const imrt_dose* dose, int64_t* entries, int32_t* workgroups);
 
-/* d = D x (CSR, voxel-parallel).  x_dev: nb floats; d_dev: nv floats. */
+/* d = D x (the quad form where D keeps it, else the CSR; voxel-parallel).
+ * x_dev: nb floats; d_dev: nv floats. */
 IMRT_API int imrt_dose_apply(const imrt_dose* dose, const float* x_dev, float* d_dev);
 /* y = D^T r (CSC, beamlet-parallel).  r_dev: nv floats; y_dev: nb floats. */
 IMRT_API int imrt_dose_apply_transpose(const imrt_dose* dose, const float* r_dev, float* y_dev);
@@ -449,7 +451,9 @@ IMRT_API int imrt_plan_destroy(imrt_plan* plan);
  * server builds take the partition of the context's per-plan targets
  * "serve_adjoint_workgroups" and "serve_forward_workgroups" (read at server
  * creation; imrt_dose_repartition_targets); a result equals imrt_solve's on
- * a matrix with that partition. */
+ * a matrix with that partition.  The quad form (option "one_read") counts in
+ * the budget, but never keeps a matrix or a request out of it: it is given up
+ * where room is short, and a result is then that of a matrix without it. */
 typedef struct imrt_server imrt_server;
 
 typedef struct {

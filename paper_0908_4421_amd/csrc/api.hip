@@ -1820,11 +1820,11 @@ hipError_t solve_start(imrt_plan* P, bool quads, int nt, const float* x) {
 
 // A plan solved alone takes its steps and passes in one launch where the step
 // is small enough for every workgroup to repeat: a column per thread, and at
-// most kWholeSums column sums to add.  Launches set the time of such plans:
-// an iteration takes 9.3 us against 10.8 in two launches at 3,840 sums, 9.6
-// against 11.1 at 7,224, 10.9 against 11.2 at 11,232, 10.9 against 10.9 at
-// 16,060.
-constexpr int64_t kWholeSums = 1 << 14;
+// most kWholeSums column sums to add and check.  Launches set the time of such
+// plans: an iteration takes 10.1 us against 11.2 in two launches at 3,840
+// sums, 10.5 against 11.6 at 7,224, 11.8 against 11.4 at 9,744, 11.7 against
+// 11.7 at 11,232, 11.8 against 11.3 at 16,060.
+constexpr int64_t kWholeSums = 1 << 13;
 
 bool whole_passes(const imrt_plan* P, bool quads, const imrt_solve_params* prm, int nt) {
   const imrt_dose* D = P->dose;

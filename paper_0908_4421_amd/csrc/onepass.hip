@@ -18,10 +18,10 @@
 // What bounds it: the read of D, 18 bytes per entry of float32 values (10
 // with 16-bit codes); at the paper's scale an entry holds 3.3 nonzeros, so
 // 5.4 bytes per nonzero where the two separate passes read 6 + 8.
-// Measured per iteration, two separate passes -> one read: 38.2 -> 20.9 us
-// (1.33 M voxels, 2,088 beamlets, 12.1 M nonzeros, float32), 41.9 -> 28.8 us
-// (the same in bfloat16 with two trials a pass), 112.8 -> 53.8 us (143 k
-// voxels, 6,000 beamlets, 41.8 M nonzeros), 212 -> 119 us (32 uneven plans of
+// Measured per iteration, two separate passes -> one read: 38.2 -> 22.0 us
+// (1.33 M voxels, 2,088 beamlets, 12.1 M nonzeros, float32), 41.9 -> 29.2 us
+// (the same in bfloat16 with two trials a pass), 111.6 -> 54.9 us (143 k
+// voxels, 6,444 beamlets, 41.8 M nonzeros), 213 -> 113 us (32 uneven plans of
 // 40.4 M nonzeros together).
 //
 // Column sums are 64-bit integers, in units of 2^-61 times a bound on the
@@ -182,7 +182,8 @@ __device__ __forceinline__ void quad_issue(const Plans& P, const uint2 rec, int 
 }
 
 // Integer nearest to t, |t| < 2^61: high 32 bits, then the exact remainder,
-// each rounded by adding 1.5 * 2^52.
+// each rounded by adding 1.5 * 2^52 (H. S. Warren, Hacker's Delight, 2nd ed.,
+// chapter 17).
 __device__ __forceinline__ unsigned long long to_fixed(double t) {
 #pragma clang fp contract(off)
   constexpr double kMagic = 6755399441055744.0;   // 1.5 * 2^52
@@ -333,8 +334,8 @@ __device__ __forceinline__ Whole whole_step(const FwdArgs& a, const WholeArgs& W
   const int tid = threadIdx.x, lane = tid & 63, nb = a.nb, sg = step_grid(nb);
   // Thread (first, c) adds column c's sums of workgroups first, first + groups,
   // ...: a thread to a column leaves most threads idle and takes several
-  // rounds of loads (73 workgroups of 220 columns: 13.5 us an iteration, 10.9
-  // with the sums shared out).
+  // rounds of loads (73 workgroups of 220 columns, without the check of the
+  // totals: 13.5 us an iteration, 10.9 with the sums shared out).
   int width = 64;
   while (width < nb) width *= 2;
   const int c = tid & (width - 1), first = tid / width, groups = THREADS / width;
@@ -900,8 +901,8 @@ __global__ __launch_bounds__(WAVES * 64, (quad_waves_per_simd<NT, WAVES>())) voi
 // A small plan's iteration in one launch: every workgroup repeats the step
 // for all columns (they are at most one per thread, and the pass's column
 // sums few) instead of waiting for a launch that does it once.  What bounds
-// it: two chains of dependent loads, with a barrier between; 11.5 us an
-// iteration in two launches, 9.2 in one (32,000 voxels, 305 beamlets).
+// it: two chains of dependent loads, with a barrier between; 11.2 us an
+// iteration in two launches, 10.1 in one (32,000 voxels, 160 beamlets).
 template <int ST>
 __global__ __launch_bounds__(16 * 64, 4) void whole_kernel(FwdArgs a, WholeArgs w) {
   quad_pass<1, QM_WHOLE, 16, ST, 0>(OnePlan{a}, Slot{static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x)},
